@@ -217,8 +217,11 @@ __global__ __launch_bounds__(BWD_THREADS) void k_out_bwd(
           for (int j = 0; j < 4; ++j) {
             const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, av[j]),
                                                              __builtin_bit_cast(unsigned, bv[j]), false, false);
-            f[j] = (bf16)__builtin_bit_cast(float, sw[0]);
-            f[4 + j] = (bf16)__builtin_bit_cast(float, sw[1]);
+            // (through integers: a bit cast of an element of the builtin's result reads
+            // element 0 whatever the index, on this compiler)
+            const unsigned u0 = sw[0], u1 = sw[1];
+            f[j] = (bf16)__builtin_bit_cast(float, u0);
+            f[4 + j] = (bf16)__builtin_bit_cast(float, u1);
           }
           wf[kb][c] = f;
         } else {

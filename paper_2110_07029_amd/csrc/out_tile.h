@@ -60,7 +60,10 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float half_swap_max(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__builtin_bit_cast(float, sw[0]), __builtin_bit_cast(float, sw[1]));
+  // (through integers: a bit cast of an element of the builtin's result reads
+  // element 0 whatever the index, on this compiler)
+  const unsigned a = sw[0], b = sw[1];
+  return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
 }
 
 __device__ __forceinline__ void tile_load(const W2Src& src, int tile, TileRegs& r) {

@@ -1,0 +1,76 @@
+"""GPU parity with weights of a trained model's scale (logits that differ by units).
+
+At the first step's weights every logit is about zero, so a wrong operand of the
+recomputed logits hardly shows in the update; here it shows in the bias update of every
+label, which is the sum of the label's probabilities."""
+import numpy as np
+import pytest
+
+import paper_2110_07029_amd as asgd
+from oracle import model as om
+from paper_2110_07029_amd import synth
+
+from gpu_util import Setup, flush, write_params
+
+pytestmark = pytest.mark.gpu
+
+H = asgd.HIDDEN
+LABELS = synth.Workload("labels-3000", 5_000, 2_999, 700, 256, 0.01, True, "lognormal", 3.5, 0.8, 500, 1.05,
+                        "uniform", "poisson", 4.0, 1.2, 2)
+
+
+def trained_scale(F, L, seed):
+    r = np.random.default_rng(seed)
+    f = lambda scale, *shape: (r.standard_normal(shape) * scale).astype(np.float32)  # noqa: E731
+    return {"W1": f(0.5, F, H), "b1": f(0.1, H), "W2": f(0.15, L, H), "b2": f(0.3, L)}
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("B", [31, 96, 128, 129, 256, 257, 300, 512, 611])
+def test_bias_update_of_labels_without_targets(B, bf16):
+    """Labels with no entry in the batch: their bias changes by -lr * mean_i softmax(Z_i)_j.
+
+    Against the oracle that rounds the same operands: the kernel's fp32 A1 may flip the bf16
+    rounding of an H1 entry (2^-8 of it), a logit moves by at most 2^-8 |h||w| for that one of
+    128 terms, here below 0.005, and the sum over rows by less; the stored bias rounds to
+    2 ulp."""
+    flush(f"trained scale: B={B} bf16={bf16}")
+    s = Setup(LABELS, 700, B, bf16=bf16)
+    try:
+        p = trained_scale(s.F, s.L, 5)
+        write_params(s.m, p)
+        lr = 0.5
+        asgd.asgd_train_step(s.m, s.xb(0, B), s.yb(0, B), lr)
+        x, y = s.host_batch(0, B)
+        ref = om.train_step(p, x, y, lr, "bf16" if bf16 else "fp32")[0]["b2"].astype(np.float64) - p["b2"]
+        got = asgd.asgd_model_get_params(s.m, asgd.ASGD_PARAM_B2, (s.L,)).astype(np.float64) - p["b2"]
+        free = np.setdiff1d(np.arange(s.L), y.indices)
+        want = ref[free]
+        bound = (5e-3 if bf16 else 1e-4) * np.abs(want) + 2.0 * np.spacing(np.abs(p["b2"][free]))
+        err = np.abs(got[free] - want)
+        assert np.all(err <= bound), (err / bound).max()
+    finally:
+        s.free()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("label", [0, 5, 34, 39])
+def test_one_label_far_above_the_rest(label, bf16):
+    """A bias 200 above the others, at labels that either half of a wavefront owns: the online
+    softmax has to raise its reference to it, or 2^(200 log2 e) overflows."""
+    flush(f"far label {label} bf16={bf16}")
+    B = 64
+    s = Setup(LABELS, 256, B, bf16=bf16)
+    try:
+        p = trained_scale(s.F, s.L, 6)
+        p["b2"][label] = 200.0
+        write_params(s.m, p)
+        x, y = s.host_batch(0, B)
+        loss = asgd.asgd_train_step(s.m, s.xb(0, B), s.yb(0, B), 0.5, want_loss=True)
+        ref, ref_loss, g, _ = om.train_step(p, x, y, 0.5, "bf16" if bf16 else "fp32")
+        assert np.isfinite(loss) and abs(loss - ref_loss) <= 1e-3 * abs(ref_loss), (loss, ref_loss)
+        got = asgd.asgd_model_get_params(s.m, asgd.ASGD_PARAM_B1, (H,)).astype(np.float64)
+        d, dr = got - p["b1"], ref["b1"].astype(np.float64) - p["b1"]
+        assert np.linalg.norm(d - dr) <= 2e-2 * np.linalg.norm(dr)
+    finally:
+        s.free()
