@@ -176,7 +176,7 @@ struct asgd_model {
   float* sm_s = nullptr;
   float* tk_s = nullptr;
   int32_t* tk_i = nullptr;
-  int64_t tk_rows = 0;
+  int64_t tk_entries = 0;
 
   // kernel timing: per group, a pool of (start, stop) event pairs
   static constexpr int kTimerPool = 1024;
@@ -210,11 +210,10 @@ int64_t layout_workspace(asgd_model* m, char* base) {
     int s = std::min(n_tiles, (m->n_cu + r - 1) / r);
     part_rows = std::max<int64_t>(part_rows, (int64_t)s * r * RB);
   }
-  int64_t tk_rows = 0;
-  for (int r = 1; r <= nrb; ++r) {
-    const int B = r * RB;
-    tk_rows = std::max<int64_t>(tk_rows, (int64_t)topk_splits(B, n_tiles) * r * RB);
-  }
+  // A prediction's lists, k entries per (row, split).  With splits <= ceil(n_cu / blocks) and
+  // B <= rows x blocks there are below rows x (n_cu + blocks) lists: k <= 32 with 256 rows per
+  // block, k <= 8 with 512.
+  const int64_t tk_entries = (int64_t)(m->n_cu + nrb) * RB * 32;
   char* p = base;
   m->A1 = carve<float>(p, (int64_t)rp * HID);
   m->A2 = carve<float>(p, m->extra ? (int64_t)rp * HID : 0);
@@ -262,9 +261,9 @@ int64_t layout_workspace(asgd_model* m, char* base) {
   m->Z = carve<float>(p, m->unfused ? (int64_t)rp * m->ldz : 0);
   m->sm_m = carve<float>(p, sm_rows);
   m->sm_s = carve<float>(p, sm_rows);
-  m->tk_s = carve<float>(p, tk_rows * 32);
-  m->tk_i = carve<int32_t>(p, tk_rows * 32);
-  m->tk_rows = tk_rows;
+  m->tk_s = carve<float>(p, tk_entries);
+  m->tk_i = carve<int32_t>(p, tk_entries);
+  m->tk_entries = tk_entries;
   return (int64_t)(p - base);
 }
 
@@ -790,14 +789,10 @@ asgd_status asgd_predict_topk(asgd_model* m, const asgd_csr* x, int32_t k, int32
   s = run_gather(m, x, nullptr, m->stream, &rows_pad);
   if (s) return s;
   const int n_tiles = (m->L + OUT_TILE - 1) / OUT_TILE;
-  const int splits = topk_splits(B, n_tiles);
-  const int tps = (n_tiles + splits - 1) / splits;
-  const int s_eff = (n_tiles + tps - 1) / tps;
-  if ((int64_t)s_eff * rows_pad > m->tk_rows) return fail(ASGD_ERANGE, "top-k buffer too small");
-  HIP_TRY(launch_out_fwd_topk(m->bf16, m->W2(), m->b2(), m->L, m->H1, B, splits, k, m->tk_s,
-                              m->tk_i, rows_pad, m->stream));
-  HIP_TRY(launch_topk_combine(B, s_eff, k, m->tk_s, m->tk_i, rows_pad, ids_dev, scores_dev,
-                              m->stream));
+  const TopkShape sh = topk_shape(m->bf16, B, k, n_tiles, m->n_cu);
+  if ((int64_t)B * sh.splits * k > m->tk_entries) return fail(ASGD_ERANGE, "top-k buffer too small");
+  HIP_TRY(launch_out_fwd_topk(m->bf16, m->W2(), m->b2(), m->L, m->H1, B, sh, k, m->tk_s, m->tk_i, m->stream));
+  HIP_TRY(launch_topk_combine(B, sh.splits, k, m->tk_s, m->tk_i, ids_dev, scores_dev, m->stream));
   return ASGD_OK;
 }
 

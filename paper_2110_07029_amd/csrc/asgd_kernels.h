@@ -151,13 +151,18 @@ hipError_t launch_unfused_dh(bool use_bf16, const float* W2, const float* b2, in
                              const float* rw, const float* A, float* dA, hipStream_t st);
 
 // ---- prediction ---------------------------------------------------------------
-int topk_splits(int B, int n_tiles);
+// A prediction's launch shape: 32 nb rows per wave, nrb row blocks of 8 waves,
+// `splits` label splits of tps tiles each.
+struct TopkShape {
+  int nb, nrb, splits, tps;
+};
+TopkShape topk_shape(bool use_bf16, int B, int k, int n_tiles, int n_cu);
+// Per row and split the k best (score, label), row-major: B x splits x k.
 hipError_t launch_out_fwd_topk(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
-                               int B, int splits, int k, float* part_s, int32_t* part_i,
-                               int ld_part, hipStream_t st);
-hipError_t launch_topk_combine(int B, int splits, int k, const float* part_s,
-                               const int32_t* part_i, int ld_part, int32_t* ids, float* scores,
+                               int B, const TopkShape& shape, int k, float* part_s, int32_t* part_i,
                                hipStream_t st);
+hipError_t launch_topk_combine(int B, int splits, int k, const float* part_s, const int32_t* part_i,
+                               int32_t* ids, float* scores, hipStream_t st);
 
 // ---- merge ---------------------------------------------------------------------
 constexpr int MERGE_MAX = 16;

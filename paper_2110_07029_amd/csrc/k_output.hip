@@ -599,249 +599,374 @@ hipError_t launch_out_dA1(int B, int splits, const float* m_part, const float* s
 
 // ---------------------------------------------------------------------------
 // Prediction: per (split, row) top-k lists of (score, label), ties -> smaller id.
+//
+// Workgroup = (label split, 8 waves x 32 NB rows), W2 tiles through the LDS ring
+// of the training forward.  A wave issues the next tile's logits to the matrix
+// cores and meanwhile compares this tile's best score per row with the row's k-th
+// best so far.  With 64 rows per wave (NB = 2) every W2 fragment read from LDS
+// feeds two products: at 32 rows per wave the reads alone (64 KB per tile and CU)
+// take as long as the products.
+// A row is a lane pair (n, n + 32).  Up to 8 entries (KR = 1 or 8) its list lives in
+// registers, the same on both lanes; longer lists (KR = 0) are in LDS.  A tile with
+// scores that reach the list gives them up best first, one per row and round, so it
+// takes as many rounds as the row with the most new entries has: with an insertion
+// per score, the first tiles of every split (which fill the lists) took 50 of 70 us
+// for 50 rows of 30,000 labels.
 // ---------------------------------------------------------------------------
-constexpr int TOPK_MAX = 32;
+constexpr int TOPK_REG_K = 8;
 
 __device__ __forceinline__ bool better(float s, int i, float ts, int ti) {
   return s > ts || (s == ts && i < ti);
 }
 
-template <bool BF16>
+template <bool BF16, int NB, int KR>
 __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
     const float* __restrict__ W2, const float* __restrict__ b2, int L,
     const typename Mma<BF16>::elem* __restrict__ H1, int B, int tiles_per_split, int n_tiles,
-    int k, float* __restrict__ part_s, int32_t* __restrict__ part_i, int ld_part) {
+    int s_eff, int k, float* __restrict__ part_s, int32_t* __restrict__ part_i) {
   using M = Mma<BF16>;
   using E = typename M::elem;
   using Fr = typename M::frag;
-  constexpr int NB = FwdShape<BF16>::NB;
-  constexpr int RB = FwdShape<BF16>::RB;
-  constexpr int NCH = 32 / M::KC;
+  constexpr int WAVES = FwdShape<BF16>::WAVES;
   constexpr int WROWS = 32 * NB;
-  __shared__ __attribute__((aligned(16))) E wr[2][tile_elems<BF16>()];
-  __shared__ __attribute__((aligned(16))) float bt[2][OUT_TILE];
-  __shared__ float ls[FwdShape<BF16>::WAVES][WROWS][TOPK_MAX];
-  __shared__ int li[FwdShape<BF16>::WAVES][WROWS][TOPK_MAX];
+  constexpr int RB = WAVES * WROWS;
+  constexpr int NCH = 32 / M::KC;
+  constexpr int P = FwdRing<BF16>::P, NRING = FwdRing<BF16>::N;
+  __shared__ __attribute__((aligned(16))) E wr[NRING][tile_elems<BF16>()];
+  __shared__ __attribute__((aligned(16))) float bt[NRING][OUT_TILE];
+  extern __shared__ float lists[];  // KR = 0: RB x k scores, then RB x k ids
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, n = lane & 31;
-  const int split = blockIdx.x;
+  const int lane = threadIdx.x & 63, g = lane >> 5, n = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // workgroup -> (split, row block): the row blocks of a split share an XCD (see k_out_fwd_train)
+  const int n_wg = (int)gridDim.x, nrb = n_wg / s_eff, wg = (int)blockIdx.x;
+  const int v = n_wg % 8 == 0 ? (wg % 8) * (n_wg / 8) + wg / 8 : wg;
+  const int split = v / nrb;
   const int t_begin = split * tiles_per_split;
   const int t_end = min(n_tiles, t_begin + tiles_per_split);
-  const int row0 = blockIdx.y * RB + wave * WROWS;
-  const bool active = row0 < B;
+  const int t_last = t_end - 1;
+  const int row0 = (v % nrb) * RB + wave * WROWS;
+  const bool active = row0 < B;  // (waves past the batch only move W2 tiles)
   const W2Src src = w2_src(W2, b2, L);
   const int rbase[2] = {tw_row_base(n, g, 0), tw_row_base(n, g, 1)};
 
-  for (int e = lane; e < WROWS * TOPK_MAX; e += 64) {
-    ls[wave][e / TOPK_MAX][e % TOPK_MAX] = -INFINITY;
-    li[wave][e / TOPK_MAX][e % TOPK_MAX] = 0x7fffffff;
+  // KR = 0: the wave's lists in LDS, sorted, k entries per row
+  float* const ls = lists + wave * WROWS * k;
+  int* const li = reinterpret_cast<int*>(lists + RB * k) + wave * WROWS * k;
+  if constexpr (KR == 0) {
+    for (int e = lane; e < WROWS * k; e += 64) {
+      ls[e] = -INFINITY;
+      li[e] = 0x7fffffff;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
+  // KR > 0: the row's list in registers; the first KR - k entries are held by
+  // (+inf, -1), which nothing displaces, so the k-th best is always the last entry
+  constexpr int KN = KR > 0 ? KR : 1;
+  float ks[NB][KN];
+  int ki[NB][KN];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int j = 0; j < KN; ++j) {
+      ks[nb][j] = KR > 0 && j < KR - k ? INFINITY : -INFINITY;
+      ki[nb][j] = KR > 0 && j < KR - k ? -1 : 0x7fffffff;
+    }
   Fr hf[NB][4][NCH];
+  float thr[NB];  // the row's k-th best score so far (+inf: no such row, nothing reaches it)
+  bool rvalid[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const E* hrow = H1 + (size_t)(row0 + nb * 32 + n) * HID;
+    // (rows past round_up(B, 32) of the buffer are not read)
+    const int row = row0 + nb * 32 + n;
+    rvalid[nb] = row < B;
+    thr[nb] = rvalid[nb] ? -INFINITY : INFINITY;
+    const E* hrow = H1 + (size_t)(row0 + nb * 32 < B ? row : n) * HID;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
       for (int c = 0; c < NCH; ++c) hf[nb][kb][c] = h1_frag<BF16>(hrow, kb, c, g);
   }
-  // W2 tiles are loaded three ahead: at the start of iteration t, tile t is in
-  // LDS buffer (t - t_begin) & 1 and tiles t+1, t+2, t+3 are in the register
-  // sets tr0, tr1, tr2 in turn (the loop is unrolled by three so that every
-  // set is named statically); iteration t moves tile t+1 into the other
-  // buffer and reloads its set with tile t+4.
-  const int t_last = t_end - 1;
-  TileRegs tr0, tr1, tr2;
-  if (t_begin < t_end) {
-    tile_load(src, t_begin, tr0);
-    tile_store<BF16, false>(tr0, L, t_begin, wr[0], nullptr, bt[0]);
-    tile_load(src, min(t_begin + 1, t_last), tr0);
-    tile_load(src, min(t_begin + 2, t_last), tr1);
-    tile_load(src, min(t_begin + 3, t_last), tr2);
-  }
-  __syncthreads();
-  auto iteration = [&](int t, TileRegs& trn) {
-    const int buf = (t - t_begin) & 1;
-    if (active) {
-      // the accumulators start from the biases of the tile's labels (rows of Z^T)
-      f32x16 z[NB];
-      {
-        const float4* bq = reinterpret_cast<const float4*>(bt[buf]);
-        f32x16 zb;
+  // (the loop's wait counters then track only the W2 prefetch, as in k_out_fwd_train)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 bv = bq[2 * q + g];
-          zb[4 * q + 0] = bv.x; zb[4 * q + 1] = bv.y; zb[4 * q + 2] = bv.z; zb[4 * q + 3] = bv.w;
-        }
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) z[nb] = zb;
-      }
+    for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb)
+      for (int c = 0; c < NCH; ++c) asm volatile("" : "+v"(hf[nb][kb][c]));
+
+  auto z_tile = [&](int buf, f32x16 (&z)[NB]) {
+    const float4* bq = reinterpret_cast<const float4*>(bt[buf]);
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          const Fr a = tile_frag_w<BF16>(wr[buf], rbase, n, kb, c, g);
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) z[nb] = M::mma(a, hf[nb][kb][c], z[nb]);
-        }
+    for (int q = 0; q < 4; ++q) {
+      const float4 b = bq[2 * q + g];
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
-        const int rloc = nb * 32 + n;
-        const bool rvalid = row0 + rloc < B;
-        // skip the tile unless some lane's best score reaches its row's k-th
-        // entry (NaN never does; ties go to the exact test below)
-        float m = z[nb][0];
+        z[nb][4 * q + 0] = b.x; z[nb][4 * q + 1] = b.y; z[nb][4 * q + 2] = b.z; z[nb][4 * q + 3] = b.w;
+      }
+    }
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        const Fr a = tile_frag_w<BF16>(wr[buf], rbase, n, kb, c, g);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) z[nb] = M::mma(a, hf[nb][kb][c], z[nb]);
+      }
+  };
+  // Scores of tile t into the lists.  Most tiles hold none that reaches its row's
+  // k-th: one maximum per row and a vote.
+  auto rank = [&](int t, f32x16 (&z)[NB]) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      float m = z[nb][0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) m = fmaxf(m, z[nb][r]);  // (ignores NaN: those are never ranked)
+      if (!__any(m >= thr[nb])) continue;
+      const float gone = __builtin_nanf("");
+      if (t == n_tiles - 1) {  // labels past L (their logits are -inf) are not ranked either
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (t * OUT_TILE + 8 * (r >> 2) + 4 * g + (r & 3) >= L) z[nb][r] = gone;
+      }
+#pragma unroll 1
+      for (;;) {
+        // the lane's best remaining score, at its smallest label
+        m = z[nb][0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) m = fmaxf(m, z[nb][r]);
-        if (!__any(rvalid && m >= ls[wave][rloc][k - 1])) continue;
-        for (int half = 0; half < 2; ++half) {
-          if (g == half && rvalid) {
-            float* lsr = ls[wave][rloc];
-            int* lir = li[wave][rloc];
-            // the row's current k-th entry, re-read only after an insertion:
-            // most scores fail this test and touch no LDS
-            float ts = lsr[k - 1];
-            int ti = lir[k - 1];
-            for (int r = 0; r < 16; ++r) {
-              const int ll = 8 * (r >> 2) + 4 * g + (r & 3);
-              const int id = t * OUT_TILE + ll;
-              const float sc = z[nb][r];
-              if (id >= L || !(sc == sc)) continue;  // NaN scores are never ranked
-              if (!better(sc, id, ts, ti)) continue;
-              int pos = k - 1;
-              while (pos > 0 && better(sc, id, lsr[pos - 1], lir[pos - 1])) {
-                lsr[pos] = lsr[pos - 1];
-                lir[pos] = lir[pos - 1];
-                --pos;
-              }
-              lsr[pos] = sc;
-              lir[pos] = id;
-              ts = lsr[k - 1];
-              ti = lir[k - 1];
-            }
+        int mr = 16;
+#pragma unroll
+        for (int r = 15; r >= 0; --r) mr = z[nb][r] == m ? r : mr;
+        const bool some = mr < 16;
+        const int my_id = some ? t * OUT_TILE + 8 * (mr >> 2) + 4 * g + (mr & 3) : 0x7fffffff;
+        // and the better one of the row's two lanes (through integers, see half_swap_max)
+        const unsigned us = __builtin_bit_cast(unsigned, some ? m : -INFINITY), ui = (unsigned)my_id;
+        const auto ss = __builtin_amdgcn_permlane32_swap(us, us, false, false);
+        const auto si = __builtin_amdgcn_permlane32_swap(ui, ui, false, false);
+        const unsigned s0 = ss[0], s1 = ss[1], i0 = si[0], i1 = si[1];
+        float cs = __builtin_bit_cast(float, s0);
+        int ci = (int)i0;
+        if (better(__builtin_bit_cast(float, s1), (int)i1, cs, ci)) {
+          cs = __builtin_bit_cast(float, s1);
+          ci = (int)i1;
+        }
+        if constexpr (KR > 0) {
+          const bool in = rvalid[nb] && better(cs, ci, ks[nb][KN - 1], ki[nb][KN - 1]);
+          if (!__any(in)) break;
+          const bool mine = in && some && ci == my_id;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) z[nb][r] = mine && r == mr ? gone : z[nb][r];
+#pragma unroll
+          for (int j = 0; j < KN; ++j) {
+            const bool up = in && better(cs, ci, ks[nb][j], ki[nb][j]);
+            const float os = ks[nb][j];
+            const int oi = ki[nb][j];
+            ks[nb][j] = up ? cs : os;
+            ki[nb][j] = up ? ci : oi;
+            cs = up ? os : cs;
+            ci = up ? oi : ci;
           }
+          if (rvalid[nb]) thr[nb] = ks[nb][KN - 1];
+        } else {
+          float* const lsr = ls + (nb * 32 + n) * k;
+          int* const lir = li + (nb * 32 + n) * k;
+          const bool in = rvalid[nb] && better(cs, ci, lsr[k - 1], lir[k - 1]);
+          if (!__any(in)) break;
+          const bool mine = in && some && ci == my_id;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) z[nb][r] = mine && r == mr ? gone : z[nb][r];
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+          if (in && g == 0) {
+            int pos = k - 1;
+            while (pos > 0 && better(cs, ci, lsr[pos - 1], lir[pos - 1])) {
+              lsr[pos] = lsr[pos - 1];
+              lir[pos] = lir[pos - 1];
+              --pos;
+            }
+            lsr[pos] = cs;
+            lir[pos] = ci;
+          }
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+          if (rvalid[nb]) thr[nb] = lsr[k - 1];
         }
       }
     }
-    if (t + 1 < t_end) tile_store<BF16, false>(trn, L, t + 1, wr[buf ^ 1], nullptr, bt[buf ^ 1]);
-    if (t + 4 <= t_last) tile_load(src, t + 4, trn);
-    __syncthreads();
   };
-  for (int t = t_begin; t < t_end; t += 3) {
-    iteration(t, tr0);
-    if (t + 1 >= t_end) break;
-    iteration(t + 1, tr1);
-    if (t + 2 >= t_end) break;
-    iteration(t + 2, tr2);
+
+  // The pipeline of k_out_fwd_train: tile u lives in ring slot (u - t_begin) mod
+  // NRING; the iteration of tile t issues the logits of t+1, ranks those of t,
+  // stores tile t+P+1 (loaded two iterations earlier) and loads t+P+3; a barrier
+  // closes every P-th iteration.  Indices are clamped to the split's last tile.
+  TileRegs tr0, tr1;
+  auto slot = [&](int u) { return (u - t_begin) % NRING; };
+#pragma unroll
+  for (int u = 0; u <= P; ++u) {
+    const int tu = min(t_begin + u, t_last);
+    tile_load(src, tu, tr0);
+    tile_store<BF16, false>(tr0, L, tu, wr[u], nullptr, bt[u]);
   }
-  if (active) {
+  tile_load(src, min(t_begin + P + 1, t_last), tr0);
+  tile_load(src, min(t_begin + P + 2, t_last), tr1);
+  __syncthreads();
+  f32x16 z[NB], zn[NB];
+  if (active) z_tile(0, z);
+  auto iteration = [&](int t, TileRegs& tr, f32x16 (&zc)[NB], f32x16 (&zx)[NB]) {
+    const int bst = slot(t + P + 1);
+    if (active) {
+      z_tile(slot(t + 1), zx);
+      rank(t, zc);
+    }
+    tile_store<BF16, false>(tr, L, min(t + P + 1, t_last), wr[bst], nullptr, bt[bst]);
+    tile_load(src, min(t + P + 3, t_last), tr);
+    if ((t - t_begin) % P == P - 1) __syncthreads();
+  };
+  for (int t = t_begin; t < t_end; t += 2) {
+    iteration(t, tr0, z, zn);
+    if (t + 1 >= t_end) break;
+    iteration(t + 1, tr1, zn, z);
+  }
+  // row-major lists: the combine reads a row's candidates as one run
+  if constexpr (KR == 0) {
     for (int e = lane; e < WROWS * k; e += 64) {
-      const int rl = e / k, j = e % k;
-      const int row = row0 + rl;
+      const int row = row0 + e / k;
       if (row < B) {
-        part_s[((size_t)split * ld_part + row) * k + j] = ls[wave][rl][j];
-        part_i[((size_t)split * ld_part + row) * k + j] = li[wave][rl][j];
+        const size_t o = ((size_t)row * s_eff + split) * k + e % k;
+        part_s[o] = ls[e];
+        part_i[o] = li[e];
       }
+    }
+  } else {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      if (!rvalid[nb] || g) continue;
+      const size_t o = ((size_t)(row0 + nb * 32 + n) * s_eff + split) * k;
+#pragma unroll
+      for (int j = 0; j < KN; ++j)
+        if (j >= KR - k) {
+          part_s[o + j - (KR - k)] = ks[nb][j];
+          part_i[o + j - (KR - k)] = ki[nb][j];
+        }
     }
   }
 }
 
-int topk_splits(int B, int n_tiles) {
-  const int RB = FwdShape<true>::RB;
-  int s = 256 / ((B + RB - 1) / RB);
-  if (s > 64) s = 64;
-  if (s < 1) s = 1;
+// Rows per wave and label splits of a prediction: one workgroup per CU over all
+// row blocks (a small batch needs every CU to read W2: 50 rows of 30,000 labels
+// took 110 us on 64 workgroups, and 16,384 rows of 670,091 labels 4.8 ms at 32
+// rows per wave).
+TopkShape topk_shape(bool use_bf16, int B, int k, int n_tiles, int n_cu) {
+  TopkShape p;
+  p.nb = use_bf16 && B > 256 && k <= TOPK_REG_K ? 2 : 1;
+  const int rb = FwdShape<true>::WAVES * 32 * p.nb;
+  p.nrb = (B + rb - 1) / rb;
+  int s = (n_cu + p.nrb - 1) / p.nrb;
   if (s > n_tiles) s = n_tiles;
-  return s;
+  p.tps = (n_tiles + s - 1) / s;
+  p.splits = (n_tiles + p.tps - 1) / p.tps;
+  return p;
 }
 
 hipError_t launch_out_fwd_topk(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
-                               int B, int splits, int k, float* part_s, int32_t* part_i,
-                               int ld_part, hipStream_t st) {
+                               int B, const TopkShape& sh, int k, float* part_s, int32_t* part_i,
+                               hipStream_t st) {
   const int n_tiles = (L + OUT_TILE - 1) / OUT_TILE;
-  const int tps = (n_tiles + splits - 1) / splits;
-  const int s_eff = (n_tiles + tps - 1) / tps;
-  const int RB = out_rows_per_block(use_bf16);
-  const dim3 grid(s_eff, (B + RB - 1) / RB), block(FWD_THREADS);
-  if (use_bf16)
-    hipLaunchKernelGGL(k_out_fwd_topk<true>, grid, block, 0, st, W2, b2, L, (const bf16*)H1, B,
-                       tps, n_tiles, k, part_s, part_i, ld_part);
-  else
-    hipLaunchKernelGGL(k_out_fwd_topk<false>, grid, block, 0, st, W2, b2, L, (const float*)H1, B,
-                       tps, n_tiles, k, part_s, part_i, ld_part);
-  return hipGetLastError();
+  const dim3 grid(sh.splits * sh.nrb), block(FWD_THREADS);
+  auto go = [&](auto kern, auto* h1, size_t lds) {
+    // up to 64 KB of lists beside the ring: above the default limit of a launch
+    if (lds) {
+      const hipError_t e =
+          hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, grid, block, lds, st, W2, b2, L, h1, B, sh.tps, n_tiles, sh.splits, k, part_s, part_i);
+    return hipGetLastError();
+  };
+  const size_t lds = (size_t)FwdShape<true>::WAVES * 32 * k * (sizeof(float) + sizeof(int));
+  if (!use_bf16) {
+    const float* h = (const float*)H1;
+    if (k == 1) return go(k_out_fwd_topk<false, 1, 1>, h, 0);
+    if (k <= TOPK_REG_K) return go(k_out_fwd_topk<false, 1, TOPK_REG_K>, h, 0);
+    return go(k_out_fwd_topk<false, 1, 0>, h, lds);
+  }
+  const bf16* h = (const bf16*)H1;
+  if (k == 1) return sh.nb == 2 ? go(k_out_fwd_topk<true, 2, 1>, h, 0) : go(k_out_fwd_topk<true, 1, 1>, h, 0);
+  if (k <= TOPK_REG_K)
+    return sh.nb == 2 ? go(k_out_fwd_topk<true, 2, TOPK_REG_K>, h, 0) : go(k_out_fwd_topk<true, 1, TOPK_REG_K>, h, 0);
+  return go(k_out_fwd_topk<true, 1, 0>, h, lds);
 }
 
-// Final top-k of a row from splits*k candidates: k rounds of a block arg-max.
-__global__ __launch_bounds__(256) void k_topk_combine(int splits, int k,
-                                                      const float* __restrict__ part_s,
-                                                      const int32_t* __restrict__ part_i,
-                                                      int ld_part, int32_t* __restrict__ ids,
-                                                      float* __restrict__ scores) {
+// Final top-k of a row from its splits' sorted lists, by one wavefront: the
+// row's candidates come into LDS as one run, lane l keeps the heads of lists l,
+// l + 64, ..., and each of the k rounds takes the best head and advances its
+// list.  (An exhausted or unfilled list's head is (-inf, INT_MAX).)
+constexpr int TOPK_LISTS = 6;  // lists per lane: up to 384 splits
+
+__global__ __launch_bounds__(64) void k_topk_combine(int splits, int k, const float* __restrict__ part_s,
+                                                     const int32_t* __restrict__ part_i,
+                                                     int32_t* __restrict__ ids, float* __restrict__ scores) {
   extern __shared__ float csm[];
-  const int i = blockIdx.x;
+  const int i = blockIdx.x, lane = threadIdx.x;
   const int nc = splits * k;
   float* cs = csm;
   int* ci = reinterpret_cast<int*>(csm + nc);
-  __shared__ float rs[4];
-  __shared__ int ri[4], rp[4];
-  for (int e = threadIdx.x; e < nc; e += 256) {
-    const int s = e / k, j = e % k;
-    cs[e] = part_s[((size_t)s * ld_part + i) * k + j];
-    ci[e] = part_i[((size_t)s * ld_part + i) * k + j];
+  const float* ps = part_s + (size_t)i * nc;
+  const int32_t* pi = part_i + (size_t)i * nc;
+  for (int e = lane; e < nc; e += 64) {
+    cs[e] = ps[e];
+    ci[e] = pi[e];
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  float hs[TOPK_LISTS];
+  int hi[TOPK_LISTS], pos[TOPK_LISTS];
+#pragma unroll
+  for (int j = 0; j < TOPK_LISTS; ++j) {
+    const int l = lane + 64 * j;
+    pos[j] = 0;
+    hs[j] = l < splits ? cs[l * k] : -INFINITY;
+    hi[j] = l < splits ? ci[l * k] : 0x7fffffff;
+  }
   for (int out = 0; out < k; ++out) {
-    float bs = -INFINITY;
-    int bi = 0x7fffffff, bp = -1;
-    for (int e = threadIdx.x; e < nc; e += 256) {
-      if (ci[e] < 0) continue;  // already taken
-      if (bp < 0 || better(cs[e], ci[e], bs, bi)) {
-        bs = cs[e];
-        bi = ci[e];
-        bp = e;
+    float bs = hs[0];
+    int bi = hi[0];
+#pragma unroll
+    for (int j = 1; j < TOPK_LISTS; ++j)
+      if (better(hs[j], hi[j], bs, bi)) {
+        bs = hs[j];
+        bi = hi[j];
       }
-    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
       const float os = __shfl_xor(bs, o);
-      const int oi = __shfl_xor(bi, o), op = __shfl_xor(bp, o);
-      if (op >= 0 && (bp < 0 || better(os, oi, bs, bi))) {
+      const int oi = __shfl_xor(bi, o);
+      if (better(os, oi, bs, bi)) {
         bs = os;
         bi = oi;
-        bp = op;
       }
     }
+    const bool none = bi == 0x7fffffff;  // ids are unique: the winner's list is the one whose head has its id
+#pragma unroll
+    for (int j = 0; j < TOPK_LISTS; ++j)
+      if (!none && hi[j] == bi) {
+        const int e = (lane + 64 * j) * k + ++pos[j];
+        hs[j] = pos[j] < k ? cs[e] : -INFINITY;
+        hi[j] = pos[j] < k ? ci[e] : 0x7fffffff;
+      }
     if (lane == 0) {
-      rs[w] = bs;
-      ri[w] = bi;
-      rp[w] = bp;
+      ids[(size_t)i * k + out] = none ? -1 : bi;
+      if (scores) scores[(size_t)i * k + out] = none ? -INFINITY : bs;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float s0 = rs[0];
-      int i0 = ri[0], p0 = rp[0];
-      for (int ww = 1; ww < 4; ++ww)
-        if (rp[ww] >= 0 && (p0 < 0 || better(rs[ww], ri[ww], s0, i0))) {
-          s0 = rs[ww];
-          i0 = ri[ww];
-          p0 = rp[ww];
-        }
-      ids[(size_t)i * k + out] = p0 >= 0 ? i0 : -1;
-      if (scores) scores[(size_t)i * k + out] = p0 >= 0 ? s0 : -INFINITY;
-      if (p0 >= 0) ci[p0] = -1;
-    }
-    __syncthreads();
   }
 }
 
 hipError_t launch_topk_combine(int B, int splits, int k, const float* part_s,
-                               const int32_t* part_i, int ld_part, int32_t* ids, float* scores,
-                               hipStream_t st) {
+                               const int32_t* part_i, int32_t* ids, float* scores, hipStream_t st) {
+  if (splits > 64 * TOPK_LISTS) return hipErrorInvalidValue;
   const size_t shm = (size_t)splits * k * (sizeof(float) + sizeof(int));
-  hipLaunchKernelGGL(k_topk_combine, dim3(B), dim3(256), shm, st, splits, k, part_s, part_i,
-                     ld_part, ids, scores);
+  const hipError_t e =
+      hipFuncSetAttribute((const void*)k_topk_combine, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_topk_combine, dim3(B), dim3(64), shm, st, splits, k, part_s, part_i, ids, scores);
   return hipGetLastError();
 }
 
