@@ -174,8 +174,7 @@ struct asgd_model {
   int ldz = 0;
   float* sm_m = nullptr;  // softmax partials per (column chunk, row)
   float* sm_s = nullptr;
-  float* tk_s = nullptr;
-  int32_t* tk_i = nullptr;
+  double* tk = nullptr;
   int64_t tk_entries = 0;
 
   // kernel timing: per group, a pool of (start, stop) event pairs
@@ -261,8 +260,7 @@ int64_t layout_workspace(asgd_model* m, char* base) {
   m->Z = carve<float>(p, m->unfused ? (int64_t)rp * m->ldz : 0);
   m->sm_m = carve<float>(p, sm_rows);
   m->sm_s = carve<float>(p, sm_rows);
-  m->tk_s = carve<float>(p, tk_entries);
-  m->tk_i = carve<int32_t>(p, tk_entries);
+  m->tk = carve<double>(p, tk_entries);
   m->tk_entries = tk_entries;
   return (int64_t)(p - base);
 }
@@ -791,8 +789,8 @@ asgd_status asgd_predict_topk(asgd_model* m, const asgd_csr* x, int32_t k, int32
   const int n_tiles = (m->L + OUT_TILE - 1) / OUT_TILE;
   const TopkShape sh = topk_shape(m->bf16, B, k, n_tiles, m->n_cu);
   if ((int64_t)B * sh.splits * k > m->tk_entries) return fail(ASGD_ERANGE, "top-k buffer too small");
-  HIP_TRY(launch_out_fwd_topk(m->bf16, m->W2(), m->b2(), m->L, m->H1, B, sh, k, m->tk_s, m->tk_i, m->stream));
-  HIP_TRY(launch_topk_combine(B, sh.splits, k, m->tk_s, m->tk_i, ids_dev, scores_dev, m->stream));
+  HIP_TRY(launch_out_fwd_topk(m->bf16, m->W2(), m->b2(), m->L, m->H1, B, sh, k, m->tk, m->stream));
+  HIP_TRY(launch_topk_combine(B, sh.splits, k, m->tk, ids_dev, scores_dev, m->stream));
   return ASGD_OK;
 }
 

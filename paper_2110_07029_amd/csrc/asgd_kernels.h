@@ -157,12 +157,11 @@ struct TopkShape {
   int nb, nrb, splits, tps;
 };
 TopkShape topk_shape(bool use_bf16, int B, int k, int n_tiles, int n_cu);
-// Per row and split the k best (score, label), row-major: B x splits x k.
+// Per row and split the k best (score, label), as keys, row-major: B x splits x k.
 hipError_t launch_out_fwd_topk(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
-                               int B, const TopkShape& shape, int k, float* part_s, int32_t* part_i,
+                               int B, const TopkShape& shape, int k, double* part, hipStream_t st);
+hipError_t launch_topk_combine(int B, int splits, int k, const double* part, int32_t* ids, float* scores,
                                hipStream_t st);
-hipError_t launch_topk_combine(int B, int splits, int k, const float* part_s, const int32_t* part_i,
-                               int32_t* ids, float* scores, hipStream_t st);
 
 // ---- merge ---------------------------------------------------------------------
 constexpr int MERGE_MAX = 16;

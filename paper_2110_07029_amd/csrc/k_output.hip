@@ -606,24 +606,48 @@ hipError_t launch_out_dA1(int B, int splits, const float* m_part, const float* s
 // best so far.  With 64 rows per wave (NB = 2) every W2 fragment read from LDS
 // feeds two products: at 32 rows per wave the reads alone (64 KB per tile and CU)
 // take as long as the products.
-// A row is a lane pair (n, n + 32).  Up to 8 entries (KR = 1 or 8) its list lives in
-// registers, the same on both lanes; longer lists (KR = 0) are in LDS.  A tile with
-// scores that reach the list gives them up best first, one per row and round, so it
-// takes as many rounds as the row with the most new entries has: with an insertion
-// per score, the first tiles of every split (which fill the lists) took 50 of 70 us
-// for 50 rows of 30,000 labels.
+// A row is a lane pair (n, n + 32) whose list lives in registers, the same on both
+// lanes, as KR = 1, 8 or 32 sorted double keys (below): an entry enters by a chain of
+// max / min pairs, and only the accumulator registers with a score that reaches the
+// list are looked at.  (Sorted lists of scores and ids in LDS took 4 us per tile
+// while they filled: 50 of 70 us for 50 rows of 30,000 labels.)
 // ---------------------------------------------------------------------------
-constexpr int TOPK_REG_K = 8;
+// A (score, label) pair as a double that orders by score, then by smaller label: the
+// score's value with the label (22 bits) below its last bit, complemented for positive
+// scores.  Infinite scores become +-2^128 (so that the label bits make no NaN); NaN
+// scores and labels past L become the empty key, below every other.
+constexpr int TOPK_REG_K = 8;  // longer lists: 32 entries, 32 rows per wave
+constexpr double TOPK_INF = 0x1p128, TOPK_EMPTY = -0x1p200, TOPK_FENCE = 0x1p300;
+constexpr unsigned TOPK_ID_MASK = (1u << 22) - 1;
 
-__device__ __forceinline__ bool better(float s, int i, float ts, int ti) {
-  return s > ts || (s == ts && i < ti);
+__device__ __forceinline__ double max_key(double a, double b) {
+  double d;
+  asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));  // (no canonicalising moves: no key is NaN)
+  return d;
+}
+__device__ __forceinline__ double min_key(double a, double b) {
+  double d;
+  asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ double topk_key(float sc, int id, int L) {
+  sc += 0.0f;  // -0 ranks with +0
+  const double d = min_key(max_key((double)sc, -TOPK_INF), TOPK_INF);
+  const unsigned flip = ~(unsigned)(__builtin_bit_cast(int, sc) >> 31) & TOPK_ID_MASK;
+  const uint64_t u = __builtin_bit_cast(uint64_t, d) | ((unsigned)id ^ flip);
+  return sc == sc && id < L ? __builtin_bit_cast(double, u) : TOPK_EMPTY;
+}
+__device__ __forceinline__ float topk_score(double key) { return (float)key; }  // the label bits round away
+__device__ __forceinline__ int topk_id(double key) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, key);
+  return (int)(((unsigned)u ^ ((u >> 63) ? 0u : TOPK_ID_MASK)) & TOPK_ID_MASK);
 }
 
 template <bool BF16, int NB, int KR>
 __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
     const float* __restrict__ W2, const float* __restrict__ b2, int L,
     const typename Mma<BF16>::elem* __restrict__ H1, int B, int tiles_per_split, int n_tiles,
-    int s_eff, int k, float* __restrict__ part_s, int32_t* __restrict__ part_i) {
+    int s_eff, int k, double* __restrict__ part) {
   using M = Mma<BF16>;
   using E = typename M::elem;
   using Fr = typename M::frag;
@@ -634,7 +658,6 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
   constexpr int P = FwdRing<BF16>::P, NRING = FwdRing<BF16>::N;
   __shared__ __attribute__((aligned(16))) E wr[NRING][tile_elems<BF16>()];
   __shared__ __attribute__((aligned(16))) float bt[NRING][OUT_TILE];
-  extern __shared__ float lists[];  // KR = 0: RB x k scores, then RB x k ids
 
   const int lane = threadIdx.x & 63, g = lane >> 5, n = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -650,28 +673,13 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
   const W2Src src = w2_src(W2, b2, L);
   const int rbase[2] = {tw_row_base(n, g, 0), tw_row_base(n, g, 1)};
 
-  // KR = 0: the wave's lists in LDS, sorted, k entries per row
-  float* const ls = lists + wave * WROWS * k;
-  int* const li = reinterpret_cast<int*>(lists + RB * k) + wave * WROWS * k;
-  if constexpr (KR == 0) {
-    for (int e = lane; e < WROWS * k; e += 64) {
-      ls[e] = -INFINITY;
-      li[e] = 0x7fffffff;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  }
-  // KR > 0: the row's list in registers; the first KR - k entries are held by
-  // (+inf, -1), which nothing displaces, so the k-th best is always the last entry
-  constexpr int KN = KR > 0 ? KR : 1;
-  float ks[NB][KN];
-  int ki[NB][KN];
+  // the rows' lists, best first; the first KR - k entries hold a key that nothing
+  // displaces, so the k-th best is always the last entry
+  double keys[NB][KR];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int j = 0; j < KN; ++j) {
-      ks[nb][j] = KR > 0 && j < KR - k ? INFINITY : -INFINITY;
-      ki[nb][j] = KR > 0 && j < KR - k ? -1 : 0x7fffffff;
-    }
+    for (int j = 0; j < KR; ++j) keys[nb][j] = j < KR - k ? TOPK_FENCE : TOPK_EMPTY;
   Fr hf[NB][4][NCH];
   float thr[NB];  // the row's k-th best score so far (+inf: no such row, nothing reaches it)
   bool rvalid[NB];
@@ -687,7 +695,13 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
 #pragma unroll
       for (int c = 0; c < NCH; ++c) hf[nb][kb][c] = h1_frag<BF16>(hrow, kb, c, g);
   }
-  // (the loop's wait counters then track only the W2 prefetch, as in k_out_fwd_train)
+  // the first P + 3 tiles, requested together
+  TileRegs pre[P + 1], tr0, tr1;
+#pragma unroll
+  for (int u = 0; u <= P; ++u) tile_load(src, min(t_begin + u, t_last), pre[u]);
+  tile_load(src, min(t_begin + P + 1, t_last), tr0);
+  tile_load(src, min(t_begin + P + 2, t_last), tr1);
+  // (the loop's wait counters then track only the W2 prefetch)
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -716,80 +730,36 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
   };
   // Scores of tile t into the lists.  Most tiles hold none that reaches its row's
   // k-th: one maximum per row and a vote.
-  auto rank = [&](int t, f32x16 (&z)[NB]) {
+  auto rank = [&](int t, const f32x16 (&z)[NB]) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       float m = z[nb][0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) m = fmaxf(m, z[nb][r]);  // (ignores NaN: those are never ranked)
       if (!__any(m >= thr[nb])) continue;
-      const float gone = __builtin_nanf("");
-      if (t == n_tiles - 1) {  // labels past L (their logits are -inf) are not ranked either
+      unsigned hits = 0;  // registers with a score that reaches some row's list
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (t * OUT_TILE + 8 * (r >> 2) + 4 * g + (r & 3) >= L) z[nb][r] = gone;
-      }
+      for (int r = 0; r < 16; ++r) hits |= __any(z[nb][r] >= thr[nb]) ? 1u << r : 0u;
 #pragma unroll 1
-      for (;;) {
-        // the lane's best remaining score, at its smallest label
-        m = z[nb][0];
+      while (hits) {
+        const int r = __builtin_ctz(hits);
+        hits &= hits - 1;
+        // the keys of the row's two lanes, on both (through integers, see half_swap_max)
+        const uint64_t u = __builtin_bit_cast(
+            uint64_t, topk_key(z[nb][r], t * OUT_TILE + 8 * (r >> 2) + 4 * g + (r & 3), L));
+        const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+        const unsigned l0 = lo[0], l1 = lo[1], h0 = hi[0], h1 = hi[1];
+        double c0 = __builtin_bit_cast(double, (uint64_t)h0 << 32 | l0);
+        double c1 = __builtin_bit_cast(double, (uint64_t)h1 << 32 | l1);
 #pragma unroll
-        for (int r = 1; r < 16; ++r) m = fmaxf(m, z[nb][r]);
-        int mr = 16;
-#pragma unroll
-        for (int r = 15; r >= 0; --r) mr = z[nb][r] == m ? r : mr;
-        const bool some = mr < 16;
-        const int my_id = some ? t * OUT_TILE + 8 * (mr >> 2) + 4 * g + (mr & 3) : 0x7fffffff;
-        // and the better one of the row's two lanes (through integers, see half_swap_max)
-        const unsigned us = __builtin_bit_cast(unsigned, some ? m : -INFINITY), ui = (unsigned)my_id;
-        const auto ss = __builtin_amdgcn_permlane32_swap(us, us, false, false);
-        const auto si = __builtin_amdgcn_permlane32_swap(ui, ui, false, false);
-        const unsigned s0 = ss[0], s1 = ss[1], i0 = si[0], i1 = si[1];
-        float cs = __builtin_bit_cast(float, s0);
-        int ci = (int)i0;
-        if (better(__builtin_bit_cast(float, s1), (int)i1, cs, ci)) {
-          cs = __builtin_bit_cast(float, s1);
-          ci = (int)i1;
+        for (int j = 0; j < KR; ++j) {
+          const double k0 = max_key(keys[nb][j], c0);
+          c0 = min_key(keys[nb][j], c0);
+          keys[nb][j] = max_key(k0, c1);
+          c1 = min_key(k0, c1);
         }
-        if constexpr (KR > 0) {
-          const bool in = rvalid[nb] && better(cs, ci, ks[nb][KN - 1], ki[nb][KN - 1]);
-          if (!__any(in)) break;
-          const bool mine = in && some && ci == my_id;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) z[nb][r] = mine && r == mr ? gone : z[nb][r];
-#pragma unroll
-          for (int j = 0; j < KN; ++j) {
-            const bool up = in && better(cs, ci, ks[nb][j], ki[nb][j]);
-            const float os = ks[nb][j];
-            const int oi = ki[nb][j];
-            ks[nb][j] = up ? cs : os;
-            ki[nb][j] = up ? ci : oi;
-            cs = up ? os : cs;
-            ci = up ? oi : ci;
-          }
-          if (rvalid[nb]) thr[nb] = ks[nb][KN - 1];
-        } else {
-          float* const lsr = ls + (nb * 32 + n) * k;
-          int* const lir = li + (nb * 32 + n) * k;
-          const bool in = rvalid[nb] && better(cs, ci, lsr[k - 1], lir[k - 1]);
-          if (!__any(in)) break;
-          const bool mine = in && some && ci == my_id;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) z[nb][r] = mine && r == mr ? gone : z[nb][r];
-          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-          if (in && g == 0) {
-            int pos = k - 1;
-            while (pos > 0 && better(cs, ci, lsr[pos - 1], lir[pos - 1])) {
-              lsr[pos] = lsr[pos - 1];
-              lir[pos] = lir[pos - 1];
-              --pos;
-            }
-            lsr[pos] = cs;
-            lir[pos] = ci;
-          }
-          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-          if (rvalid[nb]) thr[nb] = lsr[k - 1];
-        }
+        if (rvalid[nb]) thr[nb] = topk_score(keys[nb][KR - 1]);
       }
     }
   };
@@ -798,20 +768,14 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
   // NRING; the iteration of tile t issues the logits of t+1, ranks those of t,
   // stores tile t+P+1 (loaded two iterations earlier) and loads t+P+3; a barrier
   // closes every P-th iteration.  Indices are clamped to the split's last tile.
-  TileRegs tr0, tr1;
   auto slot = [&](int u) { return (u - t_begin) % NRING; };
 #pragma unroll
-  for (int u = 0; u <= P; ++u) {
-    const int tu = min(t_begin + u, t_last);
-    tile_load(src, tu, tr0);
-    tile_store<BF16, false>(tr0, L, tu, wr[u], nullptr, bt[u]);
-  }
-  tile_load(src, min(t_begin + P + 1, t_last), tr0);
-  tile_load(src, min(t_begin + P + 2, t_last), tr1);
+  for (int u = 0; u <= P; ++u)
+    tile_store<BF16, false>(pre[u], L, min(t_begin + u, t_last), wr[u], nullptr, bt[u]);
   __syncthreads();
   f32x16 z[NB], zn[NB];
   if (active) z_tile(0, z);
-  auto iteration = [&](int t, TileRegs& tr, f32x16 (&zc)[NB], f32x16 (&zx)[NB]) {
+  auto iteration = [&](int t, TileRegs& tr, const f32x16 (&zc)[NB], f32x16 (&zx)[NB]) {
     const int bst = slot(t + P + 1);
     if (active) {
       z_tile(slot(t + 1), zx);
@@ -827,27 +791,13 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
     iteration(t + 1, tr1, zn, z);
   }
   // row-major lists: the combine reads a row's candidates as one run
-  if constexpr (KR == 0) {
-    for (int e = lane; e < WROWS * k; e += 64) {
-      const int row = row0 + e / k;
-      if (row < B) {
-        const size_t o = ((size_t)row * s_eff + split) * k + e % k;
-        part_s[o] = ls[e];
-        part_i[o] = li[e];
-      }
-    }
-  } else {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      if (!rvalid[nb] || g) continue;
-      const size_t o = ((size_t)(row0 + nb * 32 + n) * s_eff + split) * k;
+  for (int nb = 0; nb < NB; ++nb) {
+    if (!rvalid[nb] || g) continue;
+    double* o = part + ((size_t)(row0 + nb * 32 + n) * s_eff + split) * k;
 #pragma unroll
-      for (int j = 0; j < KN; ++j)
-        if (j >= KR - k) {
-          part_s[o + j - (KR - k)] = ks[nb][j];
-          part_i[o + j - (KR - k)] = ki[nb][j];
-        }
-    }
+    for (int j = 0; j < KR; ++j)
+      if (j >= KR - k) o[j - (KR - k)] = keys[nb][j];
   }
 }
 
@@ -868,105 +818,78 @@ TopkShape topk_shape(bool use_bf16, int B, int k, int n_tiles, int n_cu) {
 }
 
 hipError_t launch_out_fwd_topk(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
-                               int B, const TopkShape& sh, int k, float* part_s, int32_t* part_i,
-                               hipStream_t st) {
+                               int B, const TopkShape& sh, int k, double* part, hipStream_t st) {
   const int n_tiles = (L + OUT_TILE - 1) / OUT_TILE;
   const dim3 grid(sh.splits * sh.nrb), block(FWD_THREADS);
-  auto go = [&](auto kern, auto* h1, size_t lds) {
-    // up to 64 KB of lists beside the ring: above the default limit of a launch
-    if (lds) {
-      const hipError_t e =
-          hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kern, grid, block, lds, st, W2, b2, L, h1, B, sh.tps, n_tiles, sh.splits, k, part_s, part_i);
+  auto go = [&](auto kern, auto* h1) {
+    hipLaunchKernelGGL(kern, grid, block, 0, st, W2, b2, L, h1, B, sh.tps, n_tiles, sh.splits, k, part);
     return hipGetLastError();
   };
-  const size_t lds = (size_t)FwdShape<true>::WAVES * 32 * k * (sizeof(float) + sizeof(int));
   if (!use_bf16) {
     const float* h = (const float*)H1;
-    if (k == 1) return go(k_out_fwd_topk<false, 1, 1>, h, 0);
-    if (k <= TOPK_REG_K) return go(k_out_fwd_topk<false, 1, TOPK_REG_K>, h, 0);
-    return go(k_out_fwd_topk<false, 1, 0>, h, lds);
+    if (k == 1) return go(k_out_fwd_topk<false, 1, 1>, h);
+    return k <= TOPK_REG_K ? go(k_out_fwd_topk<false, 1, TOPK_REG_K>, h) : go(k_out_fwd_topk<false, 1, 32>, h);
   }
   const bf16* h = (const bf16*)H1;
-  if (k == 1) return sh.nb == 2 ? go(k_out_fwd_topk<true, 2, 1>, h, 0) : go(k_out_fwd_topk<true, 1, 1>, h, 0);
-  if (k <= TOPK_REG_K)
-    return sh.nb == 2 ? go(k_out_fwd_topk<true, 2, TOPK_REG_K>, h, 0) : go(k_out_fwd_topk<true, 1, TOPK_REG_K>, h, 0);
-  return go(k_out_fwd_topk<true, 1, 0>, h, lds);
+  if (sh.nb == 2) return k == 1 ? go(k_out_fwd_topk<true, 2, 1>, h) : go(k_out_fwd_topk<true, 2, TOPK_REG_K>, h);
+  if (k == 1) return go(k_out_fwd_topk<true, 1, 1>, h);
+  return k <= TOPK_REG_K ? go(k_out_fwd_topk<true, 1, TOPK_REG_K>, h) : go(k_out_fwd_topk<true, 1, 32>, h);
 }
 
 // Final top-k of a row from its splits' sorted lists, by one wavefront: the
-// row's candidates come into LDS as one run, lane l keeps the heads of lists l,
-// l + 64, ..., and each of the k rounds takes the best head and advances its
-// list.  (An exhausted or unfilled list's head is (-inf, INT_MAX).)
+// row's keys come into LDS as one run, lane l keeps the heads of lists l, l + 64,
+// ..., and each of the k rounds takes the best head and advances its list.
 constexpr int TOPK_LISTS = 6;  // lists per lane: up to 384 splits
 
-__global__ __launch_bounds__(64) void k_topk_combine(int splits, int k, const float* __restrict__ part_s,
-                                                     const int32_t* __restrict__ part_i,
+__global__ __launch_bounds__(64) void k_topk_combine(int splits, int k, const double* __restrict__ part,
                                                      int32_t* __restrict__ ids, float* __restrict__ scores) {
-  extern __shared__ float csm[];
+  extern __shared__ double ck[];
   const int i = blockIdx.x, lane = threadIdx.x;
   const int nc = splits * k;
-  float* cs = csm;
-  int* ci = reinterpret_cast<int*>(csm + nc);
-  const float* ps = part_s + (size_t)i * nc;
-  const int32_t* pi = part_i + (size_t)i * nc;
-  for (int e = lane; e < nc; e += 64) {
-    cs[e] = ps[e];
-    ci[e] = pi[e];
+  const double* pr = part + (size_t)i * nc;
+  constexpr int BATCH = 8;  // keys in flight per lane (one latency per 512 of them)
+  for (int e0 = lane; e0 < nc; e0 += 64 * BATCH) {
+    double v[BATCH];
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) v[j] = pr[min(e0 + 64 * j, nc - 1)];
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j)
+      if (e0 + 64 * j < nc) ck[e0 + 64 * j] = v[j];
   }
   __syncthreads();
-  float hs[TOPK_LISTS];
-  int hi[TOPK_LISTS], pos[TOPK_LISTS];
+  double head[TOPK_LISTS];
+  int pos[TOPK_LISTS];
 #pragma unroll
   for (int j = 0; j < TOPK_LISTS; ++j) {
     const int l = lane + 64 * j;
     pos[j] = 0;
-    hs[j] = l < splits ? cs[l * k] : -INFINITY;
-    hi[j] = l < splits ? ci[l * k] : 0x7fffffff;
+    head[j] = l < splits ? ck[l * k] : TOPK_EMPTY;
   }
   for (int out = 0; out < k; ++out) {
-    float bs = hs[0];
-    int bi = hi[0];
+    double best = head[0];
 #pragma unroll
-    for (int j = 1; j < TOPK_LISTS; ++j)
-      if (better(hs[j], hi[j], bs, bi)) {
-        bs = hs[j];
-        bi = hi[j];
-      }
+    for (int j = 1; j < TOPK_LISTS; ++j) best = max_key(best, head[j]);
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      const float os = __shfl_xor(bs, o);
-      const int oi = __shfl_xor(bi, o);
-      if (better(os, oi, bs, bi)) {
-        bs = os;
-        bi = oi;
-      }
-    }
-    const bool none = bi == 0x7fffffff;  // ids are unique: the winner's list is the one whose head has its id
+    for (int o = 32; o >= 1; o >>= 1) best = max_key(best, __shfl_xor(best, o));
+    const bool none = best == TOPK_EMPTY;  // other keys are unique: the winner's list is the one with this head
 #pragma unroll
     for (int j = 0; j < TOPK_LISTS; ++j)
-      if (!none && hi[j] == bi) {
-        const int e = (lane + 64 * j) * k + ++pos[j];
-        hs[j] = pos[j] < k ? cs[e] : -INFINITY;
-        hi[j] = pos[j] < k ? ci[e] : 0x7fffffff;
-      }
+      if (!none && head[j] == best) head[j] = ++pos[j] < k ? ck[(lane + 64 * j) * k + pos[j]] : TOPK_EMPTY;
     if (lane == 0) {
-      ids[(size_t)i * k + out] = none ? -1 : bi;
-      if (scores) scores[(size_t)i * k + out] = none ? -INFINITY : bs;
+      ids[(size_t)i * k + out] = none ? -1 : topk_id(best);
+      if (scores) scores[(size_t)i * k + out] = none ? -INFINITY : topk_score(best);
     }
   }
 }
 
-hipError_t launch_topk_combine(int B, int splits, int k, const float* part_s,
-                               const int32_t* part_i, int32_t* ids, float* scores, hipStream_t st) {
+hipError_t launch_topk_combine(int B, int splits, int k, const double* part, int32_t* ids, float* scores,
+                               hipStream_t st) {
   if (splits > 64 * TOPK_LISTS) return hipErrorInvalidValue;
-  const size_t shm = (size_t)splits * k * (sizeof(float) + sizeof(int));
+  const size_t shm = (size_t)splits * k * sizeof(double);
   const hipError_t e =
       hipFuncSetAttribute((const void*)k_topk_combine, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_topk_combine, dim3(B), dim3(64), shm, st, splits, k, part_s, part_i, ids, scores);
+  hipLaunchKernelGGL(k_topk_combine, dim3(B), dim3(64), shm, st, splits, k, part, ids, scores);
   return hipGetLastError();
 }
 

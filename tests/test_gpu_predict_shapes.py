@@ -33,7 +33,7 @@ def check(s, rows, k, nan=False):
 
 
 # rows: one, a wave's edge, the change from 32 to 64 rows per wave (256 / 257), its row
-# block (512 / 513); k: one entry, lists in registers (up to 8), lists in LDS (up to 32)
+# block (512 / 513); k: one entry, lists of up to 8, lists of up to 32
 @pytest.mark.parametrize("rows,k", [(1, 1), (1, 32), (31, 5), (33, 8), (33, 9), (256, 1), (257, 8), (257, 9), (512, 1),
                                     (513, 3), (1025, 8), (1025, 32)])
 @pytest.mark.parametrize("bf16", [True, False])
