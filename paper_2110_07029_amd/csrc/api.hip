@@ -142,8 +142,6 @@ struct asgd_model {
   // internal stream may then start the next step's gather without waiting for
   // the model's stream (the previous backward only reads the other copies)
   bool pipe = false;
-  // whether the gather runs on the internal stream (see asgd_train_step)
-  bool gather_aux = false;
   float* tw = nullptr;   // per row: mean of W2[y] over the row's labels (pre-update)
   float* dA1 = nullptr;
   float* lse = nullptr;
@@ -411,20 +409,39 @@ asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipS
   return ASGD_OK;
 }
 
-asgd_status run_sort(asgd_model* m, hipStream_t st, int n_keys, const int32_t** sk,
-                     const int32_t** sv) {
-  const int key_bits = bit_width((uint32_t)m->F);  // invalid ids carry key F
-  TIMED_ON(m, ASGD_K_SORT, st,
-           launch_sort(m->keys, n_keys, key_bits, m->ka, m->va, m->kb, m->vb, m->hist, sk, sv, st));
+// Whether a training step puts the first layer's work (gather, sort, dA1, sparse
+// update) on the internal stream, beside the output layer.  That hides it, but each
+// pair of streams' event and wait costs 10-13 us of host time and a gap of 5-8 us on
+// the GPU, so it pays only beside a long output layer or when the first layer's own
+// work is long.  Measured, us per step, one stream | two, at 75 entries per row:
+//   L = 30,000,  B = 256:  74 | 78     L = 120,000, B = 256: 106 | 104
+//   L = 205,443, B = 128: 133 | 145    L = 250,000, B = 256: 157 | 147
+//   L = 670,091, B = 256: 296 | 270    L = 670,091, B = 1024: 880 | 803
+//   L = 10,000,  B = 1024 (77,000 entries): 188 | 123; L = 60,000: 211 | 163
+bool overlap_pays(const asgd_model* m, int B, int nnz) {
+  // forward and backward of the output layer: per label 0.2 ns of memory traffic and
+  // 0.87 ns per 1,000 rows of products; the stored-logits path takes about three times that
+  const double out_us = (double)m->L * (2e-4 + 8.7e-7 * B) * (m->unfused ? 3.0 : 1.0);
+  return out_us >= 70.0 || nnz > 49152;  // (below SORT_RIDE_MAX)
+}
+
+SortPlan plan_sort(asgd_model* m, int n_keys) {
+  // (invalid ids carry key F)
+  return sort_plan(m->keys, n_keys, bit_width((uint32_t)m->F), m->ka, m->va, m->kb, m->vb);
+}
+
+asgd_status run_sort(asgd_model* m, hipStream_t st, const SortPlan& plan) {
+  TIMED_ON(m, ASGD_K_SORT, st, launch_sort(plan, m->hist, st));
   return ASGD_OK;
 }
 
 // The fused output-layer forward and the per-row lse / target terms on the
 // model's stream; with y, dA1 (dA2 with the second hidden layer) follows on
 // da_stream, after an event when that is another stream (the training step
-// runs it beside the backward).
+// runs it beside the backward).  With sort (da_stream the model's stream), the
+// passes of the feature sort run inside the two launches.
 asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int rows_pad,
-                        const LabelJob* labels, hipStream_t da_stream, hipEvent_t fused_done = nullptr) {
+                        const LabelJob* labels, hipStream_t da_stream, const SortPlan* sort = nullptr) {
   const int B = x->n_rows;
   const int splits = fwd_splits(m, B);
   const int n_tiles = (m->L + OUT_TILE - 1) / OUT_TILE;
@@ -433,7 +450,8 @@ asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int
   if ((int64_t)s_eff * rows_pad > m->part_rows) return fail(ASGD_ERANGE, "partial buffer too small");
   TIMED_LAUNCH(m, ASGD_K_OUT_FWD,
                launch_out_fwd_train(m->bf16, m->W2(), m->b2(), m->L, m->H1, B, splits, m->m_part, m->s_part,
-                                    m->o_part, rows_pad, labels, &m->label_plan, m->stream, t0_, t1_));
+                                    m->o_part, rows_pad, labels, &m->label_plan, sort && sort->passes > 0 ? &sort->pass[0] : nullptr,
+                                    m->n_cu, m->stream, t0_, t1_));
   CsrDev yd = y ? dev(y) : CsrDev{};
   float* const A = m->extra ? m->A2 : m->A1;
   float* const dA = m->extra ? m->dA2 : m->dA1;
@@ -442,9 +460,8 @@ asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int
   TIMED(m, ASGD_K_OUT_COMBINE, launch_out_lse_targets(m->bf16, B, s_eff, m->m_part, m->s_part, rows_pad, m->W2(),
                                                       m->b2(), m->L, m->H1, y ? &yd : nullptr, m->lse,
                                                       m->loss_rows, m->tw, m->o_part, A, fused ? dA : nullptr,
-                                                      m->stream,
-                                                      fused ? fused_done
-                                                            : y && da_stream != m->stream ? m->ev_dA1 : nullptr));
+                                                      sort && sort->passes > 1 ? &sort->pass[1] : nullptr, m->stream,
+                                                      y && !fused ? m->ev_dA1 : nullptr));
   if (!y || fused) return ASGD_OK;
   // the event was completed by the lse/targets launch itself: a separate record
   // would put a marker between lse/targets and the backward on the model's
@@ -524,14 +541,6 @@ asgd_status asgd_model_init(asgd_model** out, const asgd_config* cfg, uint64_t s
   m->bf16 = cfg->gemm_bf16 == 1;
   m->extra = cfg->extra_hidden_layers == 1;
   m->unfused = (cfg->flags & ASGD_UNFUSED_OUTPUT) != 0;
-  // The gather moves to the internal stream, beside the previous step's
-  // backward, when the output layer dominates the step: with many labels per
-  // batch entry the internal stream (gather, sort, sparse update: work in
-  // proportion to the batch's entries) then stays shorter than the model's
-  // stream (work in proportion to L).  Measured: L / max_nnz of 33 (the
-  // wide-label workload) gains 5 us per step; 4.9 (wide-feature) and 0.4
-  // (tiny) lose 14 and 17 us, the internal stream becoming the longer one.
-  m->gather_aux = !m->unfused && (int64_t)cfg->n_labels >= 8 * std::max<int64_t>(cfg->max_nnz, 1);
   m->elem = m->bf16 ? 2 : 4;
   m->stream = (hipStream_t)hip_stream;
   m->rows_pad_max = (int)round_up(cfg->max_batch, out_rows_per_block(m->bf16));
@@ -702,18 +711,21 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
   if (!(lr == lr)) return fail(ASGD_EINVAL, "lr is NaN");
   const int B = x->n_rows;
   int rows_pad = 0;
-  const int32_t *sk = nullptr, *sv = nullptr;
+  const SortPlan sort = plan_sort(m, x->nnz);
   const LabelJob labels{m->lkeys, y->nnz, m->lrow, m->lbeg, m->lpair, m->lcnt, 0};
   CsrDev xd = dev(x);
-  m->pipe = m->pipe && m->gather_aux;
-  if (m->gather_aux) {
+  const bool two_streams = overlap_pays(m, B, x->nnz);
+  const bool pipelined = two_streams && !m->unfused;
+  const bool one_stream = !two_streams;
+  m->pipe = m->pipe && pipelined;
+  if (pipelined) {
     // Two streams.  Internal: gather (after the previous step's W1 update,
     // so it overlaps that step's output-layer backward), feature sort, then,
     // once the forward's partials and target terms exist, dA1, the second
     // hidden layer's backward, the sparse W1 update, b1 and the mean loss.
     // Model's stream: forward (whose launch also groups the labels), lse and
     // target terms, backward with the W2 update; the step ends when both have
-    // finished.  Unless the previous call was a training step, the internal
+    // finished.  Unless the previous call was such a step, the internal
     // stream first waits for the model's stream.
     if (!m->pipe) {
       HIP_TRY(hipEventRecord(m->ev_fork, m->stream));
@@ -723,7 +735,7 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
     s = run_gather(m, x, y, m->aux, &rows_pad, m->ev_fork);
     if (s) return s;
     HIP_TRY(hipStreamWaitEvent(m->stream, m->ev_fork, 0));
-    s = run_sort(m, m->aux, x->nnz, &sk, &sv);
+    s = run_sort(m, m->aux, sort);
     if (s) return s;
     s = run_forward(m, x, y, rows_pad, &labels, m->aux);
     if (s) return s;
@@ -731,36 +743,37 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
       TIMED_ON(m, ASGD_K_DENSE_BWD, m->aux, launch_dense_bwd(m->dA2, m->A1, m->Wh(), m->bh(), B, rows_pad, lr,
                                                              m->dA1, m->aux));
   } else {
-    // The gather and the output layer's forward, and with it dA1, on the
-    // model's stream; the feature sort on the internal stream beside them,
-    // and the sparse update beside the backward.
-    // (the events are completed by the launches themselves: a separate record
-    // would put a marker, and a gap, into the model's stream)
-    s = run_gather(m, x, y, m->stream, &rows_pad, m->ev_fork);
+    // One stream (the feature sort's passes inside the forward's and the per-row
+    // launch), or, with stored logits, the sort and the sparse update on the
+    // internal one, beside the logits and the backward.
+    const bool sort_rides = !m->unfused;  // (one stream: at most 49,152 entries)
+    s = run_gather(m, x, y, m->stream, &rows_pad, one_stream ? nullptr : m->ev_fork);
     if (s) return s;
-    HIP_TRY(hipStreamWaitEvent(m->aux, m->ev_fork, 0));
-    s = run_sort(m, m->aux, x->nnz, &sk, &sv);
-    if (s) return s;
-    // dA1's event: completed by the fused lse/targets + dA1 launch, or recorded
-    // after the stored-logits path or the second layer's backward
-    const bool dA1_by_launch = !m->unfused && !m->extra;
+    if (!sort_rides) {
+      if (!one_stream) HIP_TRY(hipStreamWaitEvent(m->aux, m->ev_fork, 0));
+      s = run_sort(m, one_stream ? m->stream : m->aux, sort);
+      if (s) return s;
+    }
     s = m->unfused ? run_forward_unfused(m, x, y, rows_pad, &labels)
-                   : run_forward(m, x, y, rows_pad, &labels, m->stream, dA1_by_launch ? m->ev_dA1 : nullptr);
+                   : run_forward(m, x, y, rows_pad, &labels, m->stream, &sort);
     if (s) return s;
     if (m->extra)
       TIMED(m, ASGD_K_DENSE_BWD, launch_dense_bwd(m->dA2, m->A1, m->Wh(), m->bh(), B, rows_pad, lr, m->dA1,
                                                   m->stream));
-    if (!dA1_by_launch) HIP_TRY(hipEventRecord(m->ev_dA1, m->stream));
-    HIP_TRY(hipStreamWaitEvent(m->aux, m->ev_dA1, 0));
+    if (!one_stream) {
+      HIP_TRY(hipEventRecord(m->ev_dA1, m->stream));
+      HIP_TRY(hipStreamWaitEvent(m->aux, m->ev_dA1, 0));
+    }
   }
-  TIMED_ON(m, ASGD_K_W1_UPDATE, m->aux,
-           launch_sparse_update(m->W1(), m->F, sk, sv, x->nnz, m->row_of, xd, m->dA1, lr, B, m->b1(),
-                                m->loss_rows, m->loss, m->w1_part, m->aux, m->ev_join));
+  hipStream_t const ust = one_stream ? m->stream : m->aux;
+  TIMED_ON(m, ASGD_K_W1_UPDATE, ust,
+           launch_sparse_update(m->W1(), m->F, sort.keys_out, sort.vals_out, x->nnz, m->row_of, xd, m->dA1, lr, B,
+                                m->b1(), m->loss_rows, m->loss, m->w1_part, ust, one_stream ? nullptr : m->ev_join));
   TIMED_LAUNCH(m, ASGD_K_OUT_BWD,
                launch_out_bwd(m->bf16, m->W2(), m->b2(), m->L, m->H1, m->H1T, m->rows_pad_max, B, m->lse, m->rw,
                               m->lbeg, m->lpair, lr, m->n_cu, m->stream, t0_, t1_));
-  HIP_TRY(hipStreamWaitEvent(m->stream, m->ev_join, 0));
-  m->pipe = m->gather_aux;
+  if (!one_stream) HIP_TRY(hipStreamWaitEvent(m->stream, m->ev_join, 0));
+  m->pipe = pipelined;
   if (loss_out) return asgd_model_last_loss(m, loss_out);
   return ASGD_OK;
 }
@@ -976,10 +989,10 @@ asgd_status asgd_debug_touched_rows(asgd_model* m, const asgd_csr* x, int32_t* i
   m->pipe = false;
   s = run_gather(m, x, nullptr, m->stream, &rows_pad);
   if (s) return s;
-  const int32_t *sk = nullptr, *sv = nullptr;
-  s = run_sort(m, m->stream, x->nnz, &sk, &sv);
+  const SortPlan sort = plan_sort(m, x->nnz);
+  s = run_sort(m, m->stream, sort);
   if (s) return s;
-  HIP_TRY(launch_touched(sk, x->nnz, m->F, ids_dev, m->count, m->stream));
+  HIP_TRY(launch_touched(sort.keys_out, x->nnz, m->F, ids_dev, m->count, m->stream));
   int32_t c = 0;
   HIP_TRY(hipMemcpyAsync(&c, m->count, sizeof(c), hipMemcpyDeviceToHost, m->stream));
   HIP_TRY(hipStreamSynchronize(m->stream));

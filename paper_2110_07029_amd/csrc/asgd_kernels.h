@@ -45,12 +45,31 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
 constexpr int SORT_CHUNK = 1024;   // keys per workgroup
 constexpr int SORT_MAX_BITS = 11;  // digit width limit per pass
 int sort_blocks(int n);
-// Sorts keys[0..n) (values < 2^key_bits) stably; the payload is the original
-// position.  Result in keys_out / vals_out.  tmp buffers of n entries, hist
-// and offs of sort_blocks(n) << SORT_MAX_BITS entries.
-hipError_t launch_sort(const int32_t* keys_in, int n, int key_bits, int32_t* keys_a,
-                       int32_t* vals_a, int32_t* keys_b, int32_t* vals_b, int32_t* hist,
-                       const int32_t** keys_out, const int32_t** vals_out, hipStream_t st);
+// One pass over the digit (key >> shift) & (2^nbits - 1): keys_in / vals_in (null: the
+// positions) to keys_out / vals_out.
+struct SortJob {
+  const int32_t *keys_in, *vals_in;
+  int n, shift, nbits;
+  int32_t *keys_out, *vals_out;
+  int per_thread;  // keys per thread of a workgroup inside another launch (sort_spread)
+};
+// The passes of a sort of n keys < 2^key_bits, the payload being the original position:
+// one or two.  Pass 0 writes keys_a / vals_a, pass 1 keys_b / vals_b.
+struct SortPlan {
+  int passes;
+  SortJob pass[2];
+  const int32_t *keys_out, *vals_out;
+};
+SortPlan sort_plan(const int32_t* keys_in, int n, int key_bits, int32_t* keys_a, int32_t* vals_a, int32_t* keys_b,
+                   int32_t* vals_b);
+// Enqueues every pass.  hist: 2 * (sort_blocks(n) << SORT_MAX_BITS) entries.
+hipError_t launch_sort(const SortPlan& plan, int32_t* hist, hipStream_t st);
+// A pass inside another launch (wg_sort_pass in aux_dev.h): n < 2^16; spread over at most
+// `wgs` workgroups of nthreads threads, whose number is returned, with sort_pass_lds bytes
+// of LDS each.
+constexpr int SORT_RIDE_MAX = (1 << 16) - 1;
+int sort_spread(SortJob* job, int nthreads, int wgs);
+int sort_pass_lds(int nbits, int nthreads);
 
 // ---- (label, row) pairs grouped by 32-label block ---------------------------
 // For the m label entries: lbeg[b] .. lbeg[b+1] (b < ceil(L/32)) is the range
@@ -67,6 +86,7 @@ struct LabelJob {
 };
 struct LabelJobPlan {
   int ok, lds_bytes, in_lds;
+  int lds_budget;  // dynamic LDS that the launch can have
 };
 LabelJobPlan label_job_plan(bool use_bf16, int L);
 // The same for the label-grouping workgroup of another launch of `nthreads` threads.
@@ -81,9 +101,10 @@ int out_rows_per_block(bool use_bf16);
 // label_job_plan).
 hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
                                 int B, int splits, float* m_part, float* s_part, float* o_part,
-                                int ld_part, const LabelJob* job, const LabelJobPlan* plan, hipStream_t st,
-                                hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
-// (t0, t1: optional events that the launch itself completes at the kernel's
+                                int ld_part, const LabelJob* job, const LabelJobPlan* plan, const SortJob* sort,
+                                int n_cu, hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// (sort: a pass of the feature sort to run in the same launch, with a label job only;
+// t0, t1: optional events that the launch itself completes at the kernel's
 // start and end, for timing the kernel alone)
 // Per row, after the forward: lse, and with y the loss and tw = mean_{y in Y_i} W2[y]
 // [B x 128] (reads W2 before the backward updates it).
@@ -92,8 +113,10 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
 hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float* m_part, const float* s_part,
                                   int ld_part, const float* W2, const float* b2, int L, const void* H1,
                                   const CsrDev* y, float* lse, float* loss_rows, float* tw, const float* o_part,
-                                  const float* A1, float* dA1, hipStream_t st, hipEvent_t done = nullptr);
-// (done: an event that the launch itself completes when the kernel has
+                                  const float* A1, float* dA1, const SortJob* sort, hipStream_t st,
+                                  hipEvent_t done = nullptr);
+// (sort: a pass of the feature sort to run in the same launch, with dA1 only;
+// done: an event that the launch itself completes when the kernel has
 // finished, with no marker of its own on the stream)
 // Per row: dA1 = ((O/s - tw) / B) * [A1 > 0] from the forward's partials (reads no W2);
 // wide: twice the threads per row (for a launch that runs alone, not beside the backward).

@@ -1,7 +1,8 @@
-// Device body of the label grouping of a training step, written for one
-// workgroup so that it can ride along inside a larger launch (the output-layer
-// forward gives it one workgroup of its own) instead of needing a launch, and
-// a cross-stream event, of its own.
+// Device bodies of the index work of a training step, written for workgroups
+// that can ride along inside a larger launch instead of needing launches, and a
+// cross-stream event, of their own: the label grouping (one workgroup of the
+// output-layer forward's launch) and a pass of the feature sort (workgroups of
+// the forward's and of the per-row launch after it).
 #pragma once
 
 #include "asgd_dev.h"
@@ -90,6 +91,109 @@ __device__ void wg_label_blocks(const int32_t* __restrict__ lkeys, int m, int L,
     if (lab >= 0 && lab < L) {
       const int pos = atomicAdd(&cnt[lab >> 5], 1);
       lpair[pos] = (lrow[q] << 5) | (lab & 31);
+    }
+  }
+}
+
+// One pass of the stable radix sort over digit d = (key >> shift) & (2^nbits - 1),
+// for chunk c of NT * per_thread keys, without any launch or exchange between
+// workgroups: the workgroup itself counts all n < 2^16 keys by digit (every digit's
+// total and its count before the chunk, as the halves of one LDS counter), scans the
+// totals, ranks its own keys by 64-lane ballots and running counts per wave, and
+// scatters them.  Every workgroup counts all the keys (LDS atomics, about one per clock
+// and CU), so this is for small batches: 18,600 keys take about as long as a short
+// output layer, beside which they cost nothing; 79,000 take several times a pass of
+// k_sort.hip.
+// lds: sort_pass_lds(nbits, NT) bytes, 16-byte aligned.
+template <int NT>
+__device__ void wg_sort_pass(const SortJob& j, int c, int32_t* lds) {
+  constexpr int W = NT / 64;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int nd = 1 << j.nbits, mask = nd - 1, n = j.n;
+  unsigned* cnt = reinterpret_cast<unsigned*>(lds);                    // [nd]: total | before the chunk << 16
+  unsigned short* wcnt = reinterpret_cast<unsigned short*>(cnt + nd);  // [W][nd]: this chunk's, by wave
+  int* wsum = reinterpret_cast<int*>(wcnt + W * nd);                   // [W]
+  const int32_t* __restrict__ keys = j.keys_in;
+  const int c0 = c * NT * j.per_thread;
+  const int p0 = c0 + w * 64 * j.per_thread + lane;  // a wave's keys are consecutive
+  for (int d = t; d < nd; d += NT) cnt[d] = 0;
+  for (int d = t; d < W * nd / 2; d += NT) reinterpret_cast<unsigned*>(wcnt)[d] = 0;
+  __syncthreads();
+  // four keys per 16-byte load, BATCH loads in flight
+  constexpr int BATCH = 8;
+  const int n4 = n >> 2;
+  auto count = [&](int k, int q) {
+    atomicAdd(&cnt[(k >> j.shift) & mask], q < c0 ? 0x10001u : 1u);
+  };
+  for (int q0 = t; q0 < n4; q0 += NT * BATCH) {
+    int4 v[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) v[u] = reinterpret_cast<const int4*>(keys)[min(q0 + u * NT, n4 - 1)];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int q = q0 + u * NT;
+      if (q < n4) {  // (a chunk starts at a multiple of four keys: all four lie on one side of it)
+        count(v[u].x, 4 * q);
+        count(v[u].y, 4 * q);
+        count(v[u].z, 4 * q);
+        count(v[u].w, 4 * q);
+      }
+    }
+  }
+  if (4 * n4 + t < n) count(keys[4 * n4 + t], 4 * n4 + t);
+  // lanes of the wave with the same digit
+  auto peers_of = [&](int d, bool valid) {
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < j.nbits; ++b) {
+      const bool bit = (d >> b) & 1;
+      const uint64_t bal = __ballot(bit);
+      peers &= bit ? bal : ~bal;
+    }
+    return peers;
+  };
+  const uint64_t below = (1ull << lane) - 1ull;
+  for (int it = 0; it < j.per_thread; ++it) {
+    const int p = p0 + 64 * it;
+    const bool valid = p < n;
+    const int d = ((valid ? keys[p] : 0) >> j.shift) & mask;
+    const uint64_t peers = peers_of(d, valid);
+    if (valid && (peers & below) == 0) wcnt[w * nd + d] += (unsigned short)__popcll(peers);
+  }
+  __syncthreads();
+  // exclusive scan of the totals, over contiguous digits per thread
+  const int per = (nd + NT - 1) / NT;
+  const int d0 = min(nd, t * per), d1 = min(nd, d0 + per);
+  int local = 0;
+  for (int x = d0; x < d1; ++x) local += (int)(cnt[x] & 0xffffu);
+  int total;
+  int run = wg_exclusive_scan<NT>(local, wsum, &total);
+  for (int x = d0; x < d1; ++x) {
+    const unsigned v = cnt[x];
+    cnt[x] = (unsigned)run + (v >> 16);  // the chunk's first position of digit x
+    run += (int)(v & 0xffffu);
+    int sum = 0;
+#pragma unroll
+    for (int ww = 0; ww < W; ++ww) {
+      const int m = wcnt[ww * nd + x];
+      wcnt[ww * nd + x] = (unsigned short)sum;
+      sum += m;
+    }
+  }
+  __syncthreads();
+  for (int it = 0; it < j.per_thread; ++it) {
+    const int p = p0 + 64 * it;
+    const bool valid = p < n;
+    const int key = valid ? keys[p] : 0;
+    const int val = valid ? (j.vals_in ? j.vals_in[p] : p) : 0;
+    const int d = (key >> j.shift) & mask;
+    const uint64_t peers = peers_of(d, valid);
+    const int before = __popcll(peers & below);
+    const int c = wcnt[w * nd + d];  // every peer reads the count before the leader updates it
+    if (valid && before == 0) wcnt[w * nd + d] = (unsigned short)(c + __popcll(peers));
+    if (valid) {
+      const int pos = (int)cnt[d] + c + before;
+      j.keys_out[pos] = key;
+      j.vals_out[pos] = val;
     }
   }
 }

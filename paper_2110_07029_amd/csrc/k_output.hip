@@ -46,13 +46,14 @@ struct FwdRing {
 // the forward leaves free) groups the batch's labels for the backward: it
 // depends only on the gather and finishes long before the forward, so the
 // backward needs no event from another stream.  Its counters live in the
-// launch's dynamic LDS (or in global memory when they do not fit).
+// launch's dynamic LDS (or in global memory when they do not fit).  With a
+// sort job, the workgroups after it run the feature sort's first pass.
 template <bool BF16>
 __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_train(
     const float* __restrict__ W2, const float* __restrict__ b2, int L,
     const typename Mma<BF16>::elem* __restrict__ H1, int B, int tiles_per_split, int n_tiles,
     float* __restrict__ m_part, float* __restrict__ s_part, float* __restrict__ o_part,
-    int ld_part, int s_eff, int n_fwd, LabelJob lj) {
+    int ld_part, int s_eff, int n_fwd, LabelJob lj, SortJob sj) {
   using M = Mma<BF16>;
   using E = typename M::elem;
   using Fr = typename M::frag;
@@ -64,9 +65,13 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_train(
   __shared__ __attribute__((aligned(16))) E wt[NRING][tileT_elems<BF16>()];
   __shared__ __attribute__((aligned(16))) float bt[NRING][OUT_TILE];
 
-  if ((int)blockIdx.x >= n_fwd) {
-    extern __shared__ int32_t job_lds[];
-      if (lj.in_lds)
+  extern __shared__ __attribute__((aligned(16))) int32_t job_lds[];
+  if ((int)blockIdx.x > n_fwd) {  // the feature sort's first pass
+    wg_sort_pass<FWD_THREADS>(sj, (int)blockIdx.x - n_fwd - 1, job_lds);
+    return;
+  }
+  if ((int)blockIdx.x == n_fwd) {
+    if (lj.in_lds)
       wg_label_blocks<FWD_THREADS, true>(lj.lkeys, lj.m, L, lj.lrow, lj.lbeg, lj.lpair, job_lds,
                                          job_lds + ((L + 31) >> 5));
     else
@@ -282,6 +287,7 @@ LabelJobPlan label_job_plan_for(const void* fn, int nthreads, int L) {
     return p;
   // what the kernel's own arrays leave of a workgroup's LDS (160 KB on gfx950)
   const int budget = lds_max - (int)fa.sharedSizeBytes;
+  p.lds_budget = budget;
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, budget) != hipSuccess) return p;
   const int ints = (L + 31) / 32 + nthreads / 64;
   p.in_lds = ints * 4 <= budget;
@@ -297,8 +303,8 @@ LabelJobPlan label_job_plan(bool use_bf16, int L) {
 
 hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
                                 int B, int splits, float* m_part, float* s_part, float* o_part,
-                                int ld_part, const LabelJob* job, const LabelJobPlan* plan, hipStream_t st,
-                                hipEvent_t t0, hipEvent_t t1) {
+                                int ld_part, const LabelJob* job, const LabelJobPlan* plan, const SortJob* sort,
+                                int n_cu, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   const int n_tiles = (L + OUT_TILE - 1) / OUT_TILE;
   const int tps = (n_tiles + splits - 1) / splits;
   const int s_eff = (n_tiles + tps - 1) / tps;
@@ -313,13 +319,24 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
     lds = plan->lds_bytes;
     n_job = 1;
   }
+  SortJob sj{};
+  if (sort && sort->n > 0) {
+    if (!job || sort->n > SORT_RIDE_MAX) return hipErrorInvalidValue;  // (its workgroups follow the label job's)
+    sj = *sort;
+    const int need = sort_pass_lds(sj.nbits, FWD_THREADS);
+    if (need > plan->lds_budget) return hipErrorInvalidValue;
+    if (need > lds) lds = need;
+    // on the CUs that the forward's own workgroups and the label job leave free: more
+    // workgroups than those would run one after the other
+    n_job += sort_spread(&sj, FWD_THREADS, n_cu - n_fwd % n_cu - 1);
+  }
   const dim3 grid(n_fwd + n_job), block(FWD_THREADS);
   if (use_bf16)
     hipExtLaunchKernelGGL(k_out_fwd_train<true>, grid, block, lds, st, t0, t1, 0, W2, b2, L, (const bf16*)H1, B,
-                          tps, n_tiles, m_part, s_part, o_part, ld_part, s_eff, n_fwd, lj);
+                          tps, n_tiles, m_part, s_part, o_part, ld_part, s_eff, n_fwd, lj, sj);
   else
     hipExtLaunchKernelGGL(k_out_fwd_train<false>, grid, block, lds, st, t0, t1, 0, W2, b2, L, (const float*)H1,
-                          B, tps, n_tiles, m_part, s_part, o_part, ld_part, s_eff, n_fwd, lj);
+                          B, tps, n_tiles, m_part, s_part, o_part, ld_part, s_eff, n_fwd, lj, sj);
   return hipGetLastError();
 }
 
@@ -346,6 +363,7 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
 // ---------------------------------------------------------------------------
 constexpr int CMB_THREADS = 512;
 constexpr int CMB_WAVES = CMB_THREADS / 64;   // 8
+constexpr int LSE_SORT_WGS = 64;    // sort workgroups beside the rows' (several fit on a CU)
 constexpr int DA_GROUPS = 8;        // beside the backward: 256 threads, 4 KB of LDS
 constexpr int DA_GROUPS_WIDE = 16;  // on the model's stream, where nothing runs beside it
 
@@ -432,20 +450,28 @@ __device__ __forceinline__ void da1_row(int i, int splits, const float* __restri
 }
 
 // DA: the row's dA1 as well, in the same workgroup (16 split groups), for a
-// step that runs it on the model's stream anyway: one launch instead of two.
+// step that runs it on the model's stream anyway: one launch instead of two;
+// the launch's workgroups past the rows then run a pass of the feature sort.
 template <bool BF16, bool DA>
 __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
     int splits, const float* __restrict__ m_part, const float* __restrict__ s_part, int ld_part,
     const float* __restrict__ W2, const float* __restrict__ b2, int L,
     const typename Mma<BF16>::elem* __restrict__ H1, CsrDev y, int has_y, float* __restrict__ lse_out,
     float* __restrict__ loss_rows, float* __restrict__ tw_out, const float* __restrict__ o_part,
-    const float* __restrict__ A1, float invB, float* __restrict__ dA1) {
+    const float* __restrict__ A1, int B, float invB, float* __restrict__ dA1, SortJob sj) {
   static_assert(!DA || CMB_THREADS == 32 * DA_GROUPS_WIDE, "dA1 takes the workgroup as 16 split groups");
   __shared__ float red_s[CMB_WAVES];
   __shared__ float red_m[CMB_WAVES];
   __shared__ float red_t[CMB_WAVES][HID];
   __shared__ float red_z[CMB_WAVES];
-  const int i = xcd_row((int)blockIdx.x, (int)gridDim.x), t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if constexpr (DA) {
+    extern __shared__ __attribute__((aligned(16))) int32_t job_lds[];
+    if ((int)blockIdx.x >= B) {  // the feature sort's second pass
+      wg_sort_pass<CMB_THREADS>(sj, (int)blockIdx.x - B, job_lds);
+      return;
+    }
+  }
+  const int i = xcd_row((int)blockIdx.x, B), t = threadIdx.x, lane = t & 63, w = t >> 6;
   {
     float mg = -INFINITY, St = 0.0f;
     for (int k = t; k < splits; k += CMB_THREADS)
@@ -560,17 +586,27 @@ __global__ __launch_bounds__(32 * GROUPS) void k_out_dA1(int splits, const float
 hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float* m_part, const float* s_part,
                                   int ld_part, const float* W2, const float* b2, int L, const void* H1,
                                   const CsrDev* y, float* lse, float* loss_rows, float* tw, const float* o_part,
-                                  const float* A1, float* dA1, hipStream_t st, hipEvent_t done) {
+                                  const float* A1, float* dA1, const SortJob* sort, hipStream_t st,
+                                  hipEvent_t done) {
   CsrDev yy = y ? *y : CsrDev{0, 0, 0, nullptr, nullptr, nullptr};
   const bool da = y && dA1;
   const float invB = 1.0f / (float)B;
+  SortJob sj{};
+  int lds = 0, n_sort = 0;
+  if (sort && sort->n > 0) {
+    if (!da || sort->n > SORT_RIDE_MAX) return hipErrorInvalidValue;
+    sj = *sort;
+    lds = sort_pass_lds(sj.nbits, CMB_THREADS);
+    n_sort = sort_spread(&sj, CMB_THREADS, LSE_SORT_WGS);
+  }
+  const dim3 grid(B + n_sort), block(CMB_THREADS);
   auto go = [&](auto kern, auto* h1) {
     if (done)
-      hipExtLaunchKernelGGL(kern, dim3(B), dim3(CMB_THREADS), 0, st, nullptr, done, 0, splits, m_part, s_part, ld_part,
-                            W2, b2, L, h1, yy, (int)(y != nullptr), lse, loss_rows, tw, o_part, A1, invB, dA1);
+      hipExtLaunchKernelGGL(kern, grid, block, lds, st, nullptr, done, 0, splits, m_part, s_part, ld_part, W2, b2, L,
+                            h1, yy, (int)(y != nullptr), lse, loss_rows, tw, o_part, A1, B, invB, dA1, sj);
     else
-      hipLaunchKernelGGL(kern, dim3(B), dim3(CMB_THREADS), 0, st, splits, m_part, s_part, ld_part, W2, b2, L, h1, yy,
-                         y != nullptr, lse, loss_rows, tw, o_part, A1, invB, dA1);
+      hipLaunchKernelGGL(kern, grid, block, lds, st, splits, m_part, s_part, ld_part, W2, b2, L, h1, yy,
+                         y != nullptr, lse, loss_rows, tw, o_part, A1, B, invB, dA1, sj);
   };
   if (use_bf16) {
     if (da)
@@ -622,7 +658,10 @@ constexpr unsigned TOPK_ID_MASK = (1u << 22) - 1;
 
 __device__ __forceinline__ double max_key(double a, double b) {
   double d;
-  asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));  // (no canonicalising moves: no key is NaN)
+  // (asm: no canonicalising moves, as no key is NaN.  The compiler does not count it for
+  // a matrix product's late read of its C registers; the last product whose C is not its
+  // own result is issued 15 products before any key is formed.)
+  asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
   return d;
 }
 __device__ __forceinline__ double min_key(double a, double b) {

@@ -3,17 +3,20 @@
 // gradient becomes a segmented reduction over equal feature ids (no contended
 // atomics, fixed summation order).
 //
-// One pass over a digit of up to 11 bits = three launches:
+// One pass over a digit of up to 11 bits:
 //   hist    : per-workgroup digit counts of a 1024-key chunk (LDS counters),
 //             stored block-major: hist[block][digit]
-//   scan    : exclusive scan over (digit, workgroup) -> global scatter offsets,
-//             every read and write coalesced across the digits
-//   scatter : stable ranks inside the chunk from 64-lane ballots (lanes with the
-//             same digit in one wave), per-wave running counts, then a prefix
-//             over the four waves; keys land at offset + rank.
-// hist and scatter size their LDS counters by the pass's digit width (dynamic
-// LDS, 4 << bits and 16 << bits bytes), not by the widest digit: a narrow pass
-// then fits on a CU beside the output-layer kernels of the other stream.
+//   scatter : every workgroup sums the digits' counts (all chunks' and those before
+//             its own) and scans them into its scatter offsets; stable ranks inside
+//             the chunk from 64-lane ballots (lanes with the same digit in one wave),
+//             per-wave running counts, then a prefix over the four waves; keys land
+//             at offset + rank.
+// Summing in the scatter reads (chunks)^2 rows of counts, so above SORT_SELF_SCAN
+// chunks a launch of its own (scan, one workgroup) forms the offsets.  Up to there it
+// was the longest of the three: 14.7 us of 35 us per pass for 79,000 keys of 18 bits.
+// hist and scatter size their LDS by the pass's digit width (dynamic LDS, 4 << bits
+// and 12 << bits bytes), not by the widest digit: a narrow pass then fits on a CU
+// beside the output-layer kernels of the other stream.
 #include "asgd_dev.h"
 #include "asgd_kernels.h"
 
@@ -118,29 +121,72 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_sort_scan(const int32_t* __res
   }
 }
 
-__global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
-    const int32_t* __restrict__ keys_in, const int32_t* __restrict__ vals_in, int n, int shift,
-    int nbits, int nblk, const int32_t* __restrict__ offs, int32_t* __restrict__ keys_out,
-    int32_t* __restrict__ vals_out) {
-  extern __shared__ int wcnt_lds[];  // SORT_WAVES x (1 << nbits) counters
-  const int nd = 1 << nbits;
-  auto wcnt = [&](int ww, int d) -> int& { return wcnt_lds[ww * nd + d]; };
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int d = lane; d < nd; d += 64) wcnt(w, d) = 0;
-  __syncthreads();
-  const int p0 = blockIdx.x * SORT_CHUNK + w * SORT_PER_WAVE;
-  const uint64_t below = (1ull << lane) - 1ull;
+constexpr int SORT_SELF_SCAN = 128;
+
+// offs: the scan's offsets, or null: this workgroup forms its own from hist.
+__global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(SortJob j, int nblk, const int32_t* __restrict__ hist,
+                                                               const int32_t* __restrict__ offs) {
+  extern __shared__ int lds_sc[];
+  const int nd = 1 << j.nbits, mask = nd - 1, n = j.n;
+  int* base = lds_sc;  // [nd]: the chunk's first position of every digit
+  unsigned short* wcnt_lds = reinterpret_cast<unsigned short*>(base + nd);  // [SORT_WAVES][nd]
+  __shared__ int wsum[SORT_WAVES];
+  auto wcnt = [&](int ww, int d) -> unsigned short& { return wcnt_lds[ww * nd + d]; };
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, blk = blockIdx.x;
+  const int p0 = blk * SORT_CHUNK + w * SORT_PER_WAVE;
   int key[SORT_ITERS], val[SORT_ITERS], rank[SORT_ITERS];
 #pragma unroll
   for (int it = 0; it < SORT_ITERS; ++it) {
     const int p = p0 + it * 64 + lane;
-    const bool valid = p < n;
-    const int k = valid ? keys_in[p] : 0;
-    key[it] = k;
-    val[it] = valid ? (vals_in ? vals_in[p] : p) : 0;
-    const int d = (k >> shift) & (nd - 1);
+    key[it] = p < n ? j.keys_in[p] : 0;
+    val[it] = p < n ? (j.vals_in ? j.vals_in[p] : p) : 0;
+  }
+  for (int d = lane; d < nd; d += 64) wcnt(w, d) = 0;
+  if (offs) {
+    for (int d = t; d < nd; d += SORT_THREADS) base[d] = offs[(size_t)blk * nd + d];
+  } else {
+    int carry = 0;
+    for (int d0 = 0; d0 < nd; d0 += SORT_THREADS) {
+      const int d = d0 + t;
+      int tot = 0, bef = 0;
+      constexpr int BATCH = 16;  // chunk counts in flight
+      for (int b0 = 0; b0 < nblk; b0 += BATCH) {
+        int c[BATCH];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) c[k] = d < nd ? hist[(size_t)min(b0 + k, nblk - 1) * nd + d] : 0;
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+          tot += b0 + k < nblk ? c[k] : 0;
+          bef += b0 + k < blk ? c[k] : 0;
+        }
+      }
+      // exclusive scan of the totals over the workgroup's digits
+      int inc = tot;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o);
+        if (lane >= o) inc += y;
+      }
+      if (lane == 63) wsum[w] = inc;
+      __syncthreads();
+      int before = carry;
+#pragma unroll
+      for (int k = 0; k < SORT_WAVES; ++k) {
+        before += k < w ? wsum[k] : 0;
+        carry += wsum[k];
+      }
+      if (d < nd) base[d] = before + inc - tot + bef;
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int it = 0; it < SORT_ITERS; ++it) {
+    const bool valid = p0 + it * 64 + lane < n;
+    const int d = (key[it] >> j.shift) & mask;
     uint64_t peers = __ballot(valid);
-    for (int b = 0; b < nbits; ++b) {
+    for (int b = 0; b < j.nbits; ++b) {
       const bool bit = (d >> b) & 1;
       const uint64_t bal = __ballot(bit);
       peers &= bit ? bal : ~bal;
@@ -148,61 +194,76 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
     const int before = __popcll(peers & below);
     const int c = wcnt(w, d);  // every peer reads the count before the leader updates it
     rank[it] = c + before;
-    if (valid && before == 0) wcnt(w, d) = c + __popcll(peers);
+    if (valid && before == 0) wcnt(w, d) = (unsigned short)(c + __popcll(peers));
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < nd; d += SORT_THREADS) {
+  for (int d = t; d < nd; d += SORT_THREADS) {
     int run = 0;
 #pragma unroll
     for (int ww = 0; ww < SORT_WAVES; ++ww) {
       const int c = wcnt(ww, d);
-      wcnt(ww, d) = run;
+      wcnt(ww, d) = (unsigned short)run;
       run += c;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < SORT_ITERS; ++it) {
-    const int p = p0 + it * 64 + lane;
-    if (p < n) {
-      const int d = (key[it] >> shift) & (nd - 1);
-      const int pos = offs[blockIdx.x * nd + d] + wcnt(w, d) + rank[it];
-      keys_out[pos] = key[it];
-      vals_out[pos] = val[it];
+    if (p0 + it * 64 + lane < n) {
+      const int d = (key[it] >> j.shift) & mask;
+      const int pos = base[d] + wcnt(w, d) + rank[it];
+      j.keys_out[pos] = key[it];
+      j.vals_out[pos] = val[it];
     }
   }
 }
 
-hipError_t launch_sort(const int32_t* keys_in, int n, int key_bits, int32_t* keys_a,
-                       int32_t* vals_a, int32_t* keys_b, int32_t* vals_b, int32_t* hist,
-                       const int32_t** keys_out, const int32_t** vals_out, hipStream_t st) {
-  *keys_out = keys_a;
-  *vals_out = vals_a;
-  if (n <= 0) return hipSuccess;
+int sort_spread(SortJob* job, int nthreads, int wgs) {
+  const int keys = nthreads * (wgs > 1 ? wgs : 1);
+  job->per_thread = (job->n + keys - 1) / keys;
+  if (job->per_thread > 127) job->per_thread = 127;  // what the 16-bit counters hold
+  const int chunk = nthreads * job->per_thread;
+  return (job->n + chunk - 1) / chunk;
+}
+
+int sort_pass_lds(int nbits, int nthreads) {
+  const int nd = 1 << nbits, w = nthreads / 64;
+  return nd * 4 + w * nd * 2 + w * 4;
+}
+
+SortPlan sort_plan(const int32_t* keys_in, int n, int key_bits, int32_t* keys_a, int32_t* vals_a, int32_t* keys_b,
+                   int32_t* vals_b) {
+  SortPlan p{};
+  p.keys_out = keys_a;
+  p.vals_out = vals_a;
+  if (n <= 0) return p;
   if (key_bits < 1) key_bits = 1;
-  const int npass = (key_bits + SORT_MAX_BITS - 1) / SORT_MAX_BITS;
-  const int bits = (key_bits + npass - 1) / npass;
-  const int nblk = sort_blocks(n);
-  int32_t* offs = hist + ((size_t)nblk << SORT_MAX_BITS);
-  const int32_t* kin = keys_in;
-  const int32_t* vin = nullptr;
-  int32_t* kout = keys_a;
-  int32_t* vout = vals_a;
-  for (int pass = 0; pass < npass; ++pass) {
-    const int shift = pass * bits;
-    const int nb = key_bits - shift < bits ? key_bits - shift : bits;
-    hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(SORT_THREADS), (size_t)4 << nb, st, kin, n,
-                       shift, nb, nblk, hist);
-    hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(SCAN_THREADS), 0, st, hist, nblk, 1 << nb, offs);
-    hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(SORT_THREADS),
-                       (size_t)SORT_WAVES * 4 << nb, st, kin, vin, n, shift, nb, nblk, offs, kout,
-                       vout);
-    *keys_out = kout;
-    *vals_out = vout;
-    kin = kout;
-    vin = vout;
-    kout = (kout == keys_a) ? keys_b : keys_a;
-    vout = (vout == vals_a) ? vals_b : vals_a;
+  p.passes = key_bits > SORT_MAX_BITS ? 2 : 1;  // (key_bits <= 2 * SORT_MAX_BITS)
+  const int bits = (key_bits + p.passes - 1) / p.passes;
+  p.pass[0] = SortJob{keys_in, nullptr, n, 0, bits, keys_a, vals_a, 1};
+  if (p.passes == 2) {
+    p.pass[1] = SortJob{keys_a, vals_a, n, bits, key_bits - bits, keys_b, vals_b, 1};
+    p.keys_out = keys_b;
+    p.vals_out = vals_b;
+  }
+  return p;
+}
+
+hipError_t launch_sort(const SortPlan& plan, int32_t* hist, hipStream_t st) {
+  for (int k = 0; k < plan.passes; ++k) {
+    const SortJob& j = plan.pass[k];
+    const int nblk = sort_blocks(j.n);
+    const int32_t* offs = nullptr;
+    hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(SORT_THREADS), (size_t)4 << j.nbits, st, j.keys_in, j.n, j.shift,
+                       j.nbits, nblk, hist);
+    if (nblk > SORT_SELF_SCAN) {
+      int32_t* o = hist + ((size_t)nblk << SORT_MAX_BITS);
+      hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(SCAN_THREADS), 0, st, hist, nblk, 1 << j.nbits, o);
+      offs = o;
+    }
+    // (nd offsets of 4 bytes and SORT_WAVES x nd counters of 2)
+    hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(SORT_THREADS), (size_t)(4 + 2 * SORT_WAVES) << j.nbits, st, j,
+                       nblk, (const int32_t*)hist, offs);
   }
   return hipGetLastError();
 }
