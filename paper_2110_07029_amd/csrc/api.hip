@@ -443,13 +443,11 @@ asgd_status run_sort(asgd_model* m, hipStream_t st, const SortPlan& plan) {
 asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int rows_pad,
                         const LabelJob* labels, hipStream_t da_stream, const SortPlan* sort = nullptr) {
   const int B = x->n_rows;
-  const int splits = fwd_splits(m, B);
-  const int n_tiles = (m->L + OUT_TILE - 1) / OUT_TILE;
-  const int tps = (n_tiles + splits - 1) / splits;
-  const int s_eff = (n_tiles + tps - 1) / tps;
+  const FwdPlan fp = fwd_plan(m->bf16, m->L, B, std::max(1, m->n_cu - kAuxCus));
+  const int s_eff = fp.splits;
   if ((int64_t)s_eff * rows_pad > m->part_rows) return fail(ASGD_ERANGE, "partial buffer too small");
   TIMED_LAUNCH(m, ASGD_K_OUT_FWD,
-               launch_out_fwd_train(m->bf16, m->W2(), m->b2(), m->L, m->H1, B, splits, m->m_part, m->s_part,
+               launch_out_fwd_train(m->bf16, m->W2(), m->b2(), m->L, m->H1, B, fp, m->m_part, m->s_part,
                                     m->o_part, rows_pad, labels, &m->label_plan, sort && sort->passes > 0 ? &sort->pass[0] : nullptr,
                                     m->n_cu, m->stream, t0_, t1_));
   CsrDev yd = y ? dev(y) : CsrDev{};

@@ -99,8 +99,14 @@ int out_rows_per_block(bool use_bf16);
 // and sum_l exp(Z - m) W2[l] (flash-style); one workgroup per (split, row
 // block), plus, with job != NULL, one that groups the labels (plan from
 // label_job_plan).
+// Its launch shape: nrb row blocks x `splits` label splits of tps tiles each; is_short: 32
+// rows per row block and waves on tiles of their own (k_out_fwd_short).  wgs: workgroups wanted.
+struct FwdPlan {
+  int is_short, nrb, splits, tps;
+};
+FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs);
 hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
-                                int B, int splits, float* m_part, float* s_part, float* o_part,
+                                int B, const FwdPlan& shape, float* m_part, float* s_part, float* o_part,
                                 int ld_part, const LabelJob* job, const LabelJobPlan* plan, const SortJob* sort,
                                 int n_cu, hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 // (sort: a pass of the feature sort to run in the same launch, with a label job only;

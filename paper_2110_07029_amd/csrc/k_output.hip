@@ -26,6 +26,16 @@
 
 namespace asgd {
 
+// Number of workgroup b of n in XCD-major order.  Workgroups are dealt to the 8
+// XCDs in turn (b to XCD b mod 8), each with its own L2; numbered this way, those
+// of one XCD are consecutive, so neighbours (the row blocks of a split, which read
+// the same W2 tiles; rows that share the cache lines of the per-split arrays) are
+// served by one L2 instead of each fetching from memory.
+__device__ __forceinline__ int xcd_order(int b, int n) {
+  const int x = b & 7;
+  return x * (n >> 3) + min(x, n & 7) + (b >> 3);
+}
+
 int out_rows_per_block(bool use_bf16) { return use_bf16 ? FwdShape<true>::RB : FwdShape<false>::RB; }
 
 // ---------------------------------------------------------------------------
@@ -86,7 +96,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_train(
   // XCD-major order v: they share an XCD, and its L2 serves the tiles once.
   const int nrb = n_fwd / s_eff;
   const int b = (int)blockIdx.x;
-  const int v = n_fwd % 8 == 0 ? (b % 8) * (n_fwd / 8) + b / 8 : b;
+  const int v = xcd_order(b, n_fwd);
   const int split = v / nrb;
   const int t_begin = split * tiles_per_split;
   const int t_end = min(n_tiles, t_begin + tiles_per_split);
@@ -278,6 +288,250 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_train(
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same for short splits (k_out_fwd_short).  Workgroup = (label split, 32 rows), its 8 waves on
+// tiles of their own (t = wave, wave + 8, ... of the split): no tile is shared, so
+// nothing in the loop waits for another wave, and the waves' partials merge in LDS,
+// so a split is 8 waves' tiles long and there are few of them.  The partials are
+// what a short label space pays for above: every split writes, and the per-row pass
+// reads back, 512 bytes per row, 32 MB at 240 splits and 256 rows, where W2 of
+// 30,000 labels is 15 MB.  Batches of few rows also have no padding rows here (above,
+// a workgroup computes 256 rows).  The price is that every 32 rows read all of W2
+// (from the L2 that a split's row blocks share) and convert it: fwd_is_short says up
+// to where it is worth that.  30,000 labels, 256 rows: the kernel 17 -> 14 us and the
+// per-row pass after it 16 -> 9.
+// ---------------------------------------------------------------------------
+template <bool BF16>
+struct ShortTile {
+  static constexpr int ELEMS = tile_elems<BF16>();
+  static constexpr int BYTES = ELEMS * (int)sizeof(typename Mma<BF16>::elem);
+};
+constexpr int SHORT_LD = HID + 4;  // row stride of a wave's merged O (floats)
+// LDS: the waves' tiles during the loop, their O afterwards; biases, maxima and sums
+template <bool BF16>
+constexpr int short_lds() {
+  constexpr int tiles = 8 * ShortTile<BF16>::BYTES, merged = 8 * 32 * SHORT_LD * 4;
+  return (tiles > merged ? tiles : merged) + 3 * 8 * 32 * 4;
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_short(
+    const float* __restrict__ W2, const float* __restrict__ b2, int L,
+    const typename Mma<BF16>::elem* __restrict__ H1, int B, int tiles_per_split, int n_tiles,
+    float* __restrict__ m_part, float* __restrict__ s_part, float* __restrict__ o_part,
+    int ld_part, int s_eff, int n_fwd, LabelJob lj, SortJob sj) {
+  using M = Mma<BF16>;
+  using E = typename M::elem;
+  using Fr = typename M::frag;
+  constexpr int NCH = 32 / M::KC;
+  constexpr int WAVES = FwdShape<BF16>::WAVES;
+  extern __shared__ __attribute__((aligned(16))) char short_smem[];
+  if ((int)blockIdx.x >= n_fwd) {
+    int32_t* job_lds = reinterpret_cast<int32_t*>(short_smem);
+    if ((int)blockIdx.x > n_fwd)
+      wg_sort_pass<FWD_THREADS>(sj, (int)blockIdx.x - n_fwd - 1, job_lds);
+    else if (lj.in_lds)
+      wg_label_blocks<FWD_THREADS, true>(lj.lkeys, lj.m, L, lj.lrow, lj.lbeg, lj.lpair, job_lds,
+                                         job_lds + ((L + 31) >> 5));
+    else
+      wg_label_blocks<FWD_THREADS, false>(lj.lkeys, lj.m, L, lj.lrow, lj.lbeg, lj.lpair, lj.lcnt, job_lds);
+    return;
+  }
+  const int lane = threadIdx.x & 63, g = lane >> 5, n = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int AREA = short_lds<BF16>() - 3 * WAVES * 32 * 4;
+  E* const tile = reinterpret_cast<E*>(short_smem) + wave * ShortTile<BF16>::ELEMS;
+  float* const bt = reinterpret_cast<float*>(short_smem + AREA) + wave * 32;
+  float* const red_m = reinterpret_cast<float*>(short_smem + AREA) + WAVES * 32;      // [WAVES][32]
+  float* const red_s = reinterpret_cast<float*>(short_smem + AREA) + 2 * WAVES * 32;  // [WAVES][32]
+  // the row blocks of a split on one XCD, as in k_out_fwd_train
+  const int nrb = n_fwd / s_eff, wg = (int)blockIdx.x;
+  const int v = xcd_order(wg, n_fwd);
+  const int split = v / nrb;
+  const int t_begin = split * tiles_per_split;
+  const int t_end = min(n_tiles, t_begin + tiles_per_split);
+  const int row0 = (v % nrb) * 32;
+  const int rbase[2] = {tw_row_base(n, g, 0), tw_row_base(n, g, 1)};
+  const int cbase[2] = {tw_col_base(lane, 0), tw_col_base(lane, 1)};
+
+  // a tile's 32 rows as whole 512-byte rows, two per load (past L: zeros)
+  const __amdgpu_buffer_rsrc_t w2r =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W2), (short)0, L * HID * 4, BUF_RSRC_WORD3);
+  const __amdgpu_buffer_rsrc_t b2r =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(b2), (short)0, L * 4, BUF_RSRC_WORD3);
+  const int r_lo = lane >> 5, col = 4 * (lane & 31);
+  const int voff = (r_lo * HID + col) * 4;
+  float4 nv[16];
+  float nb;
+  auto load = [&](int t) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      nv[k] = __builtin_bit_cast(
+          float4, __builtin_amdgcn_raw_buffer_load_b128(w2r, voff + k * 2 * HID * 4,
+                                                        (int)((unsigned)t * (unsigned)(OUT_TILE * HID * 4)), 0));
+    nb = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b2r, n * 4, t * OUT_TILE * 4, 0));
+  };
+  int t = t_begin + wave;
+  const bool any = t < t_end;  // (a short last split may leave waves without a tile)
+  if (any) load(t);
+  Fr hf[4][NCH];
+  const E* hrow = H1 + (size_t)(row0 + n) * HID;
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) hf[kb][c] = h1_frag<BF16>(hrow, kb, c, g);
+
+  float m_run = -INFINITY, s_run = 0.0f;
+  f32x16 acc_o[4];
+#pragma unroll
+  for (int hb = 0; hb < 4; ++hb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc_o[hb][r] = 0.0f;
+  constexpr float LAZY = 8.0f, LAZY_SUM = 256.0f;  // as in k_out_fwd_train
+#pragma unroll 1
+  for (; t < t_end; t += WAVES) {
+    // the loaded tile into the wave's LDS tile, and the next one requested
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int r = 2 * k + r_lo;
+      if constexpr (BF16) {
+        bf16x4 p;
+        p[0] = (bf16)nv[k].x; p[1] = (bf16)nv[k].y; p[2] = (bf16)nv[k].z; p[3] = (bf16)nv[k].w;
+        *reinterpret_cast<bf16x4*>(tile + tw_off(r, col)) = p;
+      } else {
+        *reinterpret_cast<float4*>(tile + r * FwdShape<false>::WR + col) = nv[k];
+      }
+    }
+    bt[n] = t * OUT_TILE + n < L ? nb : -INFINITY;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (t + WAVES < t_end) load(t + WAVES);
+    // Z^T = W2_tile H1^T from the biases
+    f32x16 z;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 b = *reinterpret_cast<const float4*>(bt + 8 * q + 4 * g);
+      z[4 * q + 0] = b.x; z[4 * q + 1] = b.y; z[4 * q + 2] = b.z; z[4 * q + 3] = b.w;
+    }
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) z = M::mma(tile_frag_w<BF16>(tile, rbase, n, kb, c, g), hf[kb][c], z);
+    float p[16], ps = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      p[r] = __builtin_amdgcn_exp2f(fmaf(z[r], LOG2E, -m_run));
+      ps += p[r];
+    }
+    if (__any(!(ps <= LAZY_SUM))) {
+      float tmax = z[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, z[r]);
+      tmax = half_swap_max(tmax);
+      const float m2c = tmax * LOG2E;
+      const float m2n = m2c > m_run + LAZY ? m2c : m_run;
+      const float scale = __builtin_amdgcn_exp2f(m_run - m2n);
+      s_run *= scale;
+#pragma unroll
+      for (int hb = 0; hb < 4; ++hb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc_o[hb][r] *= scale;
+      m_run = m2n;
+      ps = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        p[r] = __builtin_amdgcn_exp2f(fmaf(z[r], LOG2E, -m_run));
+        ps += p[r];
+      }
+    }
+    s_run += ps;
+    // O^T += W2_t^T P^T.  fp32: the W2^T operand (lane = hidden unit) is read straight
+    // from the row-major tile, 32 consecutive floats per half wavefront.
+    Fr pf[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) pf[c] = frag_acc<BF16>(p, c);
+#pragma unroll
+    for (int hb = 0; hb < 4; ++hb)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        if constexpr (BF16)
+          acc_o[hb] = M::mma(tile_frag_wt<BF16>(tile, nullptr, cbase, hb, c, lane), pf[c], acc_o[hb]);
+        else
+          acc_o[hb] = M::mma(tile[kofs<false>(c, g, 0) * FwdShape<false>::WR + 32 * hb + n], pf[c], acc_o[hb]);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
+
+  // Merge: every wave rescales to the rows' common maximum (a wave without a tile
+  // holds m = -inf and contributes zeros), then the sums are added in wave order.
+  const float stot = s_run + __shfl_xor(s_run, 32);
+  if (g == 0) red_m[wave * 32 + n] = m_run;
+  __syncthreads();  // (and every wave is done with its tile)
+  float mx = red_m[n];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) mx = fmaxf(mx, red_m[w * 32 + n]);
+  const float sc = any ? __builtin_amdgcn_exp2f(m_run - mx) : 0.0f;
+  if (g == 0) red_s[wave * 32 + n] = any ? stot * sc : 0.0f;
+  float* const om = reinterpret_cast<float*>(short_smem) + (wave * 32 + n) * SHORT_LD;
+#pragma unroll
+  for (int hb = 0; hb < 4; ++hb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4*>(om + 32 * hb + 8 * q + 4 * g) =
+          make_float4(acc_o[hb][4 * q] * sc, acc_o[hb][4 * q + 1] * sc, acc_o[hb][4 * q + 2] * sc,
+                      acc_o[hb][4 * q + 3] * sc);
+  __syncthreads();
+  // thread: 8 hidden units of row threadIdx.x / 16
+  const int orow = threadIdx.x >> 4, h8 = (threadIdx.x & 15) * 8;
+  const int row = row0 + orow;
+  if (row >= B) return;
+  const float* src = reinterpret_cast<const float*>(short_smem) + orow * SHORT_LD + h8;
+  float4 o0 = *reinterpret_cast<const float4*>(src), o1 = *reinterpret_cast<const float4*>(src + 4);
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) {
+    const float4 a = *reinterpret_cast<const float4*>(src + w * 32 * SHORT_LD);
+    const float4 b = *reinterpret_cast<const float4*>(src + w * 32 * SHORT_LD + 4);
+    o0.x += a.x; o0.y += a.y; o0.z += a.z; o0.w += a.w;
+    o1.x += b.x; o1.y += b.y; o1.z += b.z; o1.w += b.w;
+  }
+  const size_t at = (size_t)split * ld_part + row;
+  *reinterpret_cast<float4*>(o_part + at * HID + h8) = o0;
+  *reinterpret_cast<float4*>(o_part + at * HID + h8 + 4) = o1;
+  if (h8 == 0) {
+    float M2 = red_m[orow], S = red_s[orow];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+      M2 = fmaxf(M2, red_m[w * 32 + orow]);
+      S += red_s[w * 32 + orow];
+    }
+    m_part[at] = M2 * LN2;
+    s_part[at] = S;
+  }
+}
+
+// Where the forward runs k_out_fwd_short.  Measured, us per step with it | without:
+//   L = 1,000, B = 128 (fp32): 53 | 60    L = 30,000, B = 256: 64 | 73    L = 120,000, B = 256: 100 | 106
+//   L = 670,091, B = 32: 247 | 253        L = 670,091, B = 64: 236 | 254  L = 670,091, B = 128: 253 | 251
+//   L = 205,443, B = 256: 132 | 133       L = 30,000, B = 600: 111 | 112  L = 60,000, B = 600: 126 | 122
+static bool fwd_is_short(int n_tiles, int B) {
+  return B <= 64 || n_tiles * ((B + 31) / 32) <= 32768;  // (tile, 32-row block) products
+}
+
+// Splits of the forward and whether it runs k_out_fwd_short.
+FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs) {
+  const int n_tiles = (L + OUT_TILE - 1) / OUT_TILE;
+  FwdPlan p;
+  p.is_short = fwd_is_short(n_tiles, B);
+  const int rb = p.is_short ? 32 : out_rows_per_block(use_bf16);
+  p.nrb = (B + rb - 1) / rb;
+  int s = p.is_short ? wgs / p.nrb : (wgs + p.nrb - 1) / p.nrb;
+  const int most = p.is_short ? (n_tiles + FwdShape<true>::WAVES - 1) / FwdShape<true>::WAVES : n_tiles;
+  if (s > most) s = most;
+  if (s < 1) s = 1;
+  p.tps = (n_tiles + s - 1) / s;
+  p.splits = (n_tiles + p.tps - 1) / p.tps;
+  return p;
+}
+
 LabelJobPlan label_job_plan_for(const void* fn, int nthreads, int L) {
   LabelJobPlan p{};
   hipFuncAttributes fa{};
@@ -297,19 +551,18 @@ LabelJobPlan label_job_plan_for(const void* fn, int nthreads, int L) {
 }
 
 LabelJobPlan label_job_plan(bool use_bf16, int L) {
+  const void* fn = use_bf16 ? (const void*)k_out_fwd_short<true> : (const void*)k_out_fwd_short<false>;
+  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return {};
   return label_job_plan_for(use_bf16 ? (const void*)k_out_fwd_train<true> : (const void*)k_out_fwd_train<false>,
                             FWD_THREADS, L);
 }
 
 hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
-                                int B, int splits, float* m_part, float* s_part, float* o_part,
+                                int B, const FwdPlan& fp, float* m_part, float* s_part, float* o_part,
                                 int ld_part, const LabelJob* job, const LabelJobPlan* plan, const SortJob* sort,
                                 int n_cu, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   const int n_tiles = (L + OUT_TILE - 1) / OUT_TILE;
-  const int tps = (n_tiles + splits - 1) / splits;
-  const int s_eff = (n_tiles + tps - 1) / tps;
-  const int RB = out_rows_per_block(use_bf16);
-  const int n_fwd = s_eff * ((B + RB - 1) / RB);
+  const int n_fwd = fp.splits * fp.nrb;
   LabelJob lj{};
   int lds = 0, n_job = 0;
   if (job) {
@@ -331,13 +584,17 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
     n_job += sort_spread(&sj, FWD_THREADS, n_cu - n_fwd % n_cu - 1);
   }
   const dim3 grid(n_fwd + n_job), block(FWD_THREADS);
-  if (use_bf16)
-    hipExtLaunchKernelGGL(k_out_fwd_train<true>, grid, block, lds, st, t0, t1, 0, W2, b2, L, (const bf16*)H1, B,
-                          tps, n_tiles, m_part, s_part, o_part, ld_part, s_eff, n_fwd, lj, sj);
-  else
-    hipExtLaunchKernelGGL(k_out_fwd_train<false>, grid, block, lds, st, t0, t1, 0, W2, b2, L, (const float*)H1,
-                          B, tps, n_tiles, m_part, s_part, o_part, ld_part, s_eff, n_fwd, lj, sj);
-  return hipGetLastError();
+  auto go = [&](auto kern, auto* h1) {
+    hipExtLaunchKernelGGL(kern, grid, block, lds, st, t0, t1, 0, W2, b2, L, h1, B, fp.tps, n_tiles, m_part, s_part,
+                          o_part, ld_part, fp.splits, n_fwd, lj, sj);
+    return hipGetLastError();
+  };
+  if (fp.is_short) {  // (all of its LDS is dynamic; label counters that fit the other kernel's fit here too)
+    const int own = use_bf16 ? short_lds<true>() : short_lds<false>();
+    if (own > lds) lds = own;
+    return use_bf16 ? go(k_out_fwd_short<true>, (const bf16*)H1) : go(k_out_fwd_short<false>, (const float*)H1);
+  }
+  return use_bf16 ? go(k_out_fwd_train<true>, (const bf16*)H1) : go(k_out_fwd_train<false>, (const float*)H1);
 }
 
 // ---------------------------------------------------------------------------
@@ -406,12 +663,6 @@ __device__ __forceinline__ void merge_splits(int i, int splits, const float* __r
   }
 }
 
-// Row of workgroup b in a launch of one workgroup per row over n rows.
-// Workgroups are dealt to the 8 XCDs in turn; giving each XCD a contiguous
-// range of rows lets one L2 serve the cache lines that neighbouring rows share
-// in the per-split (max, sum) arrays, instead of every XCD fetching them all.
-__device__ __forceinline__ int xcd_row(int b, int n) { return n % 8 == 0 ? (b % 8) * (n / 8) + b / 8 : b; }
-
 // dA1 of row i from the forward's partials, by a workgroup of GROUPS x 32
 // threads (every thread calls it): each group merges its splits' O online
 // against its own running maximum, then the groups are rescaled to the row's
@@ -471,7 +722,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
       return;
     }
   }
-  const int i = xcd_row((int)blockIdx.x, B), t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int i = xcd_order((int)blockIdx.x, B), t = threadIdx.x, lane = t & 63, w = t >> 6;
   {
     float mg = -INFINITY, St = 0.0f;
     for (int k = t; k < splits; k += CMB_THREADS)
@@ -578,7 +829,7 @@ __global__ __launch_bounds__(32 * GROUPS) void k_out_dA1(int splits, const float
   __shared__ float red_o[GROUPS][HID];
   __shared__ float red_s[GROUPS];
   __shared__ float red_m[GROUPS];
-  const int i = xcd_row((int)blockIdx.x, (int)gridDim.x), t = threadIdx.x;
+  const int i = xcd_order((int)blockIdx.x, (int)gridDim.x), t = threadIdx.x;
   const float tw_t = t < HID ? tw[(size_t)i * HID + t] : 0.0f;
   da1_row<GROUPS>(i, splits, m_part, s_part, o_part, ld_part, tw_t, A1, invB, dA1, red_o, red_s, red_m);
 }
@@ -702,7 +953,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_topk(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // workgroup -> (split, row block): the row blocks of a split share an XCD (see k_out_fwd_train)
   const int n_wg = (int)gridDim.x, nrb = n_wg / s_eff, wg = (int)blockIdx.x;
-  const int v = n_wg % 8 == 0 ? (wg % 8) * (n_wg / 8) + wg / 8 : wg;
+  const int v = xcd_order(wg, n_wg);
   const int split = v / nrb;
   const int t_begin = split * tiles_per_split;
   const int t_end = min(n_tiles, t_begin + tiles_per_split);
