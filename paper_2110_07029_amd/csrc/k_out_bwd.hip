@@ -13,7 +13,7 @@
 // With bf16 operands H1 is staged in LDS, in the conflict-free tile layout of
 // the forward (row stride 160, 16-byte chunks permuted by the row): the logits
 // read H1 rows with 16-byte reads, the dW2 product reads H1^T with transposed
-// reads (ds_read_b64_tr_b16) from the same copy.  Three kernels, all with
+// reads (ds_read_b64_tr_b16) from the same copy.  Four kernels, the first three with
 // persistent workgroups:
 //   k_out_bwd_prefetch (B <= 256, bf16): 4 wavefronts, the whole batch staged
 //           once per workgroup; each wave walks its own label blocks with no
@@ -25,7 +25,9 @@
 //           next one is copied from global memory straight into the other
 //           buffer (global_load_lds, no registers in between);
 //   k_out_bwd, global (fp32 operands): H1 and H1^T read from their
-//           L2-resident global copies.
+//           L2-resident global copies;
+//   k_out_bwd_short (few label blocks): a workgroup per block, its waves on row
+//           blocks of their own.
 #include <hip/hip_ext.h>
 #include <math.h>
 
@@ -65,10 +67,7 @@ __device__ __forceinline__ void lds_copy16(const void* src, unsigned lds) {
                : "memory");
 }
 
-// RS > 1 (global mode only): the RS wavefronts of a label block split its row
-// blocks (rb = rp, rp + RS, ...) and their dW2 / db2 partials meet in LDS, for
-// label spaces too small to give every wavefront a block of its own.
-template <bool BF16, int MODE, int RS>
+template <bool BF16, int MODE>
 __global__ __launch_bounds__(BWD_THREADS) void k_out_bwd(
     float* __restrict__ W2, float* __restrict__ b2, int L,
     const typename Mma<BF16>::elem* __restrict__ H1, const typename Mma<BF16>::elem* __restrict__ H1T,
@@ -82,8 +81,6 @@ __global__ __launch_bounds__(BWD_THREADS) void k_out_bwd(
   constexpr bool LDS_H1 = MODE != BWD_GLOBAL;
   static_assert(!LDS_H1 || BF16, "LDS staging is for bf16 operands");
   static_assert(MODE != BWD_STAGED, "B <= 256 with bf16 operands runs k_out_bwd_prefetch");
-  static_assert(RS == 1 || (MODE == BWD_GLOBAL && BWD_WAVES % RS == 0), "row split: global mode");
-  constexpr int LPW = BWD_WAVES / RS;  // label blocks per workgroup at a time (row split)
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const int nrb = (B + 31) >> 5;
   const int bpad = nrb * 32;
@@ -106,9 +103,6 @@ __global__ __launch_bounds__(BWD_THREADS) void k_out_bwd(
   float* tw_s = reinterpret_cast<float*>(sp);
   sp += bpad * sizeof(float);
   uint32_t* mask = reinterpret_cast<uint32_t*>(sp) + wave * 32 * mstride;
-  sp += BWD_WAVES * 32 * mstride * sizeof(uint32_t);
-  // row split: the partial dW2 (64 values per lane) and db2 of wavefronts rp > 0
-  float* red = reinterpret_cast<float*>(sp);
 
   // Row constants of rows [r0, r0 + nrows) at LDS index (row - r0).
   auto stage_rows = [&](int r0, int nrows) {
@@ -170,20 +164,16 @@ __global__ __launch_bounds__(BWD_THREADS) void k_out_bwd(
   const int n_blocks = (L + 31) >> 5;
   // global: each wave walks its own blocks; chunked: the workgroup walks
   // groups of 8 blocks together (a uniform trip count for the barriers)
-  // (row split: groups of LPW blocks, walked by the workgroup together)
-  const int n_iter_units = MODE == BWD_CHUNKED ? (n_blocks + BWD_WAVES - 1) / BWD_WAVES
-                           : RS > 1            ? (n_blocks + LPW - 1) / LPW
-                                               : n_blocks;
-  const int first = MODE == BWD_CHUNKED || RS > 1 ? blockIdx.x : blockIdx.x * BWD_WAVES + wave;
-  const int step = MODE == BWD_CHUNKED || RS > 1 ? gridDim.x : gridDim.x * BWD_WAVES;
-  const int rp = RS > 1 ? wave % RS : 0;  // this wavefront's share of the row blocks
+  const int n_iter_units = MODE == BWD_CHUNKED ? (n_blocks + BWD_WAVES - 1) / BWD_WAVES : n_blocks;
+  const int first = MODE == BWD_CHUNKED ? blockIdx.x : blockIdx.x * BWD_WAVES + wave;
+  const int step = MODE == BWD_CHUNKED ? gridDim.x : gridDim.x * BWD_WAVES;
   // chunked: chunks are consumed in the order (unit, chunk); kc counts them,
   // and chunk kc lives in buffer kc & 1.  The first one is requested here.
   const int nch = (bpad + BWD_CROWS - 1) / BWD_CROWS;
   int kc = 0;
   if (MODE == BWD_CHUNKED && first < n_iter_units) issue_chunk(0, h1b);
   for (int unit = first; unit < n_iter_units; unit += step) {
-    const int blk = MODE == BWD_CHUNKED ? unit * BWD_WAVES + wave : RS > 1 ? unit * LPW + wave / RS : unit;
+    const int blk = MODE == BWD_CHUNKED ? unit * BWD_WAVES + wave : unit;
     const bool bactive = blk < n_blocks;
     const int l0 = blk * 32;
     const int label = l0 + n;
@@ -328,35 +318,10 @@ __global__ __launch_bounds__(BWD_THREADS) void k_out_bwd(
     } else {
       if (has_targets) build_mask(lo, hi, pr0, 0, bpad);
       if (bactive)
-        for (int rb = rp; rb < nrb; rb += RS) row_block(nullptr, rb, rb * 32);
+        for (int rb = 0; rb < nrb; ++rb) row_block(nullptr, rb, rb * 32);
     }
-    if constexpr (RS > 1) {
-      // partials of wavefronts rp > 0 to LDS (value-major, lane-contiguous),
-      // added by wavefront rp = 0 in rp order
-      float* my = red + (size_t)((wave / RS) * (RS - 1) + rp - 1) * 65 * 64;
-      if (rp > 0) {
-#pragma unroll
-        for (int hb = 0; hb < 4; ++hb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) my[(16 * hb + r) * 64 + lane] = accw[hb][r];
-        my[64 * 64 + lane] = db2p;
-      }
-      __syncthreads();
-      if (rp == 0) {
-        for (int k = 1; k < RS; ++k) {
-          const float* o = red + (size_t)((wave / RS) * (RS - 1) + k - 1) * 65 * 64;
-#pragma unroll
-          for (int hb = 0; hb < 4; ++hb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) accw[hb][r] += o[(16 * hb + r) * 64 + lane];
-          db2p += o[64 * 64 + lane];
-        }
-      }
-      __syncthreads();  // the slots are free again for the next group
-    }
-
     const float db2 = db2p + __shfl_xor(db2p, 32);
-    if (bactive && lvalid && rp == 0) {
+    if (bactive && lvalid) {
       float* wout = W2 + (size_t)label * HID;
 #pragma unroll
       for (int hb = 0; hb < 4; ++hb)
@@ -696,7 +661,247 @@ __global__ __launch_bounds__(BWP_THREADS) void k_out_bwd_prefetch(
   }
 }
 
-template <bool BF16, int MODE, int RS>
+// ---------------------------------------------------------------------------
+// Few label blocks for the rows.  Workgroup = one block of 32 labels, its 4 waves on
+// row blocks of their own (rb = wave, wave + 4, ...), each staged in a wave-private LDS
+// tile, so that a small label space fills the GPU by rows as well (the chunked kernel
+// gives a workgroup 256 labels: 10,000 labels kept 40 CUs busy).  The waves' dW2
+// partials meet in LDS, each wave adding and updating a quarter of the hidden units in
+// wave order, and the rows leave whole.  The price is that every label block reads all
+// of H1 (from L2) and nothing of the next block is in flight: bwd_is_short says up to
+// where it is worth that.
+// ---------------------------------------------------------------------------
+constexpr int BWS_WAVES = 4;
+constexpr int BWS_THREADS = 64 * BWS_WAVES;
+constexpr int BWS_SLD = HID + 4;  // row stride of the W2 stage (floats)
+template <bool BF16>
+constexpr int bws_tile_bytes() {
+  return BF16 ? 32 * TW_LD * 2 : 32 * BWS_SLD * 4;
+}
+// LDS: W2 stage | the waves' H1 tiles, later the partials (4 x 3 x 16 x 64 floats) |
+// per wave row constants, target weights and db2 | target bits
+template <bool BF16>
+constexpr int bws_area() {
+  constexpr int tiles = BWS_WAVES * bws_tile_bytes<BF16>(), parts = BWS_WAVES * (BWS_WAVES - 1) * 16 * 64 * 4;
+  return tiles > parts ? tiles : parts;
+}
+template <bool BF16>
+constexpr int bws_fixed_lds() {
+  return 32 * BWS_SLD * 4 + bws_area<BF16>() + 3 * BWS_WAVES * 32 * 4;
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(BWS_THREADS, BF16 ? 2 : 1) void k_out_bwd_short(
+    float* __restrict__ W2, float* __restrict__ b2, int L, const typename Mma<BF16>::elem* __restrict__ H1, int B,
+    const float* __restrict__ lse, const float* __restrict__ rw, const int32_t* __restrict__ lbeg,
+    const int32_t* __restrict__ lpair, float lr, float invB, float log2_invB) {
+  using M = Mma<BF16>;
+  using E = typename M::elem;
+  using Fr = typename M::frag;
+  constexpr int NCH = 32 / M::KC;
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, n = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nrb = (B + 31) >> 5;
+  const int blk = blockIdx.x, l0 = blk * 32;
+  float* const stage = reinterpret_cast<float*>(smem_raw);
+  char* const area = smem_raw + 32 * BWS_SLD * 4;
+  E* const tile = reinterpret_cast<E*>(area + wave * bws_tile_bytes<BF16>());
+  float* const crow_s = reinterpret_cast<float*>(area + bws_area<BF16>()) + wave * 32;
+  float* const tw_s = crow_s + BWS_WAVES * 32;
+  float* const db_s = reinterpret_cast<float*>(area + bws_area<BF16>()) + 2 * BWS_WAVES * 32;  // [wave][32]
+  uint32_t* const mask = reinterpret_cast<uint32_t*>(area + bws_area<BF16>()) + 3 * BWS_WAVES * 32;  // [32][nrb]
+
+  // everything the first products need is requested before anything waits
+  const __amdgpu_buffer_rsrc_t w2r = __builtin_amdgcn_make_buffer_rsrc(W2, (short)0, L * HID * 4, BUF_RSRC_WORD3);
+  const int wrow = tid >> 5, wcol = 4 * (tid & 31);  // rows wrow + 8k of the block
+  const int voff = (int)((unsigned)(l0 + wrow) * (unsigned)(HID * 4)) + wcol * 4;
+  float4 wv[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    wv[k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w2r, voff + k * 8 * HID * 4, 0, 0));
+  const int label = l0 + n;
+  const bool lvalid = label < L;
+  const float bias = b2[min(label, L - 1)];
+  const int lo = lbeg[blk], hi = lbeg[blk + 1];
+  // row block rb of H1 (rows past B are zero up to the padding), its lse and row weights
+  constexpr int NLD = BF16 ? 8 : 16;
+  u32x4 hv[NLD];
+  float lse_v = 0.0f, rw_v = 0.0f;
+  auto load = [&](int rb) {
+    const u32x4* src = reinterpret_cast<const u32x4*>(H1 + (size_t)rb * 32 * HID);
+#pragma unroll
+    for (int k = 0; k < NLD; ++k) hv[k] = src[k * 64 + lane];
+    const int r = rb * 32 + n;
+    lse_v = r < B ? lse[r] : 0.0f;
+    rw_v = r < B ? rw[r] : 0.0f;
+  };
+  int rb = wave;
+  if (rb < nrb) load(rb);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) *reinterpret_cast<float4*>(stage + (wrow + 8 * k) * BWS_SLD + wcol) = wv[k];
+  const bool has_targets = hi > lo;
+  if (has_targets)
+    for (int k = tid; k < 32 * nrb; k += BWS_THREADS) mask[k] = 0u;
+  __syncthreads();
+  if (has_targets) {
+    for (int q = lo + tid; q < hi; q += BWS_THREADS) {
+      const int pr = lpair[q], row = pr >> 5;
+      atomicOr(&mask[(pr & 31) * nrb + (row >> 5)], 1u << (row & 31));
+    }
+    __syncthreads();
+  }
+  // the logits' W2 operand: label n, hidden units in the order of the H1 row reads
+  Fr wf[4][NCH];
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      if constexpr (BF16) {
+        const float* src = stage + n * BWS_SLD + 32 * kb + 16 * c + 8 * g;
+        const float4 a4 = *reinterpret_cast<const float4*>(src);
+        const float4 b4 = *reinterpret_cast<const float4*>(src + 4);
+        Fr f;
+        f[0] = (bf16)a4.x; f[1] = (bf16)a4.y; f[2] = (bf16)a4.z; f[3] = (bf16)a4.w;
+        f[4] = (bf16)b4.x; f[5] = (bf16)b4.y; f[6] = (bf16)b4.z; f[7] = (bf16)b4.w;
+        wf[kb][c] = f;
+      } else {
+        wf[kb][c] = frag_row<false>(stage + n * BWS_SLD + 32 * kb, c, g);
+      }
+    }
+  const float bb = lvalid ? bias * LOG2E : -INFINITY;
+  const int rbase[2] = {tw_row_base(n, g, 0), tw_row_base(n, g, 1)};
+  const int cbase[2] = {tw_col_base(lane, 0), tw_col_base(lane, 1)};
+  f32x16 accw[4];
+#pragma unroll
+  for (int hb = 0; hb < 4; ++hb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) accw[hb][r] = 0.0f;
+  float db2p = 0.0f;
+
+#pragma unroll 1
+  for (; rb < nrb; rb += BWS_WAVES) {
+#pragma unroll
+    for (int k = 0; k < NLD; ++k) {
+      if constexpr (BF16) {
+        const int r = 4 * k + (lane >> 4), c = lane & 15;
+        *reinterpret_cast<u32x4*>(tile + r * TW_LD + 8 * (c ^ ((r >> 2) & 3))) = hv[k];
+      } else {
+        *reinterpret_cast<u32x4*>(tile + (2 * k + g) * BWS_SLD + 4 * n) = hv[k];
+      }
+    }
+    // (the accumulator's start, as in the other kernels; -inf past B)
+    crow_s[n] = rb * 32 + n < B ? (log2_invB - lse_v * LOG2E) * LN2 : -INFINITY;
+    tw_s[n] = rw_v * invB;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (rb + BWS_WAVES < nrb) load(rb + BWS_WAVES);
+    f32x16 z;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 c4 = *reinterpret_cast<const float4*>(crow_s + 8 * q + 4 * g);
+      z[4 * q + 0] = c4.x; z[4 * q + 1] = c4.y; z[4 * q + 2] = c4.z; z[4 * q + 3] = c4.w;
+    }
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        if constexpr (BF16)
+          z = M::mma(*reinterpret_cast<const bf16x8*>(tile + rbase[c] + 32 * kb), wf[kb][c], z);
+        else
+          z = M::mma(frag_row<false>(tile + n * BWS_SLD + 32 * kb, c, g), wf[kb][c], z);
+      }
+    float dz[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dz[r] = __builtin_amdgcn_exp2f(fmaf(z[r], LOG2E, bb));
+    if (has_targets) {
+      const uint32_t mw = mask[n * nrb + rb];
+      if (__any(mw != 0u)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int rl = 8 * (r >> 2) + 4 * g + (r & 3);
+          dz[r] -= ((mw >> rl) & 1u) ? tw_s[rl] : 0.0f;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) db2p += dz[r];
+    Fr df[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) df[c] = frag_acc<BF16>(dz, c);
+#pragma unroll
+    for (int hb = 0; hb < 4; ++hb)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        if constexpr (BF16) {
+          const bf16* o = tile + 16 * c * TW_LD + 32 * hb;
+          const bf16x4 lo4 = lds_read_tr16(o + cbase[0]), hi4 = lds_read_tr16(o + cbase[1]);
+          bf16x8 af;
+          af[0] = lo4[0]; af[1] = lo4[1]; af[2] = lo4[2]; af[3] = lo4[3];
+          af[4] = hi4[0]; af[5] = hi4[1]; af[6] = hi4[2]; af[7] = hi4[3];
+          accw[hb] = M::mma(af, df[c], accw[hb]);
+        } else {
+          accw[hb] = M::mma(tile[kofs<false>(c, g, 0) * BWS_SLD + 32 * hb + n], df[c], accw[hb]);
+        }
+      }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
+
+  // Partials: wave w takes hidden block hb = w; the others hand it theirs through the
+  // tiles' area as [w][source][value / 4][lane] float4.  Added in wave order.
+  db2p += __shfl_xor(db2p, 32);
+  __syncthreads();  // every wave is done with its tile
+  float4* const parts = reinterpret_cast<float4*>(area);
+#pragma unroll
+  for (int hb = 0; hb < BWS_WAVES; ++hb) {
+    if (hb == wave) continue;
+    const int s = wave < hb ? wave : wave - 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      parts[((hb * (BWS_WAVES - 1) + s) * 4 + q) * 64 + lane] =
+          make_float4(accw[hb][4 * q], accw[hb][4 * q + 1], accw[hb][4 * q + 2], accw[hb][4 * q + 3]);
+  }
+  if (g == 0) db_s[wave * 32 + n] = db2p;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    // (wave is uniform: its own accumulators are picked by scalar branches)
+    float4 own = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int hb = 0; hb < BWS_WAVES; ++hb)
+      if (hb == wave) own = make_float4(accw[hb][4 * q], accw[hb][4 * q + 1], accw[hb][4 * q + 2], accw[hb][4 * q + 3]);
+    float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int w = 0; w < BWS_WAVES; ++w) {
+      float4 v = own;
+      if (w != wave) v = parts[((wave * (BWS_WAVES - 1) + (w < wave ? w : w - 1)) * 4 + q) * 64 + lane];
+      sum.x += v.x;
+      sum.y += v.y;
+      sum.z += v.z;
+      sum.w += v.w;
+    }
+    float4& w = *reinterpret_cast<float4*>(stage + n * BWS_SLD + 32 * wave + 8 * q + 4 * g);
+    float4 o = w;
+    o.x = fmaf(-lr, sum.x, o.x);
+    o.y = fmaf(-lr, sum.y, o.y);
+    o.z = fmaf(-lr, sum.z, o.z);
+    o.w = fmaf(-lr, sum.w, o.w);
+    w = o;
+  }
+  if (tid < 32 && lvalid) {
+    float db2 = db_s[tid];
+#pragma unroll
+    for (int w = 1; w < BWS_WAVES; ++w) db2 += db_s[w * 32 + tid];
+    b2[label] = fmaf(-lr, db2, bias);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k)  // (rows past L fall outside the buffer and are dropped)
+    __builtin_amdgcn_raw_buffer_store_b128(
+        __builtin_bit_cast(u32x4, *reinterpret_cast<const float4*>(stage + (wrow + 8 * k) * BWS_SLD + wcol)), w2r,
+        voff + k * 8 * HID * 4, 0, 0);
+}
+
+template <bool BF16, int MODE>
 static hipError_t launch_bwd(int grid, size_t shm, hipStream_t st, hipEvent_t t0, hipEvent_t t1, float* W2,
                              float* b2, int L, const void* H1, const void* H1T, int ld_t, int B, const float* lse,
                              const float* rw, const int32_t* lbeg, const int32_t* lpair, float lr,
@@ -705,14 +910,26 @@ static hipError_t launch_bwd(int grid, size_t shm, hipStream_t st, hipEvent_t t0
   const float log2_invB = (float)log2((double)invB);
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_out_bwd<BF16, MODE, RS>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_out_bwd<BF16, MODE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  hipExtLaunchKernelGGL((k_out_bwd<BF16, MODE, RS>), dim3(grid), dim3(BWD_THREADS), shm, st, t0, t1, 0, W2, b2,
+  hipExtLaunchKernelGGL((k_out_bwd<BF16, MODE>), dim3(grid), dim3(BWD_THREADS), shm, st, t0, t1, 0, W2, b2,
                         L, (const E*)H1, (const E*)H1T, ld_t, B, lse, rw, lbeg, lpair, lr, invB, log2_invB);
   return hipGetLastError();
+}
+
+// Where the backward runs k_out_bwd_short: while its workgroups (one per label block)
+// are one round of the GPU beside the kernel of B <= 256, whose waves each own a block
+// and its next one's loads, and a few rounds beside the others.  Measured, us with it | without:
+//   bf16: L = 10,000, B = 256: 10.8 | 13.4     L = 30,000, B = 256: 17.8 | 15.1
+//         L = 10,000, B = 1000: 18.8 | 63.6    L = 30,000, B = 600: 24.0 | 41.0
+//         L = 60,000, B = 600: 40.0 | 41.5     L = 120,000, B = 900: 97.0 | 95.1
+//   fp32: L = 1,000, B = 128: 10.4 | 18.7      L = 30,000, B = 200: 53.3 | 72.0
+//         L = 200,000, B = 128: 191.8 | 177.8
+static bool bwd_is_short(bool use_bf16, int n_blocks, int B) {
+  return n_blocks <= (use_bf16 && B <= BWD_CHUNK ? 512 : 2048);
 }
 
 hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void* H1,
@@ -720,6 +937,23 @@ hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void
                           const int32_t* lbeg, const int32_t* lpair, float lr, int n_cu,
                           hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   const int nrb = (B + 31) / 32;
+  if (bwd_is_short(use_bf16, (L + 31) / 32, B)) {
+    static bool attr_done[2] = {};
+    const void* fn = use_bf16 ? (const void*)k_out_bwd_short<true> : (const void*)k_out_bwd_short<false>;
+    if (!attr_done[use_bf16]) {
+      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (e != hipSuccess) return e;
+      attr_done[use_bf16] = true;
+    }
+    const size_t lds = (use_bf16 ? bws_fixed_lds<true>() : bws_fixed_lds<false>()) + (size_t)32 * nrb * 4;
+    const float inv = 1.0f / (float)B;
+    auto go = [&](auto kern, auto* h1) {
+      hipExtLaunchKernelGGL(kern, dim3((L + 31) / 32), dim3(BWS_THREADS), lds, st, t0, t1, 0, W2, b2, L, h1, B, lse, rw,
+                            lbeg, lpair, lr, inv, (float)log2((double)inv));
+      return hipGetLastError();
+    };
+    return use_bf16 ? go(k_out_bwd_short<true>, (const bf16*)H1) : go(k_out_bwd_short<false>, (const float*)H1);
+  }
   const int mode = !use_bf16 ? BWD_GLOBAL : (B <= BWD_CHUNK ? BWD_STAGED : BWD_CHUNKED);
   const int bpad = nrb * 32;
   const int mspan = mode == BWD_CHUNKED ? BWD_CROWS : bpad;  // rows of one target mask
@@ -752,19 +986,10 @@ hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void
     return hipGetLastError();
   }
   if (mode == BWD_CHUNKED)
-    return launch_bwd<true, BWD_CHUNKED, 1>(grid, shm, st, t0, t1, W2, b2, L, H1, H1T, ld_t, B, lse, rw, lbeg,
-                                            lpair, lr, invB);
-  // fp32 operands with few label blocks: 4 wavefronts share a block's rows
-  // (every wave would otherwise own a block and most of the GPU would idle)
-  constexpr int RS = 4;
-  if (n_blocks < n_cu * BWD_WAVES / RS && B <= 512) {
-    const int units = (n_blocks + BWD_WAVES / RS - 1) / (BWD_WAVES / RS);
-    const size_t shr = shm + (size_t)(BWD_WAVES / RS) * (RS - 1) * 65 * 64 * sizeof(float);
-    return launch_bwd<false, BWD_GLOBAL, RS>(units < 2 * n_cu ? units : 2 * n_cu, shr, st, t0, t1, W2, b2, L,
-                                             H1, H1T, ld_t, B, lse, rw, lbeg, lpair, lr, invB);
-  }
-  return launch_bwd<false, BWD_GLOBAL, 1>(grid, shm, st, t0, t1, W2, b2, L, H1, H1T, ld_t, B, lse, rw, lbeg,
-                                          lpair, lr, invB);
+    return launch_bwd<true, BWD_CHUNKED>(grid, shm, st, t0, t1, W2, b2, L, H1, H1T, ld_t, B, lse, rw, lbeg, lpair, lr,
+                                         invB);
+  return launch_bwd<false, BWD_GLOBAL>(grid, shm, st, t0, t1, W2, b2, L, H1, H1T, ld_t, B, lse, rw, lbeg, lpair, lr,
+                                       invB);
 }
 
 }  // namespace asgd

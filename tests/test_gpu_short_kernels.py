@@ -1,0 +1,45 @@
+"""The whole step at trained-scale weights where the output layer changes kernels: the forward
+with waves on tiles of their own and the backward with waves on row blocks of their own, on both
+sides of every line of their rules, with remainders in rows, labels and waves."""
+import numpy as np
+import pytest
+
+import paper_2110_07029_amd as asgd
+from oracle import model as om
+from paper_2110_07029_amd import synth
+
+from gpu_util import RTOL_BF16, RTOL_FP32, Setup, assert_update_close, flush, step_magnitudes, write_params
+from test_gpu_trained_scale import trained_scale
+
+pytestmark = pytest.mark.gpu
+
+
+# forward: short up to 64 rows or 32,768 (tile, 32-row block) products; backward: up to 512
+# label blocks at 256 rows or less with bf16 operands, else 2,048.  L = 7, 32, 33: less than
+# a tile, a tile and one more; 16,385 and 65,537: one label past the backward's lines
+@pytest.mark.parametrize("B,L", [(1, 7), (1, 33), (33, 32), (64, 257), (65, 1_000), (256, 16_384), (255, 16_385),
+                                 (257, 1_000), (300, 65_536), (257, 65_537), (1_000, 2_001)])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_step_parity(B, L, bf16):
+    if not bf16 and B * L > 5_000_000:
+        pytest.skip("the oracle's time")
+    flush(f"short kernels: B={B} L={L} bf16={bf16}")
+    w = synth.Workload("short", 3_000, L, B, B, 0.5, True, "lognormal", 2.5, 0.6, 100, 1.05, "uniform", "poisson",
+                       2.0, 1.1, 2)
+    s = Setup(w, B, B, bf16=bf16)
+    try:
+        p = trained_scale(s.F, s.L, 8)
+        write_params(s.m, p)
+        x, y = s.host_batch(0, B)
+        loss = asgd.asgd_train_step(s.m, s.xb(0, B), s.yb(0, B), 0.5, want_loss=True)
+        ref, ref_loss, g, fw = om.train_step(p, x, y, 0.5, "fp32")
+        assert abs(loss - ref_loss) <= 2e-3 * max(1.0, abs(ref_loss))
+        got = s.params()
+        mag = step_magnitudes(p, x, y, g, fw, 0.5)
+        rtol = RTOL_BF16 if bf16 else RTOL_FP32
+        for k in ("W2", "b2", "b1"):
+            assert_update_close(k, p[k], got[k], ref[k], rtol, mag[k])
+        t = g["touched"]
+        assert_update_close("W1", p["W1"][t], got["W1"][t], ref["W1"][t], rtol, mag["W1"])
+    finally:
+        s.free()
