@@ -386,7 +386,7 @@ asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipS
   TIMED_ON(m, ASGD_K_GATHER, st, launch_gather_fwd(m->bf16, xd, y ? &yd : nullptr, m->W1(), m->b1(), m->F, m->L,
                                                    m->A1, m->H1, m->H1T, rows_pad, m->rows_pad_max, m->keys,
                                                    m->row_of, m->lkeys, m->lrow, m->rw, m->err, validate ? 1 : 0,
-                                                   m->gpart, st, m->extra ? nullptr : done));
+                                                   m->gpart, st == m->stream, st, m->extra ? nullptr : done));
   if (m->extra) {
     TIMED_ON(m, ASGD_K_DENSE_FWD, st, launch_dense_fwd(m->bf16, m->A1, m->Wh(), m->bh(), B, rows_pad, m->A2,
                                                        m->H1, m->H1T, m->rows_pad_max, st));

@@ -30,14 +30,14 @@ hipError_t launch_fill_int(int32_t* p, int32_t v, int64_t n, hipStream_t st);
 // label id (L if invalid), lrow[q] = its row, and rw[i] = 1/|Y_i|.
 // Batches whose rows average GATHER_LONG_ROW entries or more split every row
 // over GATHER_SPLIT workgroups; gpart: workspace of GATHER_SPLIT x ld_t x HID
-// floats for their partial sums (ld_t >= rows_pad).
+// floats for their partial sums (ld_t >= rows_pad).  alone: nothing runs beside it.
 constexpr int GATHER_SPLIT = 4;
 constexpr int GATHER_LONG_ROW = 160;
 hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, const float* W1,
                              const float* b1, int F, int L, float* A1, void* H1, void* H1T,
                              int rows_pad, int ld_t, int32_t* keys, int32_t* row_of,
                              int32_t* lkeys, int32_t* lrow, float* rw, int32_t* err, int validate,
-                             float* gpart, hipStream_t st, hipEvent_t done = nullptr);
+                             float* gpart, bool alone, hipStream_t st, hipEvent_t done = nullptr);
 // (done: completed by the launcher's last kernel when it has finished, with no
 // marker of its own on the stream)
 

@@ -61,17 +61,19 @@ hipError_t launch_fill_int(int32_t* p, int32_t v, int64_t n, hipStream_t st) {
 // row of the batch, and nnz per row is heavy-tailed).  The partial sums are
 // added in wavefront order (then in workgroup order), then b1.
 // ---------------------------------------------------------------------------
-// Short rows: four wavefronts (one per SIMD), so that the workgroup can start
-// on a CU where the output-layer backward leaves room for only one more
-// wavefront per SIMD, which is where the next step's gather runs when the
-// step is pipelined.  Long rows (split over workgroups; the gather then runs
-// alone on the model's stream): eight.
-constexpr int gather_waves(int split) { return split > 1 ? 8 : 4; }
+// Beside the backward of a pipelined step: four wavefronts (one per SIMD), so that
+// the workgroup can start on a CU where the output-layer backward leaves room for
+// only one more wavefront per SIMD.  Alone on the model's stream, up to
+// GATHER_WIDE_ROWS rows: eight, as the longest row decides (15.3 -> 10.5 us for 256
+// rows of 75 entries on average, 10.7 -> 8.6 for 50; 2,000 rows: equal; 16,384 rows,
+// which fill the GPU: 78 -> 107; sixteen: slower from 600 rows on).  Long rows split
+// over workgroups: eight.
+constexpr int GATHER_WIDE_ROWS = 2048;
 constexpr int GATHER_UNROLL = 16;
 static_assert(64 % GATHER_UNROLL == 0, "readlane indices stay below 64");
 
-template <bool BF16, int SPLIT>
-__global__ __launch_bounds__(64 * gather_waves(SPLIT)) void k_gather_fwd(
+template <bool BF16, int SPLIT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_gather_fwd(
     CsrDev x, CsrDev y, int has_y, const float* __restrict__ W1, const float* __restrict__ b1,
     int F, int L, float* __restrict__ A1, typename Mma<BF16>::elem* __restrict__ H1,
     typename Mma<BF16>::elem* __restrict__ H1T, int rows_pad, int ld_t, int32_t* __restrict__ keys,
@@ -79,7 +81,6 @@ __global__ __launch_bounds__(64 * gather_waves(SPLIT)) void k_gather_fwd(
     float* __restrict__ rw,
     int32_t* __restrict__ err, int validate, float* __restrict__ gpart) {
   using E = typename Mma<BF16>::elem;
-  constexpr int WAVES = gather_waves(SPLIT);
   __shared__ float2 part[WAVES][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = (int)blockIdx.x / SPLIT, piece = (int)blockIdx.x % SPLIT;
@@ -236,12 +237,13 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
                              const float* b1, int F, int L, float* A1, void* H1, void* H1T,
                              int rows_pad, int ld_t, int32_t* keys, int32_t* row_of,
                              int32_t* lkeys, int32_t* lrow, float* rw, int32_t* err, int validate,
-                             float* gpart, hipStream_t st, hipEvent_t done) {
+                             float* gpart, bool alone, hipStream_t st, hipEvent_t done) {
   CsrDev yy = y ? *y : CsrDev{0, 0, 0, nullptr, nullptr, nullptr};
+  const bool wide = alone && x.n_rows <= GATHER_WIDE_ROWS;
   const bool split = gpart && x.n_rows > 0 && (int64_t)x.nnz >= (int64_t)GATHER_LONG_ROW * x.n_rows;
   // the last launch completes `done`
-  auto go = [&](auto kern, int pieces, auto* h1, auto* h1t, hipEvent_t ev) {
-    const dim3 grid(rows_pad * pieces), block(64 * gather_waves(pieces));
+  auto go = [&](auto kern, int pieces, int waves, auto* h1, auto* h1t, hipEvent_t ev) {
+    const dim3 grid(rows_pad * pieces), block(64 * waves);
     const int has_y = y != nullptr;
     if (ev)
       hipExtLaunchKernelGGL(kern, grid, block, 0, st, nullptr, ev, 0, x, yy, has_y, W1, b1, F, L, A1, h1, h1t,
@@ -260,17 +262,21 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
   };
   if (use_bf16) {
     if (split) {
-      go(k_gather_fwd<true, GATHER_SPLIT>, GATHER_SPLIT, (bf16*)H1, (bf16*)H1T, nullptr);
+      go(k_gather_fwd<true, GATHER_SPLIT, 8>, GATHER_SPLIT, 8, (bf16*)H1, (bf16*)H1T, nullptr);
       finish(k_gather_finish<true>, (bf16*)H1, (bf16*)H1T);
+    } else if (wide) {
+      go(k_gather_fwd<true, 1, 8>, 1, 8, (bf16*)H1, (bf16*)H1T, done);
     } else {
-      go(k_gather_fwd<true, 1>, 1, (bf16*)H1, (bf16*)H1T, done);
+      go(k_gather_fwd<true, 1, 4>, 1, 4, (bf16*)H1, (bf16*)H1T, done);
     }
   } else {
     if (split) {
-      go(k_gather_fwd<false, GATHER_SPLIT>, GATHER_SPLIT, (float*)H1, (float*)H1T, nullptr);
+      go(k_gather_fwd<false, GATHER_SPLIT, 8>, GATHER_SPLIT, 8, (float*)H1, (float*)H1T, nullptr);
       finish(k_gather_finish<false>, (float*)H1, (float*)H1T);
+    } else if (wide) {
+      go(k_gather_fwd<false, 1, 8>, 1, 8, (float*)H1, (float*)H1T, done);
     } else {
-      go(k_gather_fwd<false, 1>, 1, (float*)H1, (float*)H1T, done);
+      go(k_gather_fwd<false, 1, 4>, 1, 4, (float*)H1, (float*)H1T, done);
     }
   }
   return hipGetLastError();
