@@ -369,9 +369,10 @@ void timer_pair(asgd_model* m, int k, hipEvent_t* t0, hipEvent_t* t1) {
 
 // Gather forward (+ keys) on stream st into the next copy of H1 / H1T / rw,
 // optional validation check.  Leaves H1 / A1 ready.
-// done (optional): an event completed once the gather's work has finished on st
+// done (optional): an event completed once the gather's work has finished on st.
+// dense_rides: the second hidden layer in the gather's own launches.
 asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipStream_t st, int* rows_pad_out,
-                       hipEvent_t done = nullptr) {
+                       hipEvent_t done = nullptr, bool dense_rides = false) {
   const int B = x->n_rows;
   const int RB = out_rows_per_block(m->bf16);
   const int rows_pad = (int)round_up(B, RB);
@@ -383,11 +384,13 @@ asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipS
   if (validate) HIP_TRY(launch_fill_int(m->err, 0, 1, st));
   CsrDev xd = dev(x);
   CsrDev yd = y ? dev(y) : CsrDev{};
+  const DenseFwd dn{m->Wh(), m->bh(), m->A2};
   TIMED_ON(m, ASGD_K_GATHER, st, launch_gather_fwd(m->bf16, xd, y ? &yd : nullptr, m->W1(), m->b1(), m->F, m->L,
                                                    m->A1, m->H1, m->H1T, rows_pad, m->rows_pad_max, m->keys,
                                                    m->row_of, m->lkeys, m->lrow, m->rw, m->err, validate ? 1 : 0,
-                                                   m->gpart, st == m->stream, st, m->extra ? nullptr : done));
-  if (m->extra) {
+                                                   m->gpart, st == m->stream, dense_rides ? &dn : nullptr, st,
+                                                   m->extra && !dense_rides ? nullptr : done));
+  if (m->extra && !dense_rides) {
     TIMED_ON(m, ASGD_K_DENSE_FWD, st, launch_dense_fwd(m->bf16, m->A1, m->Wh(), m->bh(), B, rows_pad, m->A2,
                                                        m->H1, m->H1T, m->rows_pad_max, st));
     if (done) HIP_TRY(hipEventRecord(done, st));
@@ -439,7 +442,8 @@ asgd_status run_sort(asgd_model* m, hipStream_t st, const SortPlan& plan) {
 // model's stream; with y, dA1 (dA2 with the second hidden layer) follows on
 // da_stream, after an event when that is another stream (the training step
 // runs it beside the backward).  With sort (da_stream the model's stream), the
-// passes of the feature sort run inside the two launches.
+// passes of the feature sort run inside the two launches, and the second of them
+// carries dA2 on to dA1.
 asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int rows_pad,
                         const LabelJob* labels, hipStream_t da_stream, const SortPlan* sort = nullptr) {
   const int B = x->n_rows;
@@ -453,12 +457,14 @@ asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int
   CsrDev yd = y ? dev(y) : CsrDev{};
   float* const A = m->extra ? m->A2 : m->A1;
   float* const dA = m->extra ? m->dA2 : m->dA1;
-  // dA1 on the model's stream: in the same launch as lse and the target terms
+  // dA1 on the model's stream: in the same launch as lse and the target terms, and, on one
+  // stream (with sort), through the second hidden layer
+  const DenseBwd dn{m->Wh(), m->A1, m->dA1};
   const bool fused = y && da_stream == m->stream;
   TIMED(m, ASGD_K_OUT_COMBINE, launch_out_lse_targets(m->bf16, B, s_eff, m->m_part, m->s_part, rows_pad, m->W2(),
                                                       m->b2(), m->L, m->H1, y ? &yd : nullptr, m->lse,
                                                       m->loss_rows, m->tw, m->o_part, A, fused ? dA : nullptr,
-                                                      sort && sort->passes > 1 ? &sort->pass[1] : nullptr, m->stream,
+                                                      sort && m->extra ? &dn : nullptr, sort && sort->passes > 1 ? &sort->pass[1] : nullptr, m->stream,
                                                       y && !fused ? m->ev_dA1 : nullptr));
   if (!y || fused) return ASGD_OK;
   // the event was completed by the lse/targets launch itself: a separate record
@@ -716,6 +722,7 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
   const bool pipelined = two_streams && !m->unfused;
   const bool one_stream = !two_streams;
   m->pipe = m->pipe && pipelined;
+  bool wgrad_rides = false;  // the second hidden layer's update inside the sparse update's launch
   if (pipelined) {
     // Two streams.  Internal: gather (after the previous step's W1 update,
     // so it overlaps that step's output-layer backward), feature sort, then,
@@ -745,7 +752,7 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
     // launch), or, with stored logits, the sort and the sparse update on the
     // internal one, beside the logits and the backward.
     const bool sort_rides = !m->unfused;  // (one stream: at most 49,152 entries)
-    s = run_gather(m, x, y, m->stream, &rows_pad, one_stream ? nullptr : m->ev_fork);
+    s = run_gather(m, x, y, m->stream, &rows_pad, one_stream ? nullptr : m->ev_fork, sort_rides && m->extra);
     if (s) return s;
     if (!sort_rides) {
       if (!one_stream) HIP_TRY(hipStreamWaitEvent(m->aux, m->ev_fork, 0));
@@ -755,7 +762,8 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
     s = m->unfused ? run_forward_unfused(m, x, y, rows_pad, &labels)
                    : run_forward(m, x, y, rows_pad, &labels, m->stream, &sort);
     if (s) return s;
-    if (m->extra)
+    wgrad_rides = m->extra && sort_rides;
+    if (m->extra && !wgrad_rides)
       TIMED(m, ASGD_K_DENSE_BWD, launch_dense_bwd(m->dA2, m->A1, m->Wh(), m->bh(), B, rows_pad, lr, m->dA1,
                                                   m->stream));
     if (!one_stream) {
@@ -764,12 +772,17 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
     }
   }
   hipStream_t const ust = one_stream ? m->stream : m->aux;
+  // on one stream the sparse update's second half runs inside the backward's launch
+  JoinJob join{};
+  const bool join_rides = one_stream && out_bwd_takes_join(m->bf16, m->L, B, x->nnz, m->n_cu);
+  const DenseWgrad wgrad{m->dA2, m->A1, m->Wh(), m->bh()};
   TIMED_ON(m, ASGD_K_W1_UPDATE, ust,
            launch_sparse_update(m->W1(), m->F, sort.keys_out, sort.vals_out, x->nnz, m->row_of, xd, m->dA1, lr, B,
-                                m->b1(), m->loss_rows, m->loss, m->w1_part, ust, one_stream ? nullptr : m->ev_join));
+                                m->b1(), m->loss_rows, m->loss, m->w1_part, join_rides ? &join : nullptr,
+                                wgrad_rides ? &wgrad : nullptr, ust, one_stream ? nullptr : m->ev_join));
   TIMED_LAUNCH(m, ASGD_K_OUT_BWD,
                launch_out_bwd(m->bf16, m->W2(), m->b2(), m->L, m->H1, m->H1T, m->rows_pad_max, B, m->lse, m->rw,
-                              m->lbeg, m->lpair, lr, m->n_cu, m->stream, t0_, t1_));
+                              m->lbeg, m->lpair, lr, m->n_cu, join_rides ? &join : nullptr, m->stream, t0_, t1_));
   if (!one_stream) HIP_TRY(hipStreamWaitEvent(m->stream, m->ev_join, 0));
   m->pipe = pipelined;
   if (loss_out) return asgd_model_last_loss(m, loss_out);

@@ -33,12 +33,18 @@ hipError_t launch_fill_int(int32_t* p, int32_t v, int64_t n, hipStream_t st);
 // floats for their partial sums (ld_t >= rows_pad).  alone: nothing runs beside it.
 constexpr int GATHER_SPLIT = 4;
 constexpr int GATHER_LONG_ROW = 160;
+struct DenseFwd {
+  const float *Wh, *bh;
+  float* A2;
+};
 hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, const float* W1,
                              const float* b1, int F, int L, float* A1, void* H1, void* H1T,
                              int rows_pad, int ld_t, int32_t* keys, int32_t* row_of,
                              int32_t* lkeys, int32_t* lrow, float* rw, int32_t* err, int validate,
-                             float* gpart, bool alone, hipStream_t st, hipEvent_t done = nullptr);
-// (done: completed by the launcher's last kernel when it has finished, with no
+                             float* gpart, bool alone, const DenseFwd* dense, hipStream_t st,
+                             hipEvent_t done = nullptr);
+// (dense, with alone only: the second hidden layer in the same launches; H1 / H1T then
+// receive its output.  done: completed by the launcher's last kernel when it has finished, with no
 // marker of its own on the stream)
 
 // ---- stable LSD radix sort of (key, position) -----------------------------
@@ -70,6 +76,19 @@ hipError_t launch_sort(const SortPlan& plan, int32_t* hist, hipStream_t st);
 constexpr int SORT_RIDE_MAX = (1 << 16) - 1;
 int sort_spread(SortJob* job, int nthreads, int wgs);
 int sort_pass_lds(int nbits, int nthreads);
+
+// ---- the sparse update's second half (k_sparse.hip) --------------------------------
+// Joins the segments of W1 that cross a window, from the partial rows of the first half:
+// a launch of its own, or join_wgs workgroups of four wavefronts in the backward's.
+struct JoinJob {
+  float* W1;
+  int F;
+  const int32_t* skeys;
+  int n_keys;  // 0: nothing to join
+  float lr;
+  const float* part;
+};
+int join_wgs(int n_keys);
 
 // ---- (label, row) pairs grouped by 32-label block ---------------------------
 // For the m label entries: lbeg[b] .. lbeg[b+1] (b < ceil(L/32)) is the range
@@ -116,12 +135,17 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
 // [B x 128] (reads W2 before the backward updates it).
 // With y and dA1 (non-null), the same launch also forms dA1 = ((O/s - tw) / B) * [A1 > 0]
 // from the partials (o_part, A1 as for launch_out_dA1); dA1 null: lse and targets only.
+struct DenseBwd {
+  const float *Wh, *A1;
+  float* dA1;
+};
 hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float* m_part, const float* s_part,
                                   int ld_part, const float* W2, const float* b2, int L, const void* H1,
                                   const CsrDev* y, float* lse, float* loss_rows, float* tw, const float* o_part,
-                                  const float* A1, float* dA1, const SortJob* sort, hipStream_t st,
-                                  hipEvent_t done = nullptr);
-// (sort: a pass of the feature sort to run in the same launch, with dA1 only;
+                                  const float* A1, float* dA1, const DenseBwd* dense, const SortJob* sort,
+                                  hipStream_t st, hipEvent_t done = nullptr);
+// (dense, with dA1 only: A1 and dA1 above are the second hidden layer's A2 and dA2, and the
+// launch goes on to the first layer's dA1 = (dA2 Wh) * [A1 > 0].  sort: a pass of the feature sort to run in the same launch, with dA1 only;
 // done: an event that the launch itself completes when the kernel has
 // finished, with no marker of its own on the stream)
 // Per row: dA1 = ((O/s - tw) / B) * [A1 > 0] from the forward's partials (reads no W2);
@@ -131,17 +155,26 @@ hipError_t launch_out_dA1(int B, int splits, const float* m_part, const float* s
 // Recompute Z per label tile, dZ = (softmax - T)/B, dW2 = dZ^T H1, db2; update W2, b2 in place.
 hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void* H1,
                           const void* H1T, int ld_t, int B, const float* lse, const float* rw,
-                          const int32_t* lbeg, const int32_t* lpair, float lr, int n_cu,
+                          const int32_t* lbeg, const int32_t* lpair, float lr, int n_cu, const JoinJob* join,
                           hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// Whether its launch takes the join of n_keys entries along.
+bool out_bwd_takes_join(bool use_bf16, int L, int B, int n_keys, int n_cu);
 // (t0, t1 as for launch_out_fwd_train)
 // W1[f] -= lr * sum_{entries of f} x * dA1[row], one segment per distinct f
 // (keys sorted by feature, invalid ids >= F last); and, in the same launch,
 // db1 = sum_i dA1[i]; b1 -= lr db1; loss = mean_i loss_rows[i].
 // part: 2 * sparse_windows(n_keys) * HID floats of scratch.
+// join: receives the second half's job instead of its launch.  wgrad: the second hidden
+// layer's weight update in the same launch (its workgroups read dA2 and A1, write Wh and bh).
+struct DenseWgrad {
+  const float *dA2, *A1;
+  float *Wh, *bh;
+};
 int sparse_windows(int n_keys);
 hipError_t launch_sparse_update(float* W1, int F, const int32_t* skeys, const int32_t* svals, int n_keys,
                                 const int32_t* row_of, const CsrDev& x, const float* dA1, float lr, int B,
-                                float* b1, const float* loss_rows, float* loss, float* part, hipStream_t st,
+                                float* b1, const float* loss_rows, float* loss, float* part, JoinJob* join,
+                                const DenseWgrad* wgrad, hipStream_t st,
                                 hipEvent_t done = nullptr);  // done: as for launch_gather_fwd
 // Distinct sorted feature ids (compaction of segment heads); count to *count_dev.
 hipError_t launch_touched(const int32_t* skeys, int n_keys, int F, int32_t* ids, int32_t* count_dev,

@@ -198,4 +198,133 @@ __device__ void wg_sort_pass(const SortJob& j, int c, int32_t* lds) {
   }
 }
 
+// ---- joining the sparse update's segments that cross windows ----------------------
+// (k_sparse.hip; also workgroups of the backward's launch)
+constexpr int SPU_WIN = 32;      // sorted entries per window
+constexpr int JOIN_BATCH = 16;   // continuing pieces loaded together
+constexpr int JOIN_WINDOWS = 8;  // windows per wavefront beside the backward (their joins run one after the other)
+
+// Windows [first, first + COUNT) by one wavefront: a window whose last entry's
+// segment starts in it and runs past its end adds the segment's pieces (its own
+// part[2w + 1], then part[2v] of the windows v after it, in order) and applies the sum
+// to W1.  One lane looks at each window; the heads found are joined in turn.
+template <int COUNT>
+__device__ __forceinline__ void wave_join_windows(const JoinJob& j, int first) {
+  const int lane = threadIdx.x & 63;
+  const int32_t* __restrict__ skeys = j.skeys;
+  const int n_keys = j.n_keys, F = j.F;
+  const int w0 = (first + lane) * SPU_WIN;
+  int f = F;
+  if (lane < COUNT && w0 + SPU_WIN < n_keys) {
+    const int last = skeys[w0 + SPU_WIN - 1], next = skeys[w0 + SPU_WIN];
+    const int head = skeys[w0], before = w0 > 0 ? skeys[w0 - 1] : -1;
+    // (a segment that continues from the window before is joined by an earlier one)
+    if (last < F && next == last && !(head == last && before == last)) f = last;
+  }
+  uint64_t heads = __ballot(f < F);
+  while (heads) {
+    const int src = __builtin_ctzll(heads);
+    heads &= heads - 1;
+    const int fw = __builtin_amdgcn_readlane(f, src), win = first + src;
+    const float2* P = reinterpret_cast<const float2*>(j.part) + lane;
+    float2* wp = reinterpret_cast<float2*>(j.W1 + (size_t)fw * HID) + lane;
+    const float2 w = *wp;
+    float2 acc = P[(size_t)(2 * win + 1) * (HID / 2)];
+    // windows win+1 .. win+m hold the rest: window v is followed by another piece when it
+    // is all fw and the next window starts with fw (one lane per window)
+    int m = 0;
+    for (;;) {
+      const int v1 = (win + 2 + m + lane) * SPU_WIN;  // first entry after window win+1+m+lane
+      const bool more = v1 < n_keys && skeys[v1] == fw && skeys[v1 - 1] == fw;
+      const uint64_t stop = __ballot(!more);
+      if (stop) {
+        m += __builtin_ctzll(stop) + 1;
+        break;
+      }
+      m += 64;
+    }
+    for (int v0 = 0; v0 < m; v0 += JOIN_BATCH) {
+      float2 c[JOIN_BATCH];
+#pragma unroll
+      for (int k = 0; k < JOIN_BATCH; ++k) c[k] = P[(size_t)(2 * (win + 1 + min(v0 + k, m - 1))) * (HID / 2)];
+#pragma unroll
+      for (int k = 0; k < JOIN_BATCH; ++k)
+        if (v0 + k < m) {
+          acc.x += c[k].x;
+          acc.y += c[k].y;
+        }
+    }
+    *wp = make_float2(fmaf(-j.lr, acc.x, w.x), fmaf(-j.lr, acc.y, w.y));
+  }
+}
+
+// ---- the second hidden layer, one row in the workgroup that has it ------------------
+// A2 = relu(A1) Wh^T + bh for one row, by 256 threads of the workgroup (t < 256 work, the
+// others only pass): thread (o, half) sums 64 inputs of unit o.  h_s: relu(A1) in LDS,
+// written before a barrier.  Returns the unit's A2 on both halves.
+__device__ __forceinline__ float dense_row_unit(const float* __restrict__ Wh, const float* __restrict__ bh,
+                                                const float* h_s, int t) {
+  const int o = t >> 1, k0 = (t & 1) * (HID / 2);
+  const float4* w = reinterpret_cast<const float4*>(Wh + (size_t)o * HID + k0);
+  float acc = t & 1 ? 0.0f : bh[o];
+#pragma unroll
+  for (int k = 0; k < HID / 8; ++k) {
+    const float4 v = w[k];
+    const float4 h = *reinterpret_cast<const float4*>(h_s + k0 + 4 * k);
+    acc = fmaf(v.x, h.x, acc);
+    acc = fmaf(v.y, h.y, acc);
+    acc = fmaf(v.z, h.z, acc);
+    acc = fmaf(v.w, h.w, acc);
+  }
+  return acc + __shfl_xor(acc, 1);
+}
+
+// dWh[o][k] = sum_r dA2[r][o] relu(A1[r][k]) and dbh[o] = sum_r dA2[r][o], in row order;
+// then the update in place.  One workgroup of 256 threads: output units 2 bid and 2 bid + 1
+// x 128 input units; the rows come through LDS in chunks of 64, the next chunk's loads in
+// flight while one is summed (a chunk's load latency is longer than its sums).
+constexpr int WGRAD_WGS = HID / 2;
+__device__ inline void dense_wgrad_wg(const DenseWgrad& wg, int B, float lr, int bid) {
+  constexpr int CHUNK = 64, NT = 2 * HID, LD = CHUNK * HID / 4 / NT;  // 8 float4 per thread
+  __shared__ float hs[CHUNK][HID];
+  __shared__ float ds[CHUNK][2];
+  const int tid = threadIdx.x;
+  const int k = tid % HID, half = tid / HID;
+  const int o = bid * 2 + half;
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  v4 a[LD];
+  float d = 0.0f;
+  auto load = [&](int c0) {  // (rows past B: the last one, multiplied by a zero dA2)
+#pragma unroll
+    for (int u = 0; u < LD; ++u) {
+      const int e = tid + u * NT, r = min(c0 + e / (HID / 4), B - 1);
+      a[u] = *reinterpret_cast<const v4*>(wg.A1 + (size_t)r * HID + 4 * (e % (HID / 4)));
+    }
+    const int r = c0 + tid / 2;
+    d = tid < 2 * CHUNK && r < B ? wg.dA2[(size_t)r * HID + bid * 2 + tid % 2] : 0.0f;
+  };
+  load(0);
+  const float w_old = wg.Wh[o * HID + k], b_old = wg.bh[o];
+  float acc = 0.0f, db = 0.0f;
+  for (int c0 = 0; c0 < B; c0 += CHUNK) {
+    __syncthreads();  // the previous chunk is consumed
+#pragma unroll
+    for (int u = 0; u < LD; ++u) {
+      float* p = &hs[0][0] + 4 * (tid + u * NT);
+      p[0] = fmaxf(a[u].x, 0.0f); p[1] = fmaxf(a[u].y, 0.0f); p[2] = fmaxf(a[u].z, 0.0f); p[3] = fmaxf(a[u].w, 0.0f);
+    }
+    if (tid < 2 * CHUNK) ds[tid / 2][tid % 2] = d;
+    __syncthreads();
+    if (c0 + CHUNK < B) load(c0 + CHUNK);
+#pragma unroll 8
+    for (int r = 0; r < CHUNK; ++r) {
+      const float dv = ds[r][half];
+      acc = fmaf(dv, hs[r][k], acc);
+      db += dv;
+    }
+  }
+  wg.Wh[o * HID + k] = fmaf(-lr, acc, w_old);
+  if (k == 0) wg.bh[o] = fmaf(-lr, db, b_old);
+}
+
 }  // namespace asgd

@@ -9,8 +9,12 @@
 //               operand type (and transposed, for fp32 operands)
 //   backward  : dA1 = (dA2 Wh) * [A1 > 0]        (the pre-update Wh)
 //               dWh = dA2^T ReLU(A1), dbh = 1^T dA2, Wh -= lr dWh, bh -= lr dbh
+// These launches serve the step on two streams, prediction and inspection; on one stream
+// the same work rides in the launches around it (the gather, the per-row launch and the
+// sparse update: aux_dev.h), as three launches of 6-14 us were a third of a mid-sized step.
 #include "asgd_dev.h"
 #include "asgd_kernels.h"
+#include "aux_dev.h"
 
 namespace asgd {
 
@@ -78,40 +82,8 @@ __global__ __launch_bounds__(DN_THREADS) void k_dense_rows(const float* __restri
   }
 }
 
-// dWh[o][k] = sum_r dA2[r][o] relu(A1[r][k]) and dbh[o] = sum_r dA2[r][o], in
-// row order; then the update in place.  Workgroup = 2 output units x 128
-// input units; the rows come through LDS in chunks of 64 (all of a chunk's
-// loads in flight together), the chunk's dA2 values of the two units beside.
-constexpr int WG_CHUNK = 64;
-__global__ __launch_bounds__(DN_THREADS) void k_dense_wgrad(const float* __restrict__ dA2,
-                                                           const float* __restrict__ A1, int B,
-                                                           float lr, float* __restrict__ Wh,
-                                                           float* __restrict__ bh) {
-  __shared__ float hs[WG_CHUNK][HID];
-  __shared__ float ds[WG_CHUNK][2];
-  const int tid = threadIdx.x;
-  const int k = tid % HID, half = tid / HID;
-  const int o = blockIdx.x * 2 + half;
-  float acc = 0.0f, db = 0.0f;
-  for (int c0 = 0; c0 < B; c0 += WG_CHUNK) {
-    const int nr = min(WG_CHUNK, B - c0);
-    __syncthreads();  // the previous chunk is consumed
-    for (int e = tid; e < nr * HID / 4; e += DN_THREADS) {
-      const float4 v = reinterpret_cast<const float4*>(A1 + (size_t)c0 * HID)[e];
-      float* d = &hs[0][0] + 4 * e;
-      d[0] = fmaxf(v.x, 0.0f); d[1] = fmaxf(v.y, 0.0f); d[2] = fmaxf(v.z, 0.0f); d[3] = fmaxf(v.w, 0.0f);
-    }
-    for (int e = tid; e < nr * 2; e += DN_THREADS)
-      ds[e / 2][e % 2] = dA2[(size_t)(c0 + e / 2) * HID + blockIdx.x * 2 + e % 2];
-    __syncthreads();
-    for (int r = 0; r < nr; ++r) {
-      const float d = ds[r][half];
-      acc = fmaf(d, hs[r][k], acc);
-      db += d;
-    }
-  }
-  Wh[o * HID + k] = fmaf(-lr, acc, Wh[o * HID + k]);
-  if (k == 0) bh[o] = fmaf(-lr, db, bh[o]);
+__global__ __launch_bounds__(DN_THREADS) void k_dense_wgrad(DenseWgrad wg, int B, float lr) {
+  dense_wgrad_wg(wg, B, lr, blockIdx.x);
 }
 
 hipError_t launch_dense_fwd(bool use_bf16, const float* A1, const float* Wh, const float* bh, int B,
@@ -132,7 +104,7 @@ hipError_t launch_dense_bwd(const float* dA2, const float* A1, float* Wh, float*
   hipLaunchKernelGGL((k_dense_rows<false, false>), dim3((rows_pad + DN_ROWS - 1) / DN_ROWS),
                      dim3(DN_THREADS), 0, st, dA2, Wh, nullptr, B, rows_pad, dA1, (float*)nullptr,
                      (float*)nullptr, 0, A1);
-  hipLaunchKernelGGL(k_dense_wgrad, dim3(HID / 2), dim3(DN_THREADS), 0, st, dA2, A1, B, lr, Wh, bh);
+  hipLaunchKernelGGL(k_dense_wgrad, dim3(WGRAD_WGS), dim3(DN_THREADS), 0, st, DenseWgrad{dA2, A1, Wh, bh}, B, lr);
   return hipGetLastError();
 }
 

@@ -3,8 +3,11 @@
 // backward pass and the model initialisation.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "asgd_dev.h"
 #include "asgd_kernels.h"
+#include "aux_dev.h"
 
 namespace asgd {
 
@@ -72,14 +75,31 @@ constexpr int GATHER_WIDE_ROWS = 2048;
 constexpr int GATHER_UNROLL = 16;
 static_assert(64 % GATHER_UNROLL == 0, "readlane indices stay below 64");
 
-template <bool BF16, int SPLIT, int WAVES>
+// Unit t / 2 of row i's second hidden layer, by thread t of 256 (h_s: relu(A1) in LDS).
+template <bool BF16>
+__device__ __forceinline__ void dense_row_store(const DenseFwd& dn, const float* h_s, int i, int t,
+                                                typename Mma<BF16>::elem* H1, typename Mma<BF16>::elem* H1T,
+                                                int ld_t) {
+  const float a2 = dense_row_unit(dn.Wh, dn.bh, h_s, t);
+  if (t & 1) return;
+  const int o = t >> 1;
+  dn.A2[(size_t)i * HID + o] = a2;
+  const float h = fmaxf(a2, 0.0f);
+  H1[(size_t)i * HID + o] = (typename Mma<BF16>::elem)h;
+  if constexpr (!BF16) H1T[(size_t)o * ld_t + i] = h;
+}
+
+// DENSE: the workgroup that has a row's A1 also forms the row's second hidden layer
+// (A2 = relu(A1) Wh^T + bh; Wh comes from L2) and writes relu(A2) as the operand.
+template <bool BF16, int SPLIT, int WAVES, bool DENSE>
 __global__ __launch_bounds__(64 * WAVES) void k_gather_fwd(
     CsrDev x, CsrDev y, int has_y, const float* __restrict__ W1, const float* __restrict__ b1,
     int F, int L, float* __restrict__ A1, typename Mma<BF16>::elem* __restrict__ H1,
     typename Mma<BF16>::elem* __restrict__ H1T, int rows_pad, int ld_t, int32_t* __restrict__ keys,
     int32_t* __restrict__ row_of, int32_t* __restrict__ lkeys, int32_t* __restrict__ lrow,
     float* __restrict__ rw,
-    int32_t* __restrict__ err, int validate, float* __restrict__ gpart) {
+    int32_t* __restrict__ err, int validate, float* __restrict__ gpart, DenseFwd dn) {
+  static_assert(!DENSE || SPLIT == 1, "split rows: k_gather_finish");
   using E = typename Mma<BF16>::elem;
   __shared__ float2 part[WAVES][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -194,42 +214,61 @@ __global__ __launch_bounds__(64 * WAVES) void k_gather_fwd(
     a.y = bb.y + a.y;
     *reinterpret_cast<float2*>(A1 + (size_t)i * HID + h0) = a;
     const float r0 = fmaxf(a.x, 0.0f), r1 = fmaxf(a.y, 0.0f);
-    H1[(size_t)i * HID + h0] = (E)r0;
-    H1[(size_t)i * HID + h0 + 1] = (E)r1;
-    if constexpr (!BF16) {
-      H1T[(size_t)h0 * ld_t + i] = (E)r0;
-      H1T[(size_t)(h0 + 1) * ld_t + i] = (E)r1;
+    if constexpr (DENSE) {
+      part[0][lane] = make_float2(r0, r1);  // (wave 0 has read every part)
+    } else {
+      H1[(size_t)i * HID + h0] = (E)r0;
+      H1[(size_t)i * HID + h0 + 1] = (E)r1;
+      if constexpr (!BF16) {
+        H1T[(size_t)h0 * ld_t + i] = (E)r0;
+        H1T[(size_t)(h0 + 1) * ld_t + i] = (E)r1;
+      }
     }
+  }
+  if constexpr (DENSE) {
+    __syncthreads();
+    if (threadIdx.x < 2 * HID)
+      dense_row_store<BF16>(dn, reinterpret_cast<const float*>(part[0]), i, (int)threadIdx.x, H1, H1T, ld_t);
   }
 }
 
 // Rows split over GATHER_SPLIT workgroups: A1 = b1 + the pieces' sums in
 // piece order, then H1 (and H1^T for fp32 operands) as above.
-template <bool BF16>
-__global__ __launch_bounds__(64) void k_gather_finish(int n_rows, const float* __restrict__ gpart, int ld_t,
-                                                      const float* __restrict__ b1, float* __restrict__ A1,
-                                                      typename Mma<BF16>::elem* __restrict__ H1,
-                                                      typename Mma<BF16>::elem* __restrict__ H1T) {
+template <bool BF16, bool DENSE>
+__global__ __launch_bounds__(DENSE ? 2 * HID : 64) void k_gather_finish(
+    int n_rows, const float* __restrict__ gpart, int ld_t, const float* __restrict__ b1, float* __restrict__ A1,
+    typename Mma<BF16>::elem* __restrict__ H1, typename Mma<BF16>::elem* __restrict__ H1T, DenseFwd dn) {
   using E = typename Mma<BF16>::elem;
+  __shared__ float2 h_s[64];
   const int i = blockIdx.x, h0 = 2 * threadIdx.x;
   if (i >= n_rows) return;
-  float2 a = *reinterpret_cast<const float2*>(gpart + (size_t)i * HID + h0);
+  if (threadIdx.x < 64) {
+    float2 a = *reinterpret_cast<const float2*>(gpart + (size_t)i * HID + h0);
 #pragma unroll
-  for (int k = 1; k < GATHER_SPLIT; ++k) {
-    const float2 v = *reinterpret_cast<const float2*>(gpart + ((size_t)k * ld_t + i) * HID + h0);
-    a.x += v.x;
-    a.y += v.y;
+    for (int k = 1; k < GATHER_SPLIT; ++k) {
+      const float2 v = *reinterpret_cast<const float2*>(gpart + ((size_t)k * ld_t + i) * HID + h0);
+      a.x += v.x;
+      a.y += v.y;
+    }
+    const float2 bb = *reinterpret_cast<const float2*>(b1 + h0);
+    a.x = bb.x + a.x;
+    a.y = bb.y + a.y;
+    *reinterpret_cast<float2*>(A1 + (size_t)i * HID + h0) = a;
+    const float r0 = fmaxf(a.x, 0.0f), r1 = fmaxf(a.y, 0.0f);
+    if constexpr (DENSE) {
+      h_s[threadIdx.x] = make_float2(r0, r1);
+    } else {
+      H1[(size_t)i * HID + h0] = (E)r0;
+      H1[(size_t)i * HID + h0 + 1] = (E)r1;
+      if constexpr (!BF16) {
+        H1T[(size_t)h0 * ld_t + i] = (E)r0;
+        H1T[(size_t)(h0 + 1) * ld_t + i] = (E)r1;
+      }
+    }
   }
-  const float2 bb = *reinterpret_cast<const float2*>(b1 + h0);
-  a.x = bb.x + a.x;
-  a.y = bb.y + a.y;
-  *reinterpret_cast<float2*>(A1 + (size_t)i * HID + h0) = a;
-  const float r0 = fmaxf(a.x, 0.0f), r1 = fmaxf(a.y, 0.0f);
-  H1[(size_t)i * HID + h0] = (E)r0;
-  H1[(size_t)i * HID + h0 + 1] = (E)r1;
-  if constexpr (!BF16) {
-    H1T[(size_t)h0 * ld_t + i] = (E)r0;
-    H1T[(size_t)(h0 + 1) * ld_t + i] = (E)r1;
+  if constexpr (DENSE) {
+    __syncthreads();
+    dense_row_store<BF16>(dn, reinterpret_cast<const float*>(h_s), i, (int)threadIdx.x, H1, H1T, ld_t);
   }
 }
 
@@ -237,8 +276,9 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
                              const float* b1, int F, int L, float* A1, void* H1, void* H1T,
                              int rows_pad, int ld_t, int32_t* keys, int32_t* row_of,
                              int32_t* lkeys, int32_t* lrow, float* rw, int32_t* err, int validate,
-                             float* gpart, bool alone, hipStream_t st, hipEvent_t done) {
+                             float* gpart, bool alone, const DenseFwd* dense, hipStream_t st, hipEvent_t done) {
   CsrDev yy = y ? *y : CsrDev{0, 0, 0, nullptr, nullptr, nullptr};
+  const DenseFwd dn = dense ? *dense : DenseFwd{};
   const bool wide = alone && x.n_rows <= GATHER_WIDE_ROWS;
   const bool split = gpart && x.n_rows > 0 && (int64_t)x.nnz >= (int64_t)GATHER_LONG_ROW * x.n_rows;
   // the last launch completes `done`
@@ -247,38 +287,39 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
     const int has_y = y != nullptr;
     if (ev)
       hipExtLaunchKernelGGL(kern, grid, block, 0, st, nullptr, ev, 0, x, yy, has_y, W1, b1, F, L, A1, h1, h1t,
-                            rows_pad, ld_t, keys, row_of, lkeys, lrow, rw, err, validate, gpart);
+                            rows_pad, ld_t, keys, row_of, lkeys, lrow, rw, err, validate, gpart, dn);
     else
       hipLaunchKernelGGL(kern, grid, block, 0, st, x, yy, has_y, W1, b1, F, L, A1, h1, h1t, rows_pad, ld_t, keys,
-                         row_of, lkeys, lrow, rw, err, validate, gpart);
+                         row_of, lkeys, lrow, rw, err, validate, gpart, dn);
   };
-  auto finish = [&](auto kern, auto* h1, auto* h1t) {
+  auto finish = [&](auto kern, int threads, auto* h1, auto* h1t) {
     if (done)
-      hipExtLaunchKernelGGL(kern, dim3(x.n_rows), dim3(64), 0, st, nullptr, done, 0, x.n_rows,
-                            (const float*)gpart, ld_t, b1, A1, h1, h1t);
+      hipExtLaunchKernelGGL(kern, dim3(x.n_rows), dim3(threads), 0, st, nullptr, done, 0, x.n_rows,
+                            (const float*)gpart, ld_t, b1, A1, h1, h1t, dn);
     else
-      hipLaunchKernelGGL(kern, dim3(x.n_rows), dim3(64), 0, st, x.n_rows, (const float*)gpart, ld_t, b1, A1, h1,
-                         h1t);
+      hipLaunchKernelGGL(kern, dim3(x.n_rows), dim3(threads), 0, st, x.n_rows, (const float*)gpart, ld_t, b1, A1,
+                         h1, h1t, dn);
   };
-  if (use_bf16) {
+  auto all = [&](auto bf, auto* h1, auto* h1t) {
+    constexpr bool BF = decltype(bf)::value;
     if (split) {
-      go(k_gather_fwd<true, GATHER_SPLIT, 8>, GATHER_SPLIT, 8, (bf16*)H1, (bf16*)H1T, nullptr);
-      finish(k_gather_finish<true>, (bf16*)H1, (bf16*)H1T);
+      go(k_gather_fwd<BF, GATHER_SPLIT, 8, false>, GATHER_SPLIT, 8, h1, h1t, nullptr);
+      if (dense)
+        finish(k_gather_finish<BF, true>, 2 * HID, h1, h1t);
+      else
+        finish(k_gather_finish<BF, false>, 64, h1, h1t);
+    } else if (dense) {
+      go(k_gather_fwd<BF, 1, 8, true>, 1, 8, h1, h1t, done);
     } else if (wide) {
-      go(k_gather_fwd<true, 1, 8>, 1, 8, (bf16*)H1, (bf16*)H1T, done);
+      go(k_gather_fwd<BF, 1, 8, false>, 1, 8, h1, h1t, done);
     } else {
-      go(k_gather_fwd<true, 1, 4>, 1, 4, (bf16*)H1, (bf16*)H1T, done);
+      go(k_gather_fwd<BF, 1, 4, false>, 1, 4, h1, h1t, done);
     }
-  } else {
-    if (split) {
-      go(k_gather_fwd<false, GATHER_SPLIT, 8>, GATHER_SPLIT, 8, (float*)H1, (float*)H1T, nullptr);
-      finish(k_gather_finish<false>, (float*)H1, (float*)H1T);
-    } else if (wide) {
-      go(k_gather_fwd<false, 1, 8>, 1, 8, (float*)H1, (float*)H1T, done);
-    } else {
-      go(k_gather_fwd<false, 1, 4>, 1, 4, (float*)H1, (float*)H1T, done);
-    }
-  }
+  };
+  if (use_bf16)
+    all(std::true_type{}, (bf16*)H1, (bf16*)H1T);
+  else
+    all(std::false_type{}, (float*)H1, (float*)H1T);
   return hipGetLastError();
 }
 

@@ -35,6 +35,7 @@
 
 #include "asgd_dev.h"
 #include "asgd_kernels.h"
+#include "aux_dev.h"
 
 namespace asgd {
 
@@ -361,9 +362,13 @@ constexpr int BWP_THREADS = 64 * BWP_WAVES;
 __global__ __launch_bounds__(BWP_THREADS) void k_out_bwd_prefetch(
     float* __restrict__ W2, float* __restrict__ b2, int L, const bf16* __restrict__ H1, int B,
     const float* __restrict__ lse, const float* __restrict__ rw, const int32_t* __restrict__ lbeg,
-    const int32_t* __restrict__ lpair, float lr, float invB, float log2_invB) {
+    const int32_t* __restrict__ lpair, float lr, float invB, float log2_invB, int n_wg, JoinJob join) {
   using M = Mma<true>;
   using Fr = M::frag;
+  if ((int)blockIdx.x >= n_wg) {  // the sparse update's join (dispatched last)
+    wave_join_windows<JOIN_WINDOWS>(join, (((int)blockIdx.x - n_wg) * BWP_WAVES + (int)(threadIdx.x >> 6)) * JOIN_WINDOWS);
+    return;
+  }
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const int nrb = (B + 31) >> 5;
   const int bpad = nrb * 32;
@@ -398,7 +403,7 @@ __global__ __launch_bounds__(BWP_THREADS) void k_out_bwd_prefetch(
   const int cbase[2] = {tw_col_base(lane, 0), tw_col_base(lane, 1)};
 
   const int n_blocks = (L + 31) >> 5;
-  const int step = gridDim.x * BWP_WAVES;
+  const int step = n_wg * BWP_WAVES;
   // A block's 32 W2 rows move between HBM and the wave's staging tile whole:
   // load or store k covers rows 2k and 2k+1, 16 bytes per lane, so every
   // instruction reads or writes two full 512-byte rows.  The operand layout of
@@ -453,10 +458,7 @@ __global__ __launch_bounds__(BWP_THREADS) void k_out_bwd_prefetch(
   if (first >= n_blocks) return;
   load_blk(first, lbeg[first], lbeg[first + 1]);
   stage_loaded();
-  {
-    const int b = min(first + step, n_blocks - 1);
-    load_blk(b, lbeg[b], lbeg[b + 1]);
-  }
+  if (first + step < n_blocks) load_blk(first + step, lbeg[first + step], lbeg[first + step + 1]);
   for (int blk = first; blk < n_blocks; blk += step) {
     const int bn2 = min(blk + 2 * step, n_blocks - 1);  // the block loaded at the end of this one
     const int plo = lbeg[bn2], phi = lbeg[bn2 + 1];
@@ -694,11 +696,15 @@ template <bool BF16>
 __global__ __launch_bounds__(BWS_THREADS, BF16 ? 2 : 1) void k_out_bwd_short(
     float* __restrict__ W2, float* __restrict__ b2, int L, const typename Mma<BF16>::elem* __restrict__ H1, int B,
     const float* __restrict__ lse, const float* __restrict__ rw, const int32_t* __restrict__ lbeg,
-    const int32_t* __restrict__ lpair, float lr, float invB, float log2_invB) {
+    const int32_t* __restrict__ lpair, float lr, float invB, float log2_invB, JoinJob join) {
   using M = Mma<BF16>;
   using E = typename M::elem;
   using Fr = typename M::frag;
   constexpr int NCH = 32 / M::KC;
+  if ((int)blockIdx.x >= (L + 31) >> 5) {  // the sparse update's join (dispatched last)
+    wave_join_windows<JOIN_WINDOWS>(join, (((int)blockIdx.x - ((L + 31) >> 5)) * BWS_WAVES + (int)(threadIdx.x >> 6)) * JOIN_WINDOWS);
+    return;
+  }
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, n = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -932,10 +938,22 @@ static bool bwd_is_short(bool use_bf16, int n_blocks, int B) {
   return n_blocks <= (use_bf16 && B <= BWD_CHUNK ? 512 : 2048);
 }
 
+// (Only while all its workgroups, one per CU or two of the short kernel's, are resident
+// at once: behind a full GPU the join's would run at the end, no sooner than their own
+// launch: 132.8 against 131.7 us for the wide-feature step; mid 58.2 against 59.4.)
+bool out_bwd_takes_join(bool use_bf16, int L, int B, int n_keys, int n_cu) {
+  const int n_blocks = (L + 31) / 32, extra = join_wgs(n_keys);
+  if (bwd_is_short(use_bf16, n_blocks, B)) return n_blocks + extra <= (use_bf16 ? 2 : 1) * n_cu;
+  return use_bf16 && B <= BWD_CHUNK && (n_blocks + BWP_WAVES - 1) / BWP_WAVES + extra <= n_cu;
+}
+
 hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void* H1,
                           const void* H1T, int ld_t, int B, const float* lse, const float* rw,
-                          const int32_t* lbeg, const int32_t* lpair, float lr, int n_cu,
+                          const int32_t* lbeg, const int32_t* lpair, float lr, int n_cu, const JoinJob* join,
                           hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+  const JoinJob jj = join ? *join : JoinJob{};
+  const int n_join = jj.n_keys > 0 ? join_wgs(jj.n_keys) : 0;
+  if (n_join && !out_bwd_takes_join(use_bf16, L, B, jj.n_keys, n_cu)) return hipErrorInvalidValue;
   const int nrb = (B + 31) / 32;
   if (bwd_is_short(use_bf16, (L + 31) / 32, B)) {
     static bool attr_done[2] = {};
@@ -948,8 +966,8 @@ hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void
     const size_t lds = (use_bf16 ? bws_fixed_lds<true>() : bws_fixed_lds<false>()) + (size_t)32 * nrb * 4;
     const float inv = 1.0f / (float)B;
     auto go = [&](auto kern, auto* h1) {
-      hipExtLaunchKernelGGL(kern, dim3((L + 31) / 32), dim3(BWS_THREADS), lds, st, t0, t1, 0, W2, b2, L, h1, B, lse, rw,
-                            lbeg, lpair, lr, inv, (float)log2((double)inv));
+      hipExtLaunchKernelGGL(kern, dim3((L + 31) / 32 + n_join), dim3(BWS_THREADS), lds, st, t0, t1, 0, W2, b2, L, h1, B,
+                            lse, rw, lbeg, lpair, lr, inv, (float)log2((double)inv), jj);
       return hipGetLastError();
     };
     return use_bf16 ? go(k_out_bwd_short<true>, (const bf16*)H1) : go(k_out_bwd_short<false>, (const float*)H1);
@@ -981,8 +999,8 @@ hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void
                        (size_t)BWP_WAVES * 32 * BWP_SLD * sizeof(float);
     int gp = (n_blocks + BWP_WAVES - 1) / BWP_WAVES;
     if (gp > n_cu) gp = n_cu;
-    hipExtLaunchKernelGGL(k_out_bwd_prefetch, dim3(gp), dim3(BWP_THREADS), shp, st, t0, t1, 0, W2, b2, L,
-                          (const bf16*)H1, B, lse, rw, lbeg, lpair, lr, invB, (float)log2((double)invB));
+    hipExtLaunchKernelGGL(k_out_bwd_prefetch, dim3(gp + n_join), dim3(BWP_THREADS), shp, st, t0, t1, 0, W2, b2, L,
+                          (const bf16*)H1, B, lse, rw, lbeg, lpair, lr, invB, (float)log2((double)invB), gp, jj);
     return hipGetLastError();
   }
   if (mode == BWD_CHUNKED)

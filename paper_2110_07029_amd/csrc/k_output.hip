@@ -668,8 +668,9 @@ __device__ __forceinline__ void merge_splits(int i, int splits, const float* __r
 // against its own running maximum, then the groups are rescaled to the row's
 // maximum; thread t < HID writes hidden unit t, with tw_t the row's mean target
 // weight of that unit.  red_o [GROUPS][HID], red_s and red_m [GROUPS]: LDS.
+// Returns that value (threads t < HID).
 template <int GROUPS>
-__device__ __forceinline__ void da1_row(int i, int splits, const float* __restrict__ m_part,
+__device__ __forceinline__ float da1_row(int i, int splits, const float* __restrict__ m_part,
                                         const float* __restrict__ s_part, const float* __restrict__ o_part,
                                         int ld_part, float tw_t, const float* __restrict__ A1, float invB,
                                         float* __restrict__ dA1, float (*red_o)[HID], float* red_s, float* red_m) {
@@ -696,8 +697,11 @@ __device__ __forceinline__ void da1_row(int i, int splits, const float* __restri
       Stot = fmaf(e, red_s[k], Stot);
     }
     const float dh = (Ot / Stot - tw_t) * invB;
-    dA1[(size_t)i * HID + t] = A1[(size_t)i * HID + t] > 0.0f ? dh : 0.0f;
+    const float d = A1[(size_t)i * HID + t] > 0.0f ? dh : 0.0f;
+    dA1[(size_t)i * HID + t] = d;
+    return d;
   }
+  return 0.0f;
 }
 
 // DA: the row's dA1 as well, in the same workgroup (16 split groups), for a
@@ -709,7 +713,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
     const float* __restrict__ W2, const float* __restrict__ b2, int L,
     const typename Mma<BF16>::elem* __restrict__ H1, CsrDev y, int has_y, float* __restrict__ lse_out,
     float* __restrict__ loss_rows, float* __restrict__ tw_out, const float* __restrict__ o_part,
-    const float* __restrict__ A1, int B, float invB, float* __restrict__ dA1, SortJob sj) {
+    const float* __restrict__ A1, int B, float invB, float* __restrict__ dA1, DenseBwd dn, SortJob sj) {
   static_assert(!DA || CMB_THREADS == 32 * DA_GROUPS_WIDE, "dA1 takes the workgroup as 16 split groups");
   __shared__ float red_s[CMB_WAVES];
   __shared__ float red_m[CMB_WAVES];
@@ -815,8 +819,26 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
     __shared__ float red_o[DA_GROUPS_WIDE][HID];
     __shared__ float red_s2[DA_GROUPS_WIDE];
     __shared__ float red_m2[DA_GROUPS_WIDE];
-    da1_row<DA_GROUPS_WIDE>(i, splits, m_part, s_part, o_part, ld_part, my_tw, A1, invB, dA1, red_o, red_s2,
-                            red_m2);
+    const float d = da1_row<DA_GROUPS_WIDE>(i, splits, m_part, s_part, o_part, ld_part, my_tw, A1, invB, dA1, red_o,
+                                            red_s2, red_m2);
+    if (dn.Wh) {
+      // d is the row's dA2: the first layer's dA1 = (dA2 Wh) * [A1 > 0], 4 groups of 128
+      // threads over 32 units of the second layer each, added in group order
+      __shared__ float d2[HID];
+      if (t < HID) d2[t] = d;
+      __syncthreads();
+      const int k = t & (HID - 1), q = t / HID;
+      float acc = 0.0f;
+#pragma unroll
+      for (int o = 0; o < HID / 4; ++o)
+        acc = fmaf(d2[q * (HID / 4) + o], dn.Wh[(size_t)(q * (HID / 4) + o) * HID + k], acc);
+      red_o[q][k] = acc;  // (read by everyone before the barrier above)
+      __syncthreads();
+      if (t < HID) {
+        const float s = ((red_o[0][t] + red_o[1][t]) + red_o[2][t]) + red_o[3][t];
+        dn.dA1[(size_t)i * HID + t] = dn.A1[(size_t)i * HID + t] > 0.0f ? s : 0.0f;
+      }
+    }
   }
 }
 
@@ -837,11 +859,13 @@ __global__ __launch_bounds__(32 * GROUPS) void k_out_dA1(int splits, const float
 hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float* m_part, const float* s_part,
                                   int ld_part, const float* W2, const float* b2, int L, const void* H1,
                                   const CsrDev* y, float* lse, float* loss_rows, float* tw, const float* o_part,
-                                  const float* A1, float* dA1, const SortJob* sort, hipStream_t st,
-                                  hipEvent_t done) {
+                                  const float* A1, float* dA1, const DenseBwd* dense, const SortJob* sort,
+                                  hipStream_t st, hipEvent_t done) {
   CsrDev yy = y ? *y : CsrDev{0, 0, 0, nullptr, nullptr, nullptr};
   const bool da = y && dA1;
   const float invB = 1.0f / (float)B;
+  if (dense && !da) return hipErrorInvalidValue;
+  const DenseBwd dn = dense ? *dense : DenseBwd{};
   SortJob sj{};
   int lds = 0, n_sort = 0;
   if (sort && sort->n > 0) {
@@ -854,10 +878,10 @@ hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float*
   auto go = [&](auto kern, auto* h1) {
     if (done)
       hipExtLaunchKernelGGL(kern, grid, block, lds, st, nullptr, done, 0, splits, m_part, s_part, ld_part, W2, b2, L,
-                            h1, yy, (int)(y != nullptr), lse, loss_rows, tw, o_part, A1, B, invB, dA1, sj);
+                            h1, yy, (int)(y != nullptr), lse, loss_rows, tw, o_part, A1, B, invB, dA1, dn, sj);
     else
       hipLaunchKernelGGL(kern, grid, block, lds, st, splits, m_part, s_part, ld_part, W2, b2, L, h1, yy,
-                         y != nullptr, lse, loss_rows, tw, o_part, A1, B, invB, dA1, sj);
+                         y != nullptr, lse, loss_rows, tw, o_part, A1, B, invB, dA1, dn, sj);
   };
   if (use_bf16) {
     if (da)

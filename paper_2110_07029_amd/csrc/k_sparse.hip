@@ -11,6 +11,7 @@
 
 #include "asgd_dev.h"
 #include "asgd_kernels.h"
+#include "aux_dev.h"
 
 namespace asgd {
 
@@ -60,28 +61,40 @@ __device__ void hidden_bias_wg(int B, const float* __restrict__ dA1, float* __re
 // feature's).  A segment that lies inside the window is applied to W1 at once;
 // the piece that continues a segment from the previous window goes to
 // part[2w] and the piece that starts a segment running past the window's end
-// to part[2w + 1].  Join: the wave whose window holds the head of such a
-// segment finds how many windows it spans (one lane per window), adds their
-// continuing pieces to its own in window order and applies the sum.  The
+// to part[2w + 1].  Join (wave_join_windows): the head of such a segment finds how
+// many windows it spans (one lane per window), adds their continuing pieces to its
+// own in window order and applies the sum; on one stream these workgroups ride in
+// the backward's launch.  The
 // summation order is fixed (entry order inside a piece, window order across
 // pieces), so results do not depend on scheduling, and a long segment (a
 // feature in most rows) costs every wave at most one window of entries.  The
 // last workgroup of the first launch updates b1 and the loss.
-constexpr int SPU_WIN = 32;
 constexpr int SPU_BATCH = 16;  // entries whose dA1 and W1 rows are loaded together
 int sparse_windows(int n_keys) { return (n_keys + SPU_WIN - 1) / SPU_WIN; }
 
+// WGRAD: the first workgroups of the launch update the second hidden layer's weights
+// (they take the longest); without it the kernel keeps to 4 KB of LDS, which fits beside
+// the output-layer backward.
+template <bool WGRAD>
 __global__ __launch_bounds__(SPU_THREADS) void k_sparse_pieces(
     float* __restrict__ W1, int F, const int32_t* __restrict__ skeys, const int32_t* __restrict__ svals,
     int n_keys, const int32_t* __restrict__ row_of, CsrDev x, const float* __restrict__ dA1, float lr, int B,
     float* __restrict__ b1, const float* __restrict__ loss_rows, float* __restrict__ loss,
-    float* __restrict__ part, int n_win_blocks) {
-  if ((int)blockIdx.x == n_win_blocks) {
+    float* __restrict__ part, int n_win_blocks, DenseWgrad wg) {
+  int bid = (int)blockIdx.x;
+  if constexpr (WGRAD) {
+    if (bid < WGRAD_WGS) {
+      dense_wgrad_wg(wg, B, lr, bid);
+      return;
+    }
+    bid -= WGRAD_WGS;
+  }
+  if (bid == n_win_blocks) {
     hidden_bias_wg(B, dA1, b1, lr, loss_rows, loss);
     return;
   }
   const int lane = threadIdx.x & 63;
-  const int win = blockIdx.x * SPU_WAVES + (threadIdx.x >> 6);
+  const int win = bid * SPU_WAVES + (threadIdx.x >> 6);
   const int w0 = win * SPU_WIN;
   if (w0 >= n_keys) return;
   // lanes 0..SPU_WIN-1: the window's entries; lane SPU_WIN: the next window's first
@@ -154,73 +167,46 @@ __global__ __launch_bounds__(SPU_THREADS) void k_sparse_pieces(
   }
 }
 
-constexpr int JOIN_BATCH = 16;  // continuing pieces loaded together
+__global__ __launch_bounds__(SPU_THREADS) void k_sparse_join(JoinJob j) {
+  wave_join_windows<1>(j, blockIdx.x * SPU_WAVES + (threadIdx.x >> 6));
+}
 
-__global__ __launch_bounds__(SPU_THREADS) void k_sparse_join(float* __restrict__ W1, int F,
-                                                              const int32_t* __restrict__ skeys, int n_keys,
-                                                              float lr, const float* __restrict__ part) {
-  const int lane = threadIdx.x & 63;
-  const int win = blockIdx.x * SPU_WAVES + (threadIdx.x >> 6);
-  const int w0 = win * SPU_WIN;
-  // this window's last entry starts or continues a segment that runs past it ...
-  if (w0 + SPU_WIN >= n_keys) return;
-  const int f = skeys[w0 + SPU_WIN - 1];
-  if (f >= F || skeys[w0 + SPU_WIN] != f) return;
-  // ... and the segment's head lies in this window (else an earlier wave joins it)
-  if (skeys[w0] == f && w0 > 0 && skeys[w0 - 1] == f) return;
-  // windows win+1 .. win+m hold the rest: window v is followed by another piece
-  // when it is all f and the next window starts with f (one lane per window)
-  int m = 0;
-  for (;;) {
-    const int v1 = (win + 2 + m + lane) * SPU_WIN;  // first entry after window win+1+m+lane
-    const bool more = v1 < n_keys && skeys[v1] == f && skeys[v1 - 1] == f;
-    const uint64_t stop = __ballot(!more);
-    if (stop) {
-      m += __builtin_ctzll(stop) + 1;
-      break;
-    }
-    m += 64;
-  }
-  const float2* P = reinterpret_cast<const float2*>(part) + lane;
-  float2 acc = P[(size_t)(2 * win + 1) * (HID / 2)];
-  for (int v0 = 0; v0 < m; v0 += JOIN_BATCH) {
-    float2 c[JOIN_BATCH];
-#pragma unroll
-    for (int k = 0; k < JOIN_BATCH; ++k)
-      c[k] = P[(size_t)(2 * (win + 1 + min(v0 + k, m - 1))) * (HID / 2)];
-#pragma unroll
-    for (int k = 0; k < JOIN_BATCH; ++k)
-      if (v0 + k < m) {
-        acc.x += c[k].x;
-        acc.y += c[k].y;
-      }
-  }
-  float2* wp = reinterpret_cast<float2*>(W1 + (size_t)f * HID) + lane;
-  const float2 w = *wp;
-  *wp = make_float2(fmaf(-lr, acc.x, w.x), fmaf(-lr, acc.y, w.y));
+int join_wgs(int n_keys) {
+  const int per = SPU_WAVES * JOIN_WINDOWS;
+  return (sparse_windows(n_keys) + per - 1) / per;
 }
 
 hipError_t launch_sparse_update(float* W1, int F, const int32_t* skeys, const int32_t* svals, int n_keys,
                                 const int32_t* row_of, const CsrDev& x, const float* dA1, float lr, int B,
-                                float* b1, const float* loss_rows, float* loss, float* part, hipStream_t st,
-                                hipEvent_t done) {
+                                float* b1, const float* loss_rows, float* loss, float* part, JoinJob* join,
+                                const DenseWgrad* wgrad, hipStream_t st, hipEvent_t done) {
   const int nwin = n_keys > 0 ? sparse_windows(n_keys) : 0;
   const int nwb = (nwin + SPU_WAVES - 1) / SPU_WAVES;
+  // (one window: no segment crosses)
+  const JoinJob jj{W1, F, skeys, nwin > 1 ? n_keys : 0, lr, part};
+  const bool own_join = jj.n_keys > 0 && !join;
+  if (join) *join = jj;
+  const DenseWgrad wg = wgrad ? *wgrad : DenseWgrad{};
+  const dim3 gp(nwb + 1 + (wgrad ? WGRAD_WGS : 0)), blk(SPU_THREADS);
   // the last launch completes `done`
-  const bool join = nwin > 1;
-  const dim3 gp(nwb + 1), gj(nwb), blk(SPU_THREADS);
-  if (done && !join)
-    hipExtLaunchKernelGGL(k_sparse_pieces, gp, blk, 0, st, nullptr, done, 0, W1, F, skeys, svals, n_keys, row_of, x,
-                          dA1, lr, B, b1, loss_rows, loss, part, nwb);
-  else
-    hipLaunchKernelGGL(k_sparse_pieces, gp, blk, 0, st, W1, F, skeys, svals, n_keys, row_of, x, dA1, lr, B, b1,
-                       loss_rows, loss, part, nwb);
-  if (join) {
-    if (done)
-      hipExtLaunchKernelGGL(k_sparse_join, gj, blk, 0, st, nullptr, done, 0, W1, F, skeys, n_keys, lr,
-                            (const float*)part);
+  auto pieces = [&](auto kern) {
+    if (done && !own_join)
+      hipExtLaunchKernelGGL(kern, gp, blk, 0, st, nullptr, done, 0, W1, F, skeys, svals, n_keys, row_of, x, dA1, lr, B,
+                            b1, loss_rows, loss, part, nwb, wg);
     else
-      hipLaunchKernelGGL(k_sparse_join, gj, blk, 0, st, W1, F, skeys, n_keys, lr, (const float*)part);
+      hipLaunchKernelGGL(kern, gp, blk, 0, st, W1, F, skeys, svals, n_keys, row_of, x, dA1, lr, B, b1, loss_rows, loss,
+                         part, nwb, wg);
+  };
+  if (wgrad)
+    pieces(k_sparse_pieces<true>);
+  else
+    pieces(k_sparse_pieces<false>);
+  if (own_join) {
+    const dim3 gj(nwb);
+    if (done)
+      hipExtLaunchKernelGGL(k_sparse_join, gj, blk, 0, st, nullptr, done, 0, jj);
+    else
+      hipLaunchKernelGGL(k_sparse_join, gj, blk, 0, st, jj);
   }
   return hipGetLastError();
 }
