@@ -370,9 +370,9 @@ void timer_pair(asgd_model* m, int k, hipEvent_t* t0, hipEvent_t* t1) {
 // Gather forward (+ keys) on stream st into the next copy of H1 / H1T / rw,
 // optional validation check.  Leaves H1 / A1 ready.
 // done (optional): an event completed once the gather's work has finished on st.
-// dense_rides: the second hidden layer in the gather's own launches.
+// dense_rides: the second hidden layer in the gather's own launches.  zero: ints it clears.
 asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipStream_t st, int* rows_pad_out,
-                       hipEvent_t done = nullptr, bool dense_rides = false) {
+                       hipEvent_t done = nullptr, bool dense_rides = false, int32_t* zero = nullptr, int n_zero = 0) {
   const int B = x->n_rows;
   const int RB = out_rows_per_block(m->bf16);
   const int rows_pad = (int)round_up(B, RB);
@@ -388,7 +388,7 @@ asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipS
   TIMED_ON(m, ASGD_K_GATHER, st, launch_gather_fwd(m->bf16, xd, y ? &yd : nullptr, m->W1(), m->b1(), m->F, m->L,
                                                    m->A1, m->H1, m->H1T, rows_pad, m->rows_pad_max, m->keys,
                                                    m->row_of, m->lkeys, m->lrow, m->rw, m->err, validate ? 1 : 0,
-                                                   m->gpart, st == m->stream, dense_rides ? &dn : nullptr, st,
+                                                   m->gpart, st == m->stream, dense_rides ? &dn : nullptr, zero, n_zero, st,
                                                    m->extra && !dense_rides ? nullptr : done));
   if (m->extra && !dense_rides) {
     TIMED_ON(m, ASGD_K_DENSE_FWD, st, launch_dense_fwd(m->bf16, m->A1, m->Wh(), m->bh(), B, rows_pad, m->A2,
@@ -715,7 +715,7 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
   if (!(lr == lr)) return fail(ASGD_EINVAL, "lr is NaN");
   const int B = x->n_rows;
   int rows_pad = 0;
-  const SortPlan sort = plan_sort(m, x->nnz);
+  SortPlan sort = plan_sort(m, x->nnz);
   const LabelJob labels{m->lkeys, y->nnz, m->lrow, m->lbeg, m->lpair, m->lcnt, 0};
   CsrDev xd = dev(x);
   const bool two_streams = overlap_pays(m, B, x->nnz);
@@ -752,7 +752,9 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
     // launch), or, with stored logits, the sort and the sparse update on the
     // internal one, beside the logits and the backward.
     const bool sort_rides = !m->unfused;  // (one stream: at most 49,152 entries)
-    s = run_gather(m, x, y, m->stream, &rows_pad, one_stream ? nullptr : m->ev_fork, sort_rides && m->extra);
+    const int n_zero = sort_rides ? sort_plan_ride(&sort, lse_sort_threads(), LSE_SORT_WGS, m->hist) : 0;
+    s = run_gather(m, x, y, m->stream, &rows_pad, one_stream ? nullptr : m->ev_fork, sort_rides && m->extra, m->hist,
+                   n_zero);
     if (s) return s;
     if (!sort_rides) {
       if (!one_stream) HIP_TRY(hipStreamWaitEvent(m->aux, m->ev_fork, 0));

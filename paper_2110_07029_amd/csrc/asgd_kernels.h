@@ -41,10 +41,10 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
                              const float* b1, int F, int L, float* A1, void* H1, void* H1T,
                              int rows_pad, int ld_t, int32_t* keys, int32_t* row_of,
                              int32_t* lkeys, int32_t* lrow, float* rw, int32_t* err, int validate,
-                             float* gpart, bool alone, const DenseFwd* dense, hipStream_t st,
-                             hipEvent_t done = nullptr);
+                             float* gpart, bool alone, const DenseFwd* dense, int32_t* zero, int n_zero,
+                             hipStream_t st, hipEvent_t done = nullptr);
 // (dense, with alone only: the second hidden layer in the same launches; H1 / H1T then
-// receive its output.  done: completed by the launcher's last kernel when it has finished, with no
+// receive its output.  zero: n_zero ints to clear in the same launch.  done: completed by the launcher's last kernel when it has finished, with no
 // marker of its own on the stream)
 
 // ---- stable LSD radix sort of (key, position) -----------------------------
@@ -58,6 +58,11 @@ struct SortJob {
   int n, shift, nbits;
   int32_t *keys_out, *vals_out;
   int per_thread;  // keys per thread of a workgroup inside another launch (sort_spread)
+  // inside other launches only.  Pass 0: the counts that pass 1 starts from, per (chunk of
+  // pass 1, digit of pass 1), are added up here as the keys land; zeroed before.  Pass 1: the
+  // same counts (null: the workgroup counts the keys itself).
+  int32_t* hist;
+  int next_chunk, next_shift, next_nbits;  // pass 0: pass 1's keys per chunk and digit
 };
 // The passes of a sort of n keys < 2^key_bits, the payload being the original position:
 // one or two.  Pass 0 writes keys_a / vals_a, pass 1 keys_b / vals_b.
@@ -74,6 +79,10 @@ hipError_t launch_sort(const SortPlan& plan, int32_t* hist, hipStream_t st);
 // `wgs` workgroups of nthreads threads, whose number is returned, with sort_pass_lds bytes
 // of LDS each.
 constexpr int SORT_RIDE_MAX = (1 << 16) - 1;
+// Prepares a plan for riding: pass 1 in chunks of nthreads1 threads spread over at most wgs1
+// workgroups, its counts collected in hist (room for sort_blocks(n) << SORT_MAX_BITS);
+// returns how many of its entries have to be zero before pass 0.
+int sort_plan_ride(SortPlan* plan, int nthreads1, int wgs1, int32_t* hist);
 int sort_spread(SortJob* job, int nthreads, int wgs);
 int sort_pass_lds(int nbits, int nthreads);
 
@@ -135,6 +144,10 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
 // [B x 128] (reads W2 before the backward updates it).
 // With y and dA1 (non-null), the same launch also forms dA1 = ((O/s - tw) / B) * [A1 > 0]
 // from the partials (o_part, A1 as for launch_out_dA1); dA1 null: lse and targets only.
+// Threads of a sort workgroup in that launch, and how many of them it takes along (several
+// fit on a CU beside the rows').
+int lse_sort_threads();
+constexpr int LSE_SORT_WGS = 64;
 struct DenseBwd {
   const float *Wh, *A1;
   float* dA1;

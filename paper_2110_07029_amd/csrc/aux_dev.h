@@ -103,7 +103,9 @@ __device__ void wg_label_blocks(const int32_t* __restrict__ lkeys, int m, int L,
 // scatters them.  Every workgroup counts all the keys (LDS atomics, about one per clock
 // and CU), so this is for small batches: 18,600 keys take about as long as a short
 // output layer, beside which they cost nothing; 79,000 take several times a pass of
-// k_sort.hip.
+// k_sort.hip.  Beside the shorter per-row launch the counting decided (10.4 us for 18,600
+// keys, 6.7 without the sort), so pass 0 adds up pass 1's counts per chunk in memory as
+// its keys land, and pass 1 reads those.
 // lds: sort_pass_lds(nbits, NT) bytes, 16-byte aligned.
 template <int NT>
 __device__ void wg_sort_pass(const SortJob& j, int c, int32_t* lds) {
@@ -116,31 +118,51 @@ __device__ void wg_sort_pass(const SortJob& j, int c, int32_t* lds) {
   const int32_t* __restrict__ keys = j.keys_in;
   const int c0 = c * NT * j.per_thread;
   const int p0 = c0 + w * 64 * j.per_thread + lane;  // a wave's keys are consecutive
-  for (int d = t; d < nd; d += NT) cnt[d] = 0;
+  for (int d = t; d < nd; d += NT) cnt[d] = 0;  // (before the barrier; the counts come after it)
   for (int d = t; d < W * nd / 2; d += NT) reinterpret_cast<unsigned*>(wcnt)[d] = 0;
   __syncthreads();
-  // four keys per 16-byte load, BATCH loads in flight
-  constexpr int BATCH = 8;
-  const int n4 = n >> 2;
-  auto count = [&](int k, int q) {
-    atomicAdd(&cnt[(k >> j.shift) & mask], q < c0 ? 0x10001u : 1u);
-  };
-  for (int q0 = t; q0 < n4; q0 += NT * BATCH) {
-    int4 v[BATCH];
+  if (j.hist && j.next_chunk == 0) {
+    // pass 1: pass 0 has left the counts of every chunk
+    const int nc = (n + NT * j.per_thread - 1) / (NT * j.per_thread);
+    for (int d = t; d < nd; d += NT) {
+      unsigned tot = 0, bef = 0;
+      constexpr int BATCH = 16;  // counts in flight
+      for (int b0 = 0; b0 < nc; b0 += BATCH) {
+        int v[BATCH];
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) v[u] = reinterpret_cast<const int4*>(keys)[min(q0 + u * NT, n4 - 1)];
+        for (int u = 0; u < BATCH; ++u) v[u] = j.hist[min(b0 + u, nc - 1) * nd + d];
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
-      const int q = q0 + u * NT;
-      if (q < n4) {  // (a chunk starts at a multiple of four keys: all four lie on one side of it)
-        count(v[u].x, 4 * q);
-        count(v[u].y, 4 * q);
-        count(v[u].z, 4 * q);
-        count(v[u].w, 4 * q);
+        for (int u = 0; u < BATCH; ++u) {
+          tot += b0 + u < nc ? v[u] : 0;
+          bef += b0 + u < c ? v[u] : 0;
+        }
+      }
+      cnt[d] = tot | bef << 16;
+    }
+  } else {
+    // four keys per 16-byte load, BATCH loads in flight
+    constexpr int BATCH = 8;
+    const int n4 = n >> 2;
+    auto count = [&](int k, int q) {
+      atomicAdd(&cnt[(k >> j.shift) & mask], q < c0 ? 0x10001u : 1u);
+    };
+    for (int q0 = t; q0 < n4; q0 += NT * BATCH) {
+      int4 v[BATCH];
+  #pragma unroll
+      for (int u = 0; u < BATCH; ++u) v[u] = reinterpret_cast<const int4*>(keys)[min(q0 + u * NT, n4 - 1)];
+  #pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const int q = q0 + u * NT;
+        if (q < n4) {  // (a chunk starts at a multiple of four keys: all four lie on one side of it)
+          count(v[u].x, 4 * q);
+          count(v[u].y, 4 * q);
+          count(v[u].z, 4 * q);
+          count(v[u].w, 4 * q);
+        }
       }
     }
+    if (4 * n4 + t < n) count(keys[4 * n4 + t], 4 * n4 + t);
   }
-  if (4 * n4 + t < n) count(keys[4 * n4 + t], 4 * n4 + t);
   // lanes of the wave with the same digit
   auto peers_of = [&](int d, bool valid) {
     uint64_t peers = __ballot(valid);
@@ -194,6 +216,8 @@ __device__ void wg_sort_pass(const SortJob& j, int c, int32_t* lds) {
       const int pos = (int)cnt[d] + c + before;
       j.keys_out[pos] = key;
       j.vals_out[pos] = val;
+      if (j.next_chunk > 0)
+        atomicAdd(&j.hist[(pos / j.next_chunk << j.next_nbits) | (key >> j.next_shift & ((1 << j.next_nbits) - 1))], 1);
     }
   }
 }

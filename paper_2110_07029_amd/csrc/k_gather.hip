@@ -98,13 +98,16 @@ __global__ __launch_bounds__(64 * WAVES) void k_gather_fwd(
     typename Mma<BF16>::elem* __restrict__ H1T, int rows_pad, int ld_t, int32_t* __restrict__ keys,
     int32_t* __restrict__ row_of, int32_t* __restrict__ lkeys, int32_t* __restrict__ lrow,
     float* __restrict__ rw,
-    int32_t* __restrict__ err, int validate, float* __restrict__ gpart, DenseFwd dn) {
+    int32_t* __restrict__ err, int validate, float* __restrict__ gpart, DenseFwd dn,
+    int32_t* __restrict__ zero, int n_zero) {
   static_assert(!DENSE || SPLIT == 1, "split rows: k_gather_finish");
   using E = typename Mma<BF16>::elem;
   __shared__ float2 part[WAVES][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = (int)blockIdx.x / SPLIT, piece = (int)blockIdx.x % SPLIT;
   const int h0 = 2 * lane;
+  for (int e = (int)blockIdx.x * (64 * WAVES) + (int)threadIdx.x; e < n_zero; e += (int)gridDim.x * (64 * WAVES))
+    zero[e] = 0;
   if (i >= x.n_rows) {  // padding rows of the output-layer operands are zero
     if (wave == 0 && piece == 0) {
       H1[(size_t)i * HID + h0] = (E)0.0f;
@@ -276,7 +279,8 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
                              const float* b1, int F, int L, float* A1, void* H1, void* H1T,
                              int rows_pad, int ld_t, int32_t* keys, int32_t* row_of,
                              int32_t* lkeys, int32_t* lrow, float* rw, int32_t* err, int validate,
-                             float* gpart, bool alone, const DenseFwd* dense, hipStream_t st, hipEvent_t done) {
+                             float* gpart, bool alone, const DenseFwd* dense, int32_t* zero, int n_zero,
+                             hipStream_t st, hipEvent_t done) {
   CsrDev yy = y ? *y : CsrDev{0, 0, 0, nullptr, nullptr, nullptr};
   const DenseFwd dn = dense ? *dense : DenseFwd{};
   const bool wide = alone && x.n_rows <= GATHER_WIDE_ROWS;
@@ -287,10 +291,10 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
     const int has_y = y != nullptr;
     if (ev)
       hipExtLaunchKernelGGL(kern, grid, block, 0, st, nullptr, ev, 0, x, yy, has_y, W1, b1, F, L, A1, h1, h1t,
-                            rows_pad, ld_t, keys, row_of, lkeys, lrow, rw, err, validate, gpart, dn);
+                            rows_pad, ld_t, keys, row_of, lkeys, lrow, rw, err, validate, gpart, dn, zero, n_zero);
     else
       hipLaunchKernelGGL(kern, grid, block, 0, st, x, yy, has_y, W1, b1, F, L, A1, h1, h1t, rows_pad, ld_t, keys,
-                         row_of, lkeys, lrow, rw, err, validate, gpart, dn);
+                         row_of, lkeys, lrow, rw, err, validate, gpart, dn, zero, n_zero);
   };
   auto finish = [&](auto kern, int threads, auto* h1, auto* h1t) {
     if (done)

@@ -620,7 +620,6 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
 // ---------------------------------------------------------------------------
 constexpr int CMB_THREADS = 512;
 constexpr int CMB_WAVES = CMB_THREADS / 64;   // 8
-constexpr int LSE_SORT_WGS = 64;    // sort workgroups beside the rows' (several fit on a CU)
 constexpr int DA_GROUPS = 8;        // beside the backward: 256 threads, 4 KB of LDS
 constexpr int DA_GROUPS_WIDE = 16;  // on the model's stream, where nothing runs beside it
 
@@ -856,6 +855,8 @@ __global__ __launch_bounds__(32 * GROUPS) void k_out_dA1(int splits, const float
   da1_row<GROUPS>(i, splits, m_part, s_part, o_part, ld_part, tw_t, A1, invB, dA1, red_o, red_s, red_m);
 }
 
+int lse_sort_threads() { return CMB_THREADS; }
+
 hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float* m_part, const float* s_part,
                                   int ld_part, const float* W2, const float* b2, int L, const void* H1,
                                   const CsrDev* y, float* lse, float* loss_rows, float* tw, const float* o_part,
@@ -872,7 +873,8 @@ hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float*
     if (!da || sort->n > SORT_RIDE_MAX) return hipErrorInvalidValue;
     sj = *sort;
     lds = sort_pass_lds(sj.nbits, CMB_THREADS);
-    n_sort = sort_spread(&sj, CMB_THREADS, LSE_SORT_WGS);
+    const int chunk = CMB_THREADS * sj.per_thread;  // (spread by sort_plan_ride)
+    n_sort = (sj.n + chunk - 1) / chunk;
   }
   const dim3 grid(B + n_sort), block(CMB_THREADS);
   auto go = [&](auto kern, auto* h1) {

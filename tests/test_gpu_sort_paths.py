@@ -39,9 +39,9 @@ def dataset(F, L, B, nnz, seed):
 
 
 # F 2,000: one pass; 3,000 / 100,000 / 2^21: two passes of 6 / 9 / 11 bits.  Entries: around a
-# chunk of 512 or 1,024, at the change from one stream to two (49,152), at the 16-bit counters'
+# chunk of 512 or 1,024, where pass 0 starts to leave pass 1's counts (16,384), at the change from one stream to two (49,152), at the 16-bit counters'
 # limit and at 128 chunks
-@pytest.mark.parametrize("F,nnz", [(2_000, 511), (3_000, 512), (100_000, 513), (100_000, 1_025), (1 << 21, 18_600),
+@pytest.mark.parametrize("F,nnz", [(2_000, 511), (3_000, 512), (100_000, 513), (100_000, 1_025), (100_000, 16_383), (2_500, 16_384), (1 << 21, 18_600),
                                    (100_000, 49_152), (100_000, 49_153), (100_000, 65_537), (2_000, 131_072),
                                    (100_000, 131_073)])
 def test_touched_rows_and_w1_update(F, nnz):
