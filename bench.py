@@ -543,9 +543,13 @@ def main():
     uniq = float(np.mean([len(np.unique(ds.x.indices[ipx[bounds[j][0]]:ipx[bounds[j][1]]]))
                           for j in used[:32]]))
     # label splits of the forward (and of the unfused path's P W2): one persistent workgroup per CU
-    # but 16, shared by the 256-row blocks
+    # but 16, shared by the 256-row blocks; short splits (8 tiles at a time) by the 32-row blocks
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    splits = min((w.n_labels + 31) // 32, -(-(n_cu - 16) // -(-B // 256)))
+    n_tiles = (w.n_labels + 31) // 32
+    if not args.unfused and (B <= 64 or n_tiles * -(-B // 32) <= 32768):
+        splits = max(1, min(-(-n_tiles // 8), (n_cu - 16) // -(-B // 32)))
+    else:
+        splits = min(n_tiles, -(-(n_cu - 16) // -(-B // 256)))
     model = kernel_model(w, B, mean_nnz, mean_lnnz, uniq, splits)
     dtype = "bf16" if w.gemm_bf16 else "fp32"
     kernels = {}
@@ -562,8 +566,9 @@ def main():
         if name in OVERLAPPED:
             kernels[name]["overlapped"] = True
     # the sort and the W1 update run on the library's second stream, overlapped with
-    # the output layer (their event spans include time spent waiting for CUs), and the
-    # label grouping is a workgroup of the forward launch: none is a candidate
+    # the output layer (their event spans include time spent waiting for CUs), or inside
+    # its launches, and the label grouping is a workgroup of the forward launch: none is a
+    # candidate
     dom = max((k for k in kt if k not in OVERLAPPED), key=lambda k: kt[k][0])
     if args.workload == "wide-label":
         # the merge of the elastic configuration: 4 replicas of this model

@@ -384,7 +384,9 @@ asgd_status asgd_libsvm_read(const char* path, int32_t one_based, const asgd_lib
 /* Kernel groups that can be timed. */
 enum {
   ASGD_K_GATHER = 0,      /* first-layer gather + sort keys */
-  ASGD_K_SORT = 1,        /* radix sort of the batch's feature ids (internal stream) */
+  ASGD_K_SORT = 1,        /* radix sort of the batch's feature ids, where it has launches of its
+                             own (a step on two streams, inspection); on one stream it runs
+                             inside OUT_FWD's and OUT_COMBINE's launches */
   ASGD_K_OUT_FWD = 2,     /* output-layer forward over all labels */
   ASGD_K_OUT_COMBINE = 3, /* per-row merge of the label splits: lse, loss, target terms (and
                              dA1 too, in the same launch, when the step forms dA1 on the
@@ -392,12 +394,16 @@ enum {
   ASGD_K_HIDDEN = 4,      /* per-row dA1 from the forward's partials, when it runs on the
                              internal stream beside the backward */
   ASGD_K_OUT_BWD = 5,     /* output-layer backward + W2/b2 update */
-  ASGD_K_W1_UPDATE = 6,   /* sparse W1 gradient + update, b1 update, mean loss (internal stream) */
+  ASGD_K_W1_UPDATE = 6,   /* sparse W1 gradient + update, b1 update, mean loss (internal stream,
+                             or the model's when a step runs on one; its join of segments may
+                             then run inside OUT_BWD's launch) */
   ASGD_K_MERGE = 7,       /* normalized merge (timed on the global model) */
   ASGD_K_LABELS = 8,      /* (label, row) pairs grouped by label block: a workgroup of the
                              OUT_FWD (or LOGITS) launch, so never recorded on its own */
-  ASGD_K_DENSE_FWD = 9,   /* second hidden layer forward (extra_hidden_layers = 1) */
-  ASGD_K_DENSE_BWD = 10,  /* second hidden layer: dA1, and the Wh / bh update */
+  ASGD_K_DENSE_FWD = 9,   /* second hidden layer forward (extra_hidden_layers = 1); inside
+                             GATHER's launches when a step runs on one stream */
+  ASGD_K_DENSE_BWD = 10,  /* second hidden layer: dA1, and the Wh / bh update; inside
+                             OUT_COMBINE's and W1_UPDATE's launches on one stream */
   ASGD_K_LOGITS = 11,     /* unfused output: the logits Z written to memory */
   ASGD_K_SOFTMAX = 12,    /* unfused output: the softmax / cross-entropy pass over Z (lse, loss) */
   ASGD_K_DH = 13,         /* unfused output: dH = dZ W2 from the stored Z, and dA */

@@ -1202,9 +1202,11 @@ hipError_t launch_topk_combine(int B, int splits, int k, const double* part, int
                                hipStream_t st) {
   if (splits > 64 * TOPK_LISTS) return hipErrorInvalidValue;
   const size_t shm = (size_t)splits * k * sizeof(double);
-  const hipError_t e =
-      hipFuncSetAttribute((const void*)k_topk_combine, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (e != hipSuccess) return e;
+  if (shm > 64 * 1024) {  // (above the default limit of a launch: 256 splits of more than 32 entries)
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)k_topk_combine, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(k_topk_combine, dim3(B), dim3(64), shm, st, splits, k, part, ids, scores);
   return hipGetLastError();
 }
