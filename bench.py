@@ -39,20 +39,20 @@ FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 PMC_TRAFFIC = {
     ("wide-label", 256, "out_bwd"): dict(
         sources=('csrc/k_out_bwd.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="bd515fcc493667e9f5aed09b57095f2055fc1c03542cdaac00d2cd86aa7de0a9",
-        fetch_kib=169819.5, write_kib=337663.1),
+        sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
+        fetch_kib=169865.5, write_kib=337663.1),
     ("wide-label", 1024, "out_bwd"): dict(
         sources=('csrc/k_out_bwd.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="bd515fcc493667e9f5aed09b57095f2055fc1c03542cdaac00d2cd86aa7de0a9",
-        fetch_kib=177337.2, write_kib=337920.8),
+        sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
+        fetch_kib=177892.1, write_kib=338237.3),
     ("wide-feature", 128, "out_bwd"): dict(
         sources=('csrc/k_out_bwd.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="bd515fcc493667e9f5aed09b57095f2055fc1c03542cdaac00d2cd86aa7de0a9",
-        fetch_kib=52256.6, write_kib=103524.0),
+        sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
+        fetch_kib=52272.6, write_kib=103524.0),
     ("elastic", 4, "merge"): dict(
         sources=('csrc/k_merge.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="76e8aa214af20f11e78470a2185c4c56fa9aadc98d47c7ddc7b4e6ab63479ba6",
-        fetch_kib=1216912.0, write_kib=2028091.2),
+        sha256="c895a649d5cee7beeed44a8dd0c4fc327f1e8af60498452bbdc54a8b9c966e38",
+        fetch_kib=1216912.6, write_kib=2028091.2),
 }
 
 
