@@ -543,11 +543,13 @@ def main():
     uniq = float(np.mean([len(np.unique(ds.x.indices[ipx[bounds[j][0]]:ipx[bounds[j][1]]]))
                           for j in used[:32]]))
     # label splits of the forward (and of the unfused path's P W2): one persistent workgroup per CU
-    # but 16, shared by the 256-row blocks; short splits (8 tiles at a time) by the 32-row blocks
+    # but 16, shared by the 256-row blocks; short splits (of 8 tiles, or up to 32 of fewer) by the
+    # 32-row blocks
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     n_tiles = (w.n_labels + 31) // 32
     if not args.unfused and (B <= 64 or n_tiles * -(-B // 32) <= 32768):
-        splits = max(1, min(-(-n_tiles // 8), (n_cu - 16) // -(-B // 32)))
+        most = max(-(-n_tiles // 8), min(n_tiles, 32))
+        splits = max(1, min(most, (n_cu - 16) // -(-B // 32)))
     else:
         splits = min(n_tiles, -(-(n_cu - 16) // -(-B // 256)))
     model = kernel_model(w, B, mean_nnz, mean_lnnz, uniq, splits)

@@ -14,6 +14,8 @@
 // merges the splits' O (dH1 = (O/s - mean_{y in Y_i} W2[y]) / B,
 // dA1 = dH1 * [A1 > 0]); one launch does both when they share a stream.
 // The backward with the W2 / b2 update is in k_out_bwd.hip.
+#include <algorithm>
+
 #include <float.h>
 #include <math.h>
 
@@ -292,7 +294,8 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_train(
 // The same for short splits (k_out_fwd_short).  Workgroup = (label split, 32 rows), its 8 waves on
 // tiles of their own (t = wave, wave + 8, ... of the split): no tile is shared, so
 // nothing in the loop waits for another wave, and the waves' partials merge in LDS,
-// so a split is 8 waves' tiles long and there are few of them.  The partials are
+// so a split is 8 waves' tiles long and there are few of them (at least 32 splits
+// where there are the tiles, see fwd_plan).  The partials are
 // what a short label space pays for above: every split writes, and the per-row pass
 // reads back, 512 bytes per row, 32 MB at 240 splits and 256 rows, where W2 of
 // 30,000 labels is 15 MB.  Batches of few rows also have no padding rows here (above,
@@ -524,7 +527,14 @@ FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs) {
   const int rb = p.is_short ? 32 : out_rows_per_block(use_bf16);
   p.nrb = (B + rb - 1) / rb;
   int s = p.is_short ? wgs / p.nrb : (wgs + p.nrb - 1) / p.nrb;
-  const int most = p.is_short ? (n_tiles + FwdShape<true>::WAVES - 1) / FwdShape<true>::WAVES : n_tiles;
+  // Short: a tile for each wave, or up to 32 splits of fewer tiles.  A step of so few labels
+  // is one tile's chain per wave, and two waves of a SIMD share its matrix cores (128 fp32
+  // products of a tile: 3.4 us), so the tiles go to more CUs until the per-row pass pays for
+  // the splits.  us per step, 8 tiles per split | up to 32 splits | 60 splits:
+  //   fp32, B = 128: L = 1,000 41.7 | 37.0 | -    L = 4,000 42.3 | 39.1 | 39.3   L = 10,000 55.7 | 55.7 | 56.3
+  //   bf16, B = 128: L = 1,000 34.4 | 33.4 | -    L = 4,000 34.7 | 34.4 | 34.6   L = 10,000 37.2 | 37.2 | 37.4
+  constexpr int WAVES = FwdShape<true>::WAVES, SPREAD = 32;
+  const int most = p.is_short ? std::max((n_tiles + WAVES - 1) / WAVES, std::min(n_tiles, SPREAD)) : n_tiles;
   if (s > most) s = most;
   if (s < 1) s = 1;
   p.tps = (n_tiles + s - 1) / s;
