@@ -677,9 +677,8 @@ __device__ __forceinline__ void merge_splits(int i, int splits, const float* __r
 // against its own running maximum, then the groups are rescaled to the row's
 // maximum; thread t < HID writes hidden unit t, with tw_t the row's mean target
 // weight of that unit.  red_o [GROUPS][HID], red_s and red_m [GROUPS]: LDS.
-// Returns that value (threads t < HID).
 template <int GROUPS>
-__device__ __forceinline__ float da1_row(int i, int splits, const float* __restrict__ m_part,
+__device__ __forceinline__ void da1_row(int i, int splits, const float* __restrict__ m_part,
                                         const float* __restrict__ s_part, const float* __restrict__ o_part,
                                         int ld_part, float tw_t, const float* __restrict__ A1, float invB,
                                         float* __restrict__ dA1, float (*red_o)[HID], float* red_s, float* red_m) {
@@ -706,16 +705,19 @@ __device__ __forceinline__ float da1_row(int i, int splits, const float* __restr
       Stot = fmaf(e, red_s[k], Stot);
     }
     const float dh = (Ot / Stot - tw_t) * invB;
-    const float d = A1[(size_t)i * HID + t] > 0.0f ? dh : 0.0f;
-    dA1[(size_t)i * HID + t] = d;
-    return d;
+    dA1[(size_t)i * HID + t] = A1[(size_t)i * HID + t] > 0.0f ? dh : 0.0f;
   }
-  return 0.0f;
 }
 
 // DA: the row's dA1 as well, in the same workgroup (16 split groups), for a
 // step that runs it on the model's stream anyway: one launch instead of two;
-// the launch's workgroups past the rows then run a pass of the feature sort.
+// the launch's first workgroups then run a pass of the feature sort, which takes as
+// long as the rows do (as the last ones they started late: mid step 54.2 | 53.7 us).
+// The launch is a chain of memory round trips (label range, label ids, their W2
+// rows).  A group's first DA_PRE splits load before that chain and merge after it,
+// and the log-sum-exp comes from the groups' merge, so the partials add no round
+// trip, barrier or reduction of their own: tiny step 37.3 -> 35.9 us (mid and
+// wide-feature, where the sort's pass bounds the launch, within 0.3 us).
 template <bool BF16, bool DA>
 __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
     int splits, const float* __restrict__ m_part, const float* __restrict__ s_part, int ld_part,
@@ -728,15 +730,32 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
   __shared__ float red_m[CMB_WAVES];
   __shared__ float red_t[CMB_WAVES][HID];
   __shared__ float red_z[CMB_WAVES];
+  const int n_sort = DA ? (int)gridDim.x - B : 0;
   if constexpr (DA) {
     extern __shared__ __attribute__((aligned(16))) int32_t job_lds[];
-    if ((int)blockIdx.x >= B) {  // the feature sort's second pass
-      wg_sort_pass<CMB_THREADS>(sj, (int)blockIdx.x - B, job_lds);
+    if ((int)blockIdx.x < n_sort) {  // the feature sort's second pass: it takes longest, so first
+      wg_sort_pass<CMB_THREADS>(sj, (int)blockIdx.x, job_lds);
       return;
     }
   }
-  const int i = xcd_order((int)blockIdx.x, B), t = threadIdx.x, lane = t & 63, w = t >> 6;
-  {
+  const int i = xcd_order((int)blockIdx.x - n_sort, B), t = threadIdx.x, lane = t & 63, w = t >> 6;
+  constexpr int DA_PRE = DA ? 4 : 1;
+  const int grp = t >> 5, h4 = (t & 31) * 4;
+  float pm[DA_PRE], ps[DA_PRE], a1 = 0.0f;
+  float4 po[DA_PRE];
+  auto load_splits = [&](int k0) {  // (past the last split: the last, left out below)
+#pragma unroll
+    for (int u = 0; u < DA_PRE; ++u) {
+      const size_t r = (size_t)min(k0 + DA_GROUPS_WIDE * u, splits - 1) * ld_part + i;
+      pm[u] = m_part[r];
+      ps[u] = s_part[r];
+      po[u] = *reinterpret_cast<const float4*>(o_part + r * HID + h4);
+    }
+  };
+  if constexpr (DA) {
+    load_splits(grp);
+    a1 = A1[(size_t)i * HID + (t & (HID - 1))];
+  } else {
     float mg = -INFINITY, St = 0.0f;
     for (int k = t; k < splits; k += CMB_THREADS)
       ms_merge_ln(mg, St, m_part[(size_t)k * ld_part + i], s_part[(size_t)k * ld_part + i]);
@@ -803,12 +822,59 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
     red_t[w][2 * lane + 1] = tw1;
     if (lane == 0) red_z[w] = zw;
   }
-  __syncthreads();
-  float my_tw = 0.0f;
-  if (t < HID) {
-    float M = red_m[0], Stot = red_s[0];
+  __shared__ float red_o[DA ? DA_GROUPS_WIDE : 1][HID];
+  __shared__ float red_s2[DA_GROUPS_WIDE];
+  __shared__ float red_m2[DA_GROUPS_WIDE];
+  if constexpr (DA) {
+    // from -FLT_MAX, and a split of maximum -inf (labels of bias -inf) left out: no inf - inf
+    float mg = -FLT_MAX, St = 0.0f;
+    float4 O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int k0 = grp;;) {
 #pragma unroll
-    for (int k = 1; k < CMB_WAVES; ++k) ms_merge_ln(M, Stot, red_m[k], red_s[k]);
+      for (int u = 0; u < DA_PRE; ++u) {
+        // (opaque to the compiler, which otherwise moves the loads down here, into a branch each)
+        asm volatile("" : "+v"(pm[u]), "+v"(ps[u]), "+v"(po[u].x), "+v"(po[u].y), "+v"(po[u].z), "+v"(po[u].w));
+        const bool in = k0 + DA_GROUPS_WIDE * u < splits && pm[u] != -INFINITY;
+        const float mn = in ? fmaxf(mg, pm[u]) : mg;
+        const float a = exp_fast(mg - mn), e = exp_fast(pm[u] - mn);
+        St = in ? fmaf(e, ps[u], St * a) : St;
+        O.x = in ? fmaf(e, po[u].x, O.x * a) : O.x;
+        O.y = in ? fmaf(e, po[u].y, O.y * a) : O.y;
+        O.z = in ? fmaf(e, po[u].z, O.z * a) : O.z;
+        O.w = in ? fmaf(e, po[u].w, O.w * a) : O.w;
+        mg = mn;
+      }
+      k0 += DA_GROUPS_WIDE * DA_PRE;
+      if (k0 >= splits) break;
+      load_splits(k0);
+    }
+    asm volatile("" : "+v"(a1));
+    *reinterpret_cast<float4*>(&red_o[grp][h4]) = O;
+    if ((t & 31) == 0) {
+      red_s2[grp] = St;
+      red_m2[grp] = mg;
+    }
+  }
+  __syncthreads();
+  float my_d = 0.0f;
+  if (t < HID) {
+    float M, Stot, Ot = 0.0f;
+    if constexpr (DA) {
+      M = red_m2[0];
+#pragma unroll
+      for (int k = 1; k < DA_GROUPS_WIDE; ++k) M = fmaxf(M, red_m2[k]);
+      Stot = 0.0f;
+#pragma unroll
+      for (int k = 0; k < DA_GROUPS_WIDE; ++k) {
+        const float e = exp_fast(red_m2[k] - M);
+        Ot = fmaf(e, red_o[k][t], Ot);
+        Stot = fmaf(e, red_s2[k], Stot);
+      }
+    } else {
+      M = red_m[0], Stot = red_s[0];
+#pragma unroll
+      for (int k = 1; k < CMB_WAVES; ++k) ms_merge_ln(M, Stot, red_m[k], red_s[k]);
+    }
     const float lse = M + logf(Stot);
     if (t == 0) lse_out[i] = lse;
     if (has_y) {
@@ -820,21 +886,19 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
       }
       const float inv_cnt = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
       tw_out[(size_t)i * HID + t] = tw * inv_cnt;
-      my_tw = tw * inv_cnt;
+      if constexpr (DA) {
+        my_d = a1 > 0.0f ? (Ot / Stot - tw * inv_cnt) * invB : 0.0f;
+        dA1[(size_t)i * HID + t] = my_d;
+      }
       if (t == 0) loss_rows[i] = lse - zs * inv_cnt;
     }
   }
   if constexpr (DA) {
-    __shared__ float red_o[DA_GROUPS_WIDE][HID];
-    __shared__ float red_s2[DA_GROUPS_WIDE];
-    __shared__ float red_m2[DA_GROUPS_WIDE];
-    const float d = da1_row<DA_GROUPS_WIDE>(i, splits, m_part, s_part, o_part, ld_part, my_tw, A1, invB, dA1, red_o,
-                                            red_s2, red_m2);
     if (dn.Wh) {
-      // d is the row's dA2: the first layer's dA1 = (dA2 Wh) * [A1 > 0], 4 groups of 128
+      // my_d is the row's dA2: the first layer's dA1 = (dA2 Wh) * [A1 > 0], 4 groups of 128
       // threads over 32 units of the second layer each, added in group order
       __shared__ float d2[HID];
-      if (t < HID) d2[t] = d;
+      if (t < HID) d2[t] = my_d;
       __syncthreads();
       const int k = t & (HID - 1), q = t / HID;
       float acc = 0.0f;

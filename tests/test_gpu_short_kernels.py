@@ -17,10 +17,12 @@ pytestmark = pytest.mark.gpu
 # forward: short up to 64 rows or 32,768 (tile, 32-row block) products; backward: up to 512
 # label blocks at 256 rows or less with bf16 operands, else 2,048.  L = 7, 32, 33: less than
 # a tile, a tile and one more; 16,385 and 65,537: one label past the backward's lines.
-# Splits of one tile each up to 1,024 labels, of eight from 8,192 on
+# Splits of one tile each up to 1,024 labels, of eight from 8,192 on; 65 and
+# 129 splits at 16,640 and 33,000 (the per-row pass takes 64 at a time)
 @pytest.mark.parametrize("B,L", [(1, 7), (1, 33), (33, 32), (64, 257), (65, 1_000), (256, 16_384), (255, 16_385),
                                  (257, 1_000), (300, 65_536), (257, 65_537), (1_000, 2_001),
-                                 (128, 1_024), (128, 1_025), (40, 8_192), (40, 8_193)])
+                                 (128, 1_024), (128, 1_025), (40, 8_192), (40, 8_193),
+                                 (16, 16_640), (20, 33_000)])
 @pytest.mark.parametrize("bf16", [True, False])
 def test_step_parity(B, L, bf16):
     if not bf16 and B * L > 5_000_000:
