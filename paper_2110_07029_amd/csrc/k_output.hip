@@ -142,7 +142,9 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_train(
     return z;
   };
 
-  float m_run = -INFINITY, s_run = 0.0f;
+  // (from -FLT_MAX and not -inf: on a tile of nothing but labels of bias -inf, which leaves
+  // the reference where it is, -inf would make each numerator 2^(-inf + inf))
+  float m_run = -FLT_MAX, s_run = 0.0f;
   f32x16 acc_o[4];
 #pragma unroll
   for (int hb = 0; hb < 4; ++hb)
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_train(
         zn = M::mma(BF16 ? za[kb][c % PRE] : tile_frag_w<BF16>(wr[b1], rbase, n, kb, c, g), hf[kb][c], zn);
     // The tile's maximum is only formed when some lane's numerators sum past
     // 2^LAZY (or are not finite, as on a row's first tile, whose reference is
-    // -inf): no numerator exceeds its lane's sum, so every other tile keeps
+    // -FLT_MAX): no numerator exceeds its lane's sum, so every other tile keeps
     // p <= 2^LAZY against the current reference.
     float p[16];
 #pragma unroll
@@ -384,7 +386,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_short(
 #pragma unroll
     for (int c = 0; c < NCH; ++c) hf[kb][c] = h1_frag<BF16>(hrow, kb, c, g);
 
-  float m_run = -INFINITY, s_run = 0.0f;
+  float m_run = -FLT_MAX, s_run = 0.0f;  // as in k_out_fwd_train
   f32x16 acc_o[4];
 #pragma unroll
   for (int hb = 0; hb < 4; ++hb)
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_out_fwd_short(
   }
 
   // Merge: every wave rescales to the rows' common maximum (a wave without a tile
-  // holds m = -inf and contributes zeros), then the sums are added in wave order.
+  // holds m = -FLT_MAX and contributes zeros), then the sums are added in wave order.
   const float stot = s_run + __shfl_xor(s_run, 32);
   if (g == 0) red_m[wave * 32 + n] = m_run;
   __syncthreads();  // (and every wave is done with its tile)
@@ -658,7 +660,7 @@ __device__ __forceinline__ void merge_splits(int i, int splits, const float* __r
     const float ss = s_part[r];
     float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if constexpr (WITH_O) o = *reinterpret_cast<const float4*>(o_part + r * HID + h4);
-    // (no split has -inf: each holds at least one label of finite bias)
+    // (no split has -inf: one of nothing but labels of bias -inf holds -FLT_MAX ln 2 and s = 0)
     const float mn = fmaxf(mg, ms);
     const float a = exp_fast(mg - mn), e = exp_fast(ms - mn);
     St = fmaf(e, ss, St * a);
@@ -826,7 +828,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
   __shared__ float red_s2[DA_GROUPS_WIDE];
   __shared__ float red_m2[DA_GROUPS_WIDE];
   if constexpr (DA) {
-    // from -FLT_MAX, and a split of maximum -inf (labels of bias -inf) left out: no inf - inf
+    // from -FLT_MAX, and no split holds -inf (see merge_splits): no inf - inf
     float mg = -FLT_MAX, St = 0.0f;
     float4 O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int k0 = grp;;) {
@@ -834,7 +836,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
       for (int u = 0; u < DA_PRE; ++u) {
         // (opaque to the compiler, which otherwise moves the loads down here, into a branch each)
         asm volatile("" : "+v"(pm[u]), "+v"(ps[u]), "+v"(po[u].x), "+v"(po[u].y), "+v"(po[u].z), "+v"(po[u].w));
-        const bool in = k0 + DA_GROUPS_WIDE * u < splits && pm[u] != -INFINITY;
+        const bool in = k0 + DA_GROUPS_WIDE * u < splits;
         const float mn = in ? fmaxf(mg, pm[u]) : mg;
         const float a = exp_fast(mg - mn), e = exp_fast(pm[u] - mn);
         St = in ? fmaf(e, ps[u], St * a) : St;

@@ -10,7 +10,7 @@ import paper_2110_07029_amd as asgd
 from oracle import model as om
 from paper_2110_07029_amd import synth
 
-from gpu_util import Setup, flush, write_params
+from gpu_util import RTOL_BF16, RTOL_FP32, Setup, assert_update_close, flush, step_magnitudes, write_params
 
 pytestmark = pytest.mark.gpu
 
@@ -72,5 +72,47 @@ def test_one_label_far_above_the_rest(label, bf16):
         got = asgd.asgd_model_get_params(s.m, asgd.ASGD_PARAM_B1, (H,)).astype(np.float64)
         d, dr = got - p["b1"], ref["b1"].astype(np.float64) - p["b1"]
         assert np.linalg.norm(d - dr) <= 2e-2 * np.linalg.norm(dr)
+    finally:
+        s.free()
+
+
+# forwards: waves on tiles of their own (one tile each; several), workgroups on shared tiles (one
+# stream; two, by the batch's entries)
+@pytest.mark.parametrize("B,L,nnz,bf16", [(64, 2_999, 20, True), (33, 2_999, 20, False), (256, 30_000, 20, True),
+                                          (40, 33_000, 20, False), (1_000, 33_600, 20, True), (1_000, 33_600, 50, True),
+                                          (1_000, 33_600, 20, False)])
+def test_labels_masked_by_infinite_biases(B, L, nnz, bf16):
+    """Labels of bias -inf (a label space with ids out of use) have probability zero: whole tiles of
+    them, at any place of a wavefront's or a split's tiles, whole splits, and single ones.  They stay
+    as they are, and the others step as if the masked ones were not there."""
+    flush(f"masked labels: B={B} L={L} nnz={nnz} bf16={bf16}")
+    r = np.random.default_rng(21)
+    tiles = np.arange((L + 31) // 32)
+    masked = np.isin(tiles % 11, (0, 4)) | ((tiles >= 40) & (tiles < 75)) | (tiles == tiles[-1])
+    mask = np.repeat(masked, 32)[:L] | (r.random(L) < 0.1)
+    F = 4_000
+    ind = np.sort(np.argsort(r.random((B, F)), axis=1)[:, :nnz], axis=1).astype(np.int32)
+    x = synth.CSR(np.arange(B + 1, dtype=np.int64) * nnz, ind.ravel(),
+                  r.uniform(0.1, 0.5, B * nnz).astype(np.float32), F)
+    y = synth.CSR(np.arange(B + 1, dtype=np.int64), r.choice(np.flatnonzero(~mask), B).astype(np.int32), None, L)
+    wl = synth.Workload("masked", F, L, B, B, 0.5, True, "", 0, 0, 0, 1.05, "", "", 0, None, 7)
+    s = Setup(wl, B, B, bf16=bf16, ds=synth.Dataset(wl, x, y))
+    try:
+        p = trained_scale(F, L, 9)
+        p["b2"][mask] = -np.inf
+        write_params(s.m, p)
+        loss = asgd.asgd_train_step(s.m, s.xb(0, B), s.yb(0, B), 0.5, want_loss=True)
+        ref, ref_loss, g, fw = om.train_step(p, x, y, 0.5, "fp32")
+        assert abs(loss - ref_loss) <= 2e-3 * max(1.0, abs(ref_loss)), (loss, ref_loss)
+        got = s.params()
+        assert np.all(np.isneginf(got["b2"][mask]))
+        assert np.array_equal(got["W2"][mask].view(np.uint32), p["W2"][mask].view(np.uint32))
+        mag = step_magnitudes(p, x, y, g, fw, 0.5)
+        rtol = RTOL_BF16 if bf16 else RTOL_FP32
+        for k in ("W2", "b2"):
+            assert_update_close(k, p[k][~mask], got[k][~mask], ref[k][~mask], rtol, mag[k][~mask])
+        assert_update_close("b1", p["b1"], got["b1"], ref["b1"], rtol, mag["b1"])
+        t = g["touched"]
+        assert_update_close("W1", p["W1"][t], got["W1"][t], ref["W1"][t], rtol, mag["W1"])
     finally:
         s.free()
