@@ -173,6 +173,8 @@ asgd_status asgd_model_last_loss(asgd_model* m, float* loss_out);
 
 /* Top-k labels per row of x by logit Z (ties: smaller label id first), the
  * prediction used for the paper's top-1 accuracy (Sec. 5.1 "Methodology").
+ * NaN logits are not ranked: where a row has fewer than k others, the places left
+ * hold id 2^31 - 1 and score -inf.
  * ids_dev: device int32 [B x k]; scores_dev: device float [B x k] or NULL.
  * 1 <= k <= 32 and k <= L; B up to max_batch (16384 at most).  Asynchronous. */
 asgd_status asgd_predict_topk(asgd_model* m, const asgd_csr* x, int32_t k, int32_t* ids_dev,

@@ -1008,6 +1008,7 @@ hipError_t launch_out_dA1(int B, int splits, const float* m_part, const float* s
 constexpr int TOPK_REG_K = 8;  // longer lists: 32 entries, 32 rows per wave
 constexpr double TOPK_INF = 0x1p128, TOPK_EMPTY = -0x1p200, TOPK_FENCE = 0x1p300;
 constexpr unsigned TOPK_ID_MASK = (1u << 22) - 1;
+constexpr int TOPK_NONE = 0x7fffffff;  // the id where a row has fewer than k ranked labels (NaN logits are not)
 
 __device__ __forceinline__ double max_key(double a, double b) {
   double d;
@@ -1268,7 +1269,7 @@ __global__ __launch_bounds__(64) void k_topk_combine(int splits, int k, const do
     for (int j = 0; j < TOPK_LISTS; ++j)
       if (!none && head[j] == best) head[j] = ++pos[j] < k ? ck[(lane + 64 * j) * k + pos[j]] : TOPK_EMPTY;
     if (lane == 0) {
-      ids[(size_t)i * k + out] = none ? -1 : topk_id(best);
+      ids[(size_t)i * k + out] = none ? TOPK_NONE : topk_id(best);
       if (scores) scores[(size_t)i * k + out] = none ? -INFINITY : topk_score(best);
     }
   }

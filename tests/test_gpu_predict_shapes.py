@@ -63,3 +63,28 @@ def test_few_labels_and_extreme_biases(L):
         check(s, 300, min(L, 4))
     finally:
         s.free()
+
+
+@pytest.mark.parametrize("rows,k", [(40, 1), (40, 5), (300, 8), (300, 12)])
+def test_rows_with_fewer_ranked_labels_than_k(rows, k):
+    """NaN logits are never ranked: the places of a row without a ranked label hold id 2^31 - 1 and
+    score -inf."""
+    import torch
+    flush(f"predict few ranked labels: rows={rows} k={k}")
+    s = Setup(workload(2_987), 300, 300)
+    try:
+        p = trained_scale(s.F, s.L, 4)
+        p["b2"][:] = np.nan
+        ranked = [7, 1_000, 2_986][:k - 1]
+        p["b2"][ranked] = 0.0
+        write_params(s.m, p)
+        ids = torch.empty((rows, k), dtype=torch.int32, device="cuda")
+        sc = torch.empty((rows, k), dtype=torch.float32, device="cuda")
+        asgd.asgd_predict_topk(s.m, s.xb(0, rows), k, ids, sc)
+        ids, sc = ids.cpu().numpy(), sc.cpu().numpy()
+        n = len(ranked)
+        assert np.array_equal(np.sort(ids[:, :n], axis=1), np.tile(np.array(ranked, np.int32), (rows, 1)))
+        assert np.all(np.isfinite(sc[:, :n])) and np.all(np.isneginf(sc[:, n:]))
+        assert np.all(ids[:, n:] == 2 ** 31 - 1)
+    finally:
+        s.free()
