@@ -415,17 +415,27 @@ asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipS
 // Whether a training step puts the first layer's work (gather, sort, dA1, sparse
 // update) on the internal stream, beside the output layer.  That hides it, but each
 // pair of streams' event and wait costs 10-13 us of host time and a gap of 5-8 us on
-// the GPU, so it pays only beside a long output layer or when the first layer's own
-// work is long.  Measured, us per step, one stream | two, at 75 entries per row:
-//   L = 30,000,  B = 256:  74 | 78     L = 120,000, B = 256: 106 | 104
-//   L = 205,443, B = 128: 133 | 145    L = 250,000, B = 256: 157 | 147
-//   L = 670,091, B = 256: 296 | 270    L = 670,091, B = 1024: 880 | 803
-//   L = 10,000,  B = 1024 (77,000 entries): 188 | 123; L = 60,000: 211 | 163
+// the GPU, and on one stream the sort runs inside the output layer's launches, so it
+// pays only beside a long output layer or when the first layer's own work is long.
+// Measured, us per step, one stream | two, at 75 entries per row:
+//   L = 60,000,  B = 256:  68 | 85     L = 120,000, B = 256: 93 | 97
+//   L = 205,443, B = 128:  93 | 97     L = 250,000, B = 256: 127 | 127
+//   L = 300,000, B = 128: 124 | 137    L = 40,000, B = 1024 (38,000 entries): 110 | 104
+// (the 70 us line is where the two met before the one-stream launches were shortened; at
+// few rows one stream now leads beyond it.)  The entries' line is the room of the sort's
+// counters: B = 256, L = 30,000 with 58,000 entries 79 | 90, B = 1024, L = 40,000 with
+// 60,000 114 | 111.
+// Stored logits: none of their launches takes the sort along, so on one stream it stands
+// alone: two streams from 3 us of one pass's estimate on.
+//   L = 1,000,  B = 128 (fp32): 82 | 97     L = 3,000,  B = 256: 95 | 98
+//   L = 5,000,  B = 600: 114 | 104          L = 12,000, B = 256: 106 | 101
+//   L = 30,000, B = 256: 123 | 116          L = 30,000, B = 64: 100 | 100
+//   L = 45,000, B = 256: 145 | 128          L = 100,000, B = 64: 135 | 127
 bool overlap_pays(const asgd_model* m, int B, int nnz) {
   // forward and backward of the output layer: per label 0.2 ns of memory traffic and
-  // 0.87 ns per 1,000 rows of products; the stored-logits path takes about three times that
-  const double out_us = (double)m->L * (2e-4 + 8.7e-7 * B) * (m->unfused ? 3.0 : 1.0);
-  return out_us >= 70.0 || nnz > 49152;  // (below SORT_RIDE_MAX)
+  // 0.87 ns per 1,000 rows of products
+  const double out_us = (double)m->L * (2e-4 + 8.7e-7 * B);
+  return out_us >= (m->unfused ? 3.0 : 70.0) || nnz > 49152;  // (below SORT_RIDE_MAX)
 }
 
 SortPlan plan_sort(asgd_model* m, int n_keys) {

@@ -13,7 +13,9 @@ from oracle import model as om
 from paper_2110_07029_amd import synth
 
 from gpu_util import (RTOL_BF16, RTOL_FP32, Setup, a1_bound, assert_rel_close, assert_update_close, flush,
-                      h1_flip_logit_bound, step_magnitudes)
+                      h1_flip_logit_bound, step_magnitudes, write_params)
+from test_gpu_sort_paths import dataset
+from test_gpu_trained_scale import trained_scale
 
 pytestmark = pytest.mark.gpu
 
@@ -178,3 +180,67 @@ def test_variant_arguments_are_checked():
             asgd.asgd_model_get_params(m, asgd.ASGD_PARAM_WH, (128, 128))
     finally:
         asgd.asgd_model_free(m)
+
+
+def _trained(F, L, extra, seed):
+    p = trained_scale(F, L, seed)
+    if extra:
+        r = np.random.default_rng(seed + 1)
+        p["Wh"] = (r.standard_normal((128, 128)) * 0.12).astype(np.float32)
+        p["bh"] = (r.standard_normal(128) * 0.1).astype(np.float32)
+    return p
+
+
+# O = P W2 loads Z and W2 two tiles ahead: five tiles per split; six, and one in the last split;
+# six, and five in the last (600 rows: three row blocks).  All of these run on two streams.
+@pytest.mark.parametrize("B,L,bf16", [(256, 38_400, True), (256, 39_000, True), (600, 12_801, True),
+                                      (600, 12_801, False), (250, 38_390, False)])
+def test_unfused_step_parity_with_many_tiles_per_split(B, L, bf16):
+    flush(f"unfused step, many tiles per split: B={B} L={L} bf16={bf16}")
+    wl, ds = dataset(5_000, L, B, 20 * B, 13)
+    s = Setup(wl, B, B, bf16=bf16, ds=ds, flags=asgd.ASGD_UNFUSED_OUTPUT)
+    try:
+        write_params(s.m, _trained(s.F, L, False, 14))
+        _step_parity(s, 0, B, 0.5, RTOL_BF16 if bf16 else RTOL_FP32)
+    finally:
+        s.free()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_unfused_steps_alternate_between_one_stream_and_two(bf16):
+    """Stored logits with 13,001 labels: batches of 600 rows put the sort and the sparse update on
+    the internal stream, batches of 20 rows do not; issued back to back, the model follows the
+    oracle's sequence."""
+    flush(f"unfused steps on one stream and two: bf16={bf16}")
+    _sequence(13_001, bf16, 0, asgd.ASGD_UNFUSED_OUTPUT, 60_000,
+              [(0, 600), (600, 620), (620, 1_220), (1_220, 1_820), (0, 20), (20, 40), (40, 640)])
+
+
+def _sequence(L, bf16, extra, flags, nnz, bounds):
+    import torch
+    rows = max(r1 for _, r1 in bounds)
+    wl, ds = dataset(20_000, L, rows, nnz, 15)
+    s = Setup(wl, rows, max(r1 - r0 for r0, r1 in bounds), bf16=bf16, ds=ds, flags=flags, extra=extra)
+    try:
+        init = _trained(s.F, L, extra, 16)
+        write_params(s.m, init)
+        p = init
+        for r0, r1 in bounds:
+            asgd.asgd_train_step(s.m, s.xb(r0, r1), s.yb(r0, r1), 0.1)
+        mag = {k: np.zeros(v.shape) for k, v in init.items()}
+        for r0, r1 in bounds:
+            x, y = s.host_batch(r0, r1)
+            q, _, g, fw = om.train_step(p, x, y, 0.1, "fp32")
+            for k, m in step_magnitudes(p, x, y, g, fw, 0.1).items():
+                mag[k][g["touched"] if k == "W1" else slice(None)] += m
+            p = q
+        torch.cuda.synchronize()
+        got = s.params()
+        # Each step's update is within rtol (|update| + its magnitude), so their sum is within rtol
+        # times the sum of both; an error carried into the next steps enters their updates times lr
+        # and a second derivative, of second order here.  fp32: the weights' rounding in each of
+        # the steps adds up, 1e-3 as for other sequences of steps.
+        for k in init:
+            assert_update_close(k, init[k], got[k], p[k], RTOL_BF16 if bf16 else 1e-3, mag=mag[k])
+    finally:
+        s.free()
