@@ -31,6 +31,8 @@
 #include <hip/hip_ext.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include <type_traits>
 
 #include "asgd_dev.h"
@@ -929,13 +931,23 @@ static hipError_t launch_bwd(int grid, size_t shm, hipStream_t st, hipEvent_t t0
 // Where the backward runs k_out_bwd_short: while its workgroups (one per label block)
 // are one round of the GPU beside the kernel of B <= 256, whose waves each own a block
 // and its next one's loads, and a few rounds beside the others.  Measured, us with it | without:
-//   bf16: L = 10,000, B = 256: 10.8 | 13.4     L = 30,000, B = 256: 17.8 | 15.1
-//         L = 10,000, B = 1000: 18.8 | 63.6    L = 30,000, B = 600: 24.0 | 41.0
-//         L = 60,000, B = 600: 40.0 | 41.5     L = 120,000, B = 900: 97.0 | 95.1
-//   fp32: L = 1,000, B = 128: 10.4 | 18.7      L = 30,000, B = 200: 53.3 | 72.0
-//         L = 200,000, B = 128: 191.8 | 177.8
+//   bf16: L = 10,000, B = 256: 11.7 | 13.2     L = 20,000, B = 256: 16.3 | 14.3
+//         L = 16,000, B = 1024: 20.7 | 65.7    L = 48,000, B = 300: 25.6 | 26.2
+//         L = 65,000, B = 300: 31.3 | 27.2     L = 65,000, B = 1024: 60.8 | 67.2
+//         L = 65,000, B = 2048: 102 | 146      L = 80,000, B = 1500: 96.4 | 155
+// fp32: its workgroups are one per CU, so the time goes by rounds of 256 blocks, each as long
+// as the rows of one wave; the other kernel takes one round up to 2,048 blocks, as long as the
+// whole batch's rows.  So the fewer rows, the sooner it is the shorter one:
+//         L = 20,000, B = 16: 27.3 | 21.3      L = 20,000, B = 64: 27.2 | 30.5
+//         L = 30,000, B = 64: 35.6 | 29.5      L = 30,000, B = 128: 38.7 | 46.4
+//         L = 42,000, B = 128: 50.2 | 46.5     L = 48,000, B = 256: 78.7 | 81.9
+//         L = 56,000, B = 256: 91.3 | 83.2     L = 48,000, B = 400: 128 | 130
+//         L = 56,000, B = 400: 149 | 129       L = 56,000, B = 512: 151 | 156
+//         L = 65,000, B = 512: 173 | 158       L = 65,000, B = 1024: 312 | 319
+//         L = 65,000, B = 2048: 586 | 635
 static bool bwd_is_short(bool use_bf16, int n_blocks, int B) {
-  return n_blocks <= (use_bf16 && B <= BWD_CHUNK ? 512 : 2048);
+  if (use_bf16) return n_blocks <= (B <= BWD_CHUNK ? 512 : 2048);
+  return n_blocks <= (B > 512 ? 2048 : std::min(1536, 512 + 4 * B));
 }
 
 // (Only while all its workgroups, one per CU or two of the short kernel's, are resident

@@ -28,6 +28,10 @@ def test_step_parity(B, L, bf16):
     if not bf16 and B * L > 5_000_000:
         pytest.skip("the oracle's time")
     flush(f"short kernels: B={B} L={L} bf16={bf16}")
+    step_parity(B, L, bf16)
+
+
+def step_parity(B, L, bf16):
     w = synth.Workload("short", 3_000, L, B, B, 0.5, True, "lognormal", 2.5, 0.6, 100, 1.05, "uniform", "poisson",
                        2.0, 1.1, 2)
     s = Setup(w, B, B, bf16=bf16)
@@ -47,3 +51,18 @@ def test_step_parity(B, L, bf16):
         assert_update_close("W1", p["W1"][t], got["W1"][t], ref["W1"][t], rtol, mag["W1"])
     finally:
         s.free()
+
+
+def bwd_line(B):
+    """Label blocks up to which the fp32 backward gives every block a workgroup."""
+    return 2_048 if B > 512 else min(1_536, 512 + 4 * B)
+
+
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("B", [1, 40, 128, 300, 513])
+def test_step_parity_at_the_line_of_the_fp32_backward(B, past):
+    """The last label count of the backward with a workgroup per label block, and one label more:
+    the backward whose wavefronts own blocks and read H1 from global memory."""
+    L = 32 * bwd_line(B) + past
+    flush(f"fp32 backward's line: B={B} L={L}")
+    step_parity(B, L, False)
