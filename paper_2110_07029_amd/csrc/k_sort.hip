@@ -11,9 +11,12 @@
 //             the chunk from 64-lane ballots (lanes with the same digit in one wave),
 //             per-wave running counts, then a prefix over the four waves; keys land
 //             at offset + rank.
-// Summing in the scatter reads (chunks)^2 rows of counts, so above SORT_SELF_SCAN
-// chunks a launch of its own (scan, one workgroup) forms the offsets.  Up to there it
-// was the longest of the three: 14.7 us of 35 us per pass for 79,000 keys of 18 bits.
+// Summing in the scatter reads (chunks)^2 rows of counts, which beside the output layer's
+// launches, on the few CUs and registers these leave, costs more than it saves from 48 chunks
+// on: above SORT_SELF_SCAN chunks a launch of its own (scan, one workgroup) forms the offsets.
+// us per step with the sort the longest chain, summing in the scatter | in a launch: 61,000
+// keys 151 | 134, 79,000 172 | 145, 120,000 186 | 142; 46,000 keys (45 chunks) 109.0 | 110.1
+// and 139 | 132, 28,000 113 | 121 and 120 | 115.
 // hist and scatter size their LDS by the pass's digit width (dynamic LDS, 4 << bits
 // and 12 << bits bytes), not by the widest digit: a narrow pass then fits on a CU
 // beside the output-layer kernels of the other stream.
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_sort_scan(const int32_t* __res
   }
 }
 
-constexpr int SORT_SELF_SCAN = 128;
+constexpr int SORT_SELF_SCAN = 48;
 
 // offs: the scan's offsets, or null: this workgroup forms its own from hist.
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(SortJob j, int nblk, const int32_t* __restrict__ hist,
