@@ -33,6 +33,9 @@ hipError_t launch_fill_int(int32_t* p, int32_t v, int64_t n, hipStream_t st);
 // floats for their partial sums (ld_t >= rows_pad).  alone: nothing runs beside it.
 constexpr int GATHER_SPLIT = 4;
 constexpr int GATHER_LONG_ROW = 160;
+inline bool gather_splits_rows(int n_rows, int nnz) {
+  return n_rows > 0 && (int64_t)nnz >= (int64_t)GATHER_LONG_ROW * n_rows;
+}
 struct DenseFwd {
   const float *Wh, *bh;
   float* A2;
@@ -50,6 +53,7 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
 // ---- stable LSD radix sort of (key, position) -----------------------------
 constexpr int SORT_CHUNK = 1024;   // keys per workgroup
 constexpr int SORT_MAX_BITS = 11;  // digit width limit per pass
+constexpr int SORT_SCAN_CHUNKS = 48;  // chunks from which the scatter's offsets have a launch of their own
 int sort_blocks(int n);
 // One pass over the digit (key >> shift) & (2^nbits - 1): keys_in / vals_in (null: the
 // positions) to keys_out / vals_out.
@@ -129,10 +133,11 @@ int out_rows_per_block(bool use_bf16);
 // label_job_plan).
 // Its launch shape: nrb row blocks x `splits` label splits of tps tiles each; is_short: 32
 // rows per row block and waves on tiles of their own (k_out_fwd_short).  wgs: workgroups wanted.
+// sort_beside: launches of the feature sort run beside it, and the step waits for them.
 struct FwdPlan {
   int is_short, nrb, splits, tps;
 };
-FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs);
+FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs, bool sort_beside);
 hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
                                 int B, const FwdPlan& shape, float* m_part, float* s_part, float* o_part,
                                 int ld_part, const LabelJob* job, const LabelJobPlan* plan, const SortJob* sort,

@@ -284,7 +284,7 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
   CsrDev yy = y ? *y : CsrDev{0, 0, 0, nullptr, nullptr, nullptr};
   const DenseFwd dn = dense ? *dense : DenseFwd{};
   const bool wide = alone && x.n_rows <= GATHER_WIDE_ROWS;
-  const bool split = gpart && x.n_rows > 0 && (int64_t)x.nnz >= (int64_t)GATHER_LONG_ROW * x.n_rows;
+  const bool split = gpart && gather_splits_rows(x.n_rows, x.nnz);
   // the last launch completes `done`
   auto go = [&](auto kern, int pieces, int waves, auto* h1, auto* h1t, hipEvent_t ev) {
     const dim3 grid(rows_pad * pieces), block(64 * waves);

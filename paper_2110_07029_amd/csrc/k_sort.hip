@@ -12,8 +12,8 @@
 //             per-wave running counts, then a prefix over the four waves; keys land
 //             at offset + rank.
 // Summing in the scatter reads (chunks)^2 rows of counts, which beside the output layer's
-// launches, on the few CUs and registers these leave, costs more than it saves from 48 chunks
-// on: above SORT_SELF_SCAN chunks a launch of its own (scan, one workgroup) forms the offsets.
+// launches, on the few CUs and registers these leave, costs more than it saves from about
+// SORT_SCAN_CHUNKS on: from there a launch of its own (scan, one workgroup) forms the offsets.
 // us per step with the sort the longest chain, summing in the scatter | in a launch: 61,000
 // keys 151 | 134, 79,000 172 | 145, 120,000 186 | 142; 46,000 keys (45 chunks) 109.0 | 110.1
 // and 139 | 132, 28,000 113 | 121 and 120 | 115.
@@ -123,8 +123,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_sort_scan(const int32_t* __res
     }
   }
 }
-
-constexpr int SORT_SELF_SCAN = 48;
 
 // offs: the scan's offsets, or null: this workgroup forms its own from hist.
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(SortJob j, int nblk, const int32_t* __restrict__ hist,
@@ -278,7 +276,7 @@ hipError_t launch_sort(const SortPlan& plan, int32_t* hist, hipStream_t st) {
     const int32_t* offs = nullptr;
     hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(SORT_THREADS), (size_t)4 << j.nbits, st, j.keys_in, j.n, j.shift,
                        j.nbits, nblk, hist);
-    if (nblk > SORT_SELF_SCAN) {
+    if (nblk >= SORT_SCAN_CHUNKS) {
       int32_t* o = hist + ((size_t)nblk << SORT_MAX_BITS);
       hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(SCAN_THREADS), 0, st, hist, nblk, 1 << j.nbits, o);
       offs = o;
