@@ -1014,9 +1014,13 @@ constexpr int TOPK_NONE = 0x7fffffff;  // the id where a row has fewer than k ra
 
 __device__ __forceinline__ double max_key(double a, double b) {
   double d;
-  // (asm: no canonicalising moves, as no key is NaN.  The compiler does not count it for
-  // a matrix product's late read of its C registers; the last product whose C is not its
-  // own result is issued 15 products before any key is formed.)
+  // (asm: no canonicalising moves, as no key is NaN.  The compiler's hazard pass does not see
+  // that it writes registers, so no matrix product may be in flight that still reads them as its
+  // C.  Only a row block's first product of a tile can read another C than its own result, and
+  // the others of its tile follow it in one chain, at least seven of 8 passes (32 rows per wave
+  // with bf16 operands; 14 with 64 rows, 63 with fp32 operands), each waiting for the one
+  // before: over 200 cycles, where the read of C ends within 20.  Keys are formed in a later
+  // basic block than the tile's products, which none of them moves past.)
   asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
   return d;
 }
