@@ -502,9 +502,9 @@ asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int
   // the event was completed by the lse/targets launch itself: a separate record
   // would put a marker between lse/targets and the backward on the model's
   // stream, and a gap of several microseconds with it
-  if (da_stream != m->stream) HIP_TRY(hipStreamWaitEvent(da_stream, m->ev_dA1, 0));
+  HIP_TRY(hipStreamWaitEvent(da_stream, m->ev_dA1, 0));
   TIMED_ON(m, ASGD_K_HIDDEN, da_stream, launch_out_dA1(B, s_eff, m->m_part, m->s_part, m->o_part, rows_pad, m->tw,
-                                                       A, dA, da_stream == m->stream, da_stream));
+                                                       A, dA, da_stream));
   return ASGD_OK;
 }
 

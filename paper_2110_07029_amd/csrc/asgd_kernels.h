@@ -146,8 +146,8 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
 // t0, t1: optional events that the launch itself completes at the kernel's
 // start and end, for timing the kernel alone)
 // Per row, after the forward: lse, and with y the loss and tw = mean_{y in Y_i} W2[y]
-// [B x 128] (reads W2 before the backward updates it).
-// With y and dA1 (non-null), the same launch also forms dA1 = ((O/s - tw) / B) * [A1 > 0]
+// [B x 128], for launch_out_dA1 (reads W2 before the backward updates it).
+// With y and dA1 (non-null), the same launch, in the place of tw, forms dA1 = ((O/s - tw) / B) * [A1 > 0]
 // from the partials (o_part, A1 as for launch_out_dA1); dA1 null: lse and targets only.
 // Threads of a sort workgroup in that launch, and how many of them it takes along (several
 // fit on a CU beside the rows').
@@ -166,10 +166,9 @@ hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float*
 // launch goes on to the first layer's dA1 = (dA2 Wh) * [A1 > 0].  sort: a pass of the feature sort to run in the same launch, with dA1 only;
 // done: an event that the launch itself completes when the kernel has
 // finished, with no marker of its own on the stream)
-// Per row: dA1 = ((O/s - tw) / B) * [A1 > 0] from the forward's partials (reads no W2);
-// wide: twice the threads per row (for a launch that runs alone, not beside the backward).
+// Per row: dA1 = ((O/s - tw) / B) * [A1 > 0] from the forward's partials (reads no W2).
 hipError_t launch_out_dA1(int B, int splits, const float* m_part, const float* s_part, const float* o_part,
-                          int ld_part, const float* tw, const float* A1, float* dA1, bool wide, hipStream_t st);
+                          int ld_part, const float* tw, const float* A1, float* dA1, hipStream_t st);
 // Recompute Z per label tile, dZ = (softmax - T)/B, dW2 = dZ^T H1, db2; update W2, b2 in place.
 hipError_t launch_out_bwd(bool use_bf16, float* W2, float* b2, int L, const void* H1,
                           const void* H1T, int ld_t, int B, const float* lse, const float* rw,
@@ -225,7 +224,6 @@ hipError_t launch_softmax_ce(const float* Z, int ldz, int B, float* m_part, floa
                              const CsrDev* y, float* lse, float* loss_rows, hipStream_t st);
 // dA = ((P W2 - rw sum_{y in Y_i} W2[y]) / B) * [A > 0] with P = exp(Z - lse) from the stored Z;
 // o_part: splits x ld_part x 128 floats.
-int unfused_dh_splits(int n_cu, int aux_cus, int B, bool use_bf16, int n_tiles);
 hipError_t launch_unfused_dh(bool use_bf16, const float* W2, const float* b2, int L, const float* Z, int ldz,
                              const float* lse, int B, int splits, float* o_part, int ld_part, const CsrDev& y,
                              const float* rw, const float* A, float* dA, hipStream_t st);

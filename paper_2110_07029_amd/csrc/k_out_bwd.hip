@@ -48,17 +48,6 @@ constexpr int BWD_CROWS = 128;  // rows per H1 chunk of the chunked kernel (two 
 
 enum BwdMode { BWD_GLOBAL = 0, BWD_STAGED = 1, BWD_CHUNKED = 2 };  // STAGED: k_out_bwd_prefetch
 
-// Copy rows [r0, r0 + nrows) of H1 (row-major, ld HID) into the LDS tile (row
-// r of the chunk at tw_off(r, .)); nrows is a multiple of 32 and inside the
-// padded batch (rows past B are zero).  16 lanes store one row: conflict-free.
-__device__ __forceinline__ void stage_h1(bf16* h1s, const bf16* __restrict__ H1, int r0, int nrows) {
-  for (int e = threadIdx.x; e < nrows * 16; e += BWD_THREADS) {
-    const int r = e >> 4, c = e & 15;
-    const uint4 v = *reinterpret_cast<const uint4*>(H1 + (size_t)(r0 + r) * HID + c * 8);
-    *reinterpret_cast<uint4*>(h1s + r * TW_LD + 8 * (c ^ ((r >> 2) & 3))) = v;
-  }
-}
-
 // One 16-byte direct copy per lane from global memory into LDS: lane l's
 // bytes land at LDS byte lds + 16 l (lds: wave-uniform LDS byte address).
 // Written as inline asm so that the compiler's wait-count pass does not treat
@@ -132,7 +121,7 @@ __global__ __launch_bounds__(BWD_THREADS) void k_out_bwd(
   };
 
   // Rows [c0, c0 + BWD_CROWS) of H1 into chunk buffer dst, in the tile layout
-  // of stage_h1, by direct global-to-LDS copies: a wave's 16-byte copy fills
+  // (row r at tw_off(r, .)), by direct global-to-LDS copies: a wave's 16-byte copy fills
   // 1024 consecutive LDS bytes (lane l at byte 16 l), so each lane picks the
   // global chunk that belongs at its LDS slot; the 4 pad slots of a row (bytes
   // 256..319) take an arbitrary chunk of the row.  The rows read stay below

@@ -625,17 +625,16 @@ hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2,
 // (k_out_lse_targets<., true>).
 // k_out_lse_targets: 512 threads, one (max, sum) pair per thread merged by
 // wavefront reductions, 8 wavefronts x the row's labels for the target terms.
-// k_out_dA1: G split groups x 32 threads x 4 hidden units; each group merges
-// its splits online against its own running maximum, then the groups are
-// rescaled to the row's maximum.  G = 8 (256 threads, 4 KB of LDS, so that it
-// fits on a CU beside the backward) or, when nothing runs beside it, 16.
+// k_out_dA1: 8 split groups x 32 threads x 4 hidden units (256 threads, 4 KB of LDS,
+// so that it fits on a CU beside the backward); each group merges its splits online
+// against its own running maximum, then the groups are rescaled to the row's maximum.
 // Every partial is combined in a fixed order, so the results do not depend on
 // scheduling.
 // ---------------------------------------------------------------------------
 constexpr int CMB_THREADS = 512;
 constexpr int CMB_WAVES = CMB_THREADS / 64;   // 8
-constexpr int DA_GROUPS = 8;        // beside the backward: 256 threads, 4 KB of LDS
-constexpr int DA_GROUPS_WIDE = 16;  // on the model's stream, where nothing runs beside it
+constexpr int DA_GROUPS = 8;        // k_out_dA1
+constexpr int DA_GROUPS_WIDE = 16;  // k_out_lse_targets<., true>
 
 // (m, s) <- the merge of two (maximum, sum of 2^(x - maximum)) pairs, base 2 or
 // natural alike through exp_fast (natural logarithms here)
@@ -644,73 +643,6 @@ __device__ __forceinline__ void ms_merge_ln(float& m, float& s, float m2, float 
   if (mm == -INFINITY) return;
   s = (m == -INFINITY ? 0.0f : s * exp_fast(m - mm)) + (m2 == -INFINITY ? 0.0f : s2 * exp_fast(m2 - mm));
   m = mm;
-}
-
-// Group grp's online merge of splits grp, grp + 16, ...: running maximum mg,
-// sum St and (WITH_O) the weighted O of hidden units h4 .. h4 + 3.
-template <bool WITH_O, int GROUPS>
-__device__ __forceinline__ void merge_splits(int i, int splits, const float* __restrict__ m_part,
-                                             const float* __restrict__ s_part, const float* __restrict__ o_part,
-                                             int ld_part, int grp, int h4, float& mg, float& St, float4& O) {
-  mg = -INFINITY;
-  St = 0.0f;
-  O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll 8
-  for (int s = grp; s < splits; s += GROUPS) {
-    const size_t r = (size_t)s * ld_part + i;
-    const float ms = m_part[r];
-    const float ss = s_part[r];
-    float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if constexpr (WITH_O) o = *reinterpret_cast<const float4*>(o_part + r * HID + h4);
-    // (no split has -inf: one of nothing but labels of bias -inf holds -FLT_MAX ln 2 and s = 0)
-    const float mn = fmaxf(mg, ms);
-    const float a = exp_fast(mg - mn), e = exp_fast(ms - mn);
-    St = fmaf(e, ss, St * a);
-    if constexpr (WITH_O) {
-      O.x = fmaf(e, o.x, O.x * a);
-      O.y = fmaf(e, o.y, O.y * a);
-      O.z = fmaf(e, o.z, O.z * a);
-      O.w = fmaf(e, o.w, O.w * a);
-    }
-    mg = mn;
-  }
-}
-
-// dA1 of row i from the forward's partials, by a workgroup of GROUPS x 32
-// threads (every thread calls it): each group merges its splits' O online
-// against its own running maximum, then the groups are rescaled to the row's
-// maximum; thread t < HID writes hidden unit t, with tw_t the row's mean target
-// weight of that unit.  red_o [GROUPS][HID], red_s and red_m [GROUPS]: LDS.
-template <int GROUPS>
-__device__ __forceinline__ void da1_row(int i, int splits, const float* __restrict__ m_part,
-                                        const float* __restrict__ s_part, const float* __restrict__ o_part,
-                                        int ld_part, float tw_t, const float* __restrict__ A1, float invB,
-                                        float* __restrict__ dA1, float (*red_o)[HID], float* red_s, float* red_m) {
-  const int t = threadIdx.x;
-  const int grp = t >> 5, h4 = (t & 31) * 4;
-  float mg, St;
-  float4 O;
-  merge_splits<true, GROUPS>(i, splits, m_part, s_part, o_part, ld_part, grp, h4, mg, St, O);
-  *reinterpret_cast<float4*>(&red_o[grp][h4]) = O;
-  if ((t & 31) == 0) {
-    red_s[grp] = St;
-    red_m[grp] = mg;
-  }
-  __syncthreads();
-  if (t < HID) {
-    float M = red_m[0];
-#pragma unroll
-    for (int k = 1; k < GROUPS; ++k) M = fmaxf(M, red_m[k]);
-    float Ot = 0.0f, Stot = 0.0f;
-#pragma unroll
-    for (int k = 0; k < GROUPS; ++k) {
-      const float e = red_m[k] == -INFINITY ? 0.0f : exp_fast(red_m[k] - M);
-      Ot = fmaf(e, red_o[k][t], Ot);
-      Stot = fmaf(e, red_s[k], Stot);
-    }
-    const float dh = (Ot / Stot - tw_t) * invB;
-    dA1[(size_t)i * HID + t] = A1[(size_t)i * HID + t] > 0.0f ? dh : 0.0f;
-  }
 }
 
 // DA: the row's dA1 as well, in the same workgroup (16 split groups), for a
@@ -830,7 +762,7 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
   __shared__ float red_s2[DA_GROUPS_WIDE];
   __shared__ float red_m2[DA_GROUPS_WIDE];
   if constexpr (DA) {
-    // from -FLT_MAX, and no split holds -inf (see merge_splits): no inf - inf
+    // from -FLT_MAX, and no split holds -inf (see k_out_dA1): no inf - inf
     float mg = -FLT_MAX, St = 0.0f;
     float4 O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int k0 = grp;;) {
@@ -889,10 +821,16 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
         zs += red_z[k];
       }
       const float inv_cnt = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
-      tw_out[(size_t)i * HID + t] = tw * inv_cnt;
+      float mean;
+      {
+#pragma clang fp contract(off)  // (rounded by itself, as k_out_dA1 reads it)
+        mean = tw * inv_cnt;
+      }
       if constexpr (DA) {
-        my_d = a1 > 0.0f ? (Ot / Stot - tw * inv_cnt) * invB : 0.0f;
+        my_d = a1 > 0.0f ? (Ot / Stot - mean) * invB : 0.0f;
         dA1[(size_t)i * HID + t] = my_d;
+      } else {
+        tw_out[(size_t)i * HID + t] = mean;
       }
       if (t == 0) loss_rows[i] = lse - zs * inv_cnt;
     }
@@ -919,18 +857,57 @@ __global__ __launch_bounds__(CMB_THREADS) void k_out_lse_targets(
   }
 }
 
-template <int GROUPS>
-__global__ __launch_bounds__(32 * GROUPS) void k_out_dA1(int splits, const float* __restrict__ m_part,
-                                                        const float* __restrict__ s_part,
-                                                        const float* __restrict__ o_part, int ld_part,
-                                                        const float* __restrict__ tw, const float* __restrict__ A1,
-                                                        float invB, float* __restrict__ dA1) {
-  __shared__ float red_o[GROUPS][HID];
-  __shared__ float red_s[GROUPS];
-  __shared__ float red_m[GROUPS];
+// dA1 of one row: each group merges its splits' O online against its own running maximum,
+// then the groups are rescaled to the row's maximum; thread t < HID writes hidden unit t.
+__global__ __launch_bounds__(32 * DA_GROUPS) void k_out_dA1(int splits, const float* __restrict__ m_part,
+                                                           const float* __restrict__ s_part,
+                                                           const float* __restrict__ o_part, int ld_part,
+                                                           const float* __restrict__ tw, const float* __restrict__ A1,
+                                                           float invB, float* __restrict__ dA1) {
+  __shared__ float red_o[DA_GROUPS][HID];
+  __shared__ float red_s[DA_GROUPS];
+  __shared__ float red_m[DA_GROUPS];
   const int i = xcd_order((int)blockIdx.x, (int)gridDim.x), t = threadIdx.x;
   const float tw_t = t < HID ? tw[(size_t)i * HID + t] : 0.0f;
-  da1_row<GROUPS>(i, splits, m_part, s_part, o_part, ld_part, tw_t, A1, invB, dA1, red_o, red_s, red_m);
+  const int grp = t >> 5, h4 = (t & 31) * 4;
+  float mg = -INFINITY, St = 0.0f;
+  float4 O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll 8
+  for (int s = grp; s < splits; s += DA_GROUPS) {
+    const size_t r = (size_t)s * ld_part + i;
+    const float ms = m_part[r];
+    const float ss = s_part[r];
+    const float4 o = *reinterpret_cast<const float4*>(o_part + r * HID + h4);
+    // (no split has -inf: one of nothing but labels of bias -inf holds -FLT_MAX ln 2 and s = 0)
+    const float mn = fmaxf(mg, ms);
+    const float a = exp_fast(mg - mn), e = exp_fast(ms - mn);
+    St = fmaf(e, ss, St * a);
+    O.x = fmaf(e, o.x, O.x * a);
+    O.y = fmaf(e, o.y, O.y * a);
+    O.z = fmaf(e, o.z, O.z * a);
+    O.w = fmaf(e, o.w, O.w * a);
+    mg = mn;
+  }
+  *reinterpret_cast<float4*>(&red_o[grp][h4]) = O;
+  if ((t & 31) == 0) {
+    red_s[grp] = St;
+    red_m[grp] = mg;
+  }
+  __syncthreads();
+  if (t < HID) {
+    float M = red_m[0];
+#pragma unroll
+    for (int k = 1; k < DA_GROUPS; ++k) M = fmaxf(M, red_m[k]);
+    float Ot = 0.0f, Stot = 0.0f;
+#pragma unroll
+    for (int k = 0; k < DA_GROUPS; ++k) {
+      const float e = red_m[k] == -INFINITY ? 0.0f : exp_fast(red_m[k] - M);
+      Ot = fmaf(e, red_o[k][t], Ot);
+      Stot = fmaf(e, red_s[k], Stot);
+    }
+    const float dh = (Ot / Stot - tw_t) * invB;
+    dA1[(size_t)i * HID + t] = A1[(size_t)i * HID + t] > 0.0f ? dh : 0.0f;
+  }
 }
 
 int lse_sort_threads() { return CMB_THREADS; }
@@ -978,13 +955,9 @@ hipError_t launch_out_lse_targets(bool use_bf16, int B, int splits, const float*
 }
 
 hipError_t launch_out_dA1(int B, int splits, const float* m_part, const float* s_part, const float* o_part,
-                          int ld_part, const float* tw, const float* A1, float* dA1, bool wide, hipStream_t st) {
-  if (wide)
-    hipLaunchKernelGGL(k_out_dA1<DA_GROUPS_WIDE>, dim3(B), dim3(32 * DA_GROUPS_WIDE), 0, st, splits, m_part, s_part,
-                       o_part, ld_part, tw, A1, 1.0f / (float)B, dA1);
-  else
-    hipLaunchKernelGGL(k_out_dA1<DA_GROUPS>, dim3(B), dim3(32 * DA_GROUPS), 0, st, splits, m_part, s_part, o_part,
-                       ld_part, tw, A1, 1.0f / (float)B, dA1);
+                          int ld_part, const float* tw, const float* A1, float* dA1, hipStream_t st) {
+  hipLaunchKernelGGL(k_out_dA1, dim3(B), dim3(32 * DA_GROUPS), 0, st, splits, m_part, s_part, o_part, ld_part, tw, A1,
+                     1.0f / (float)B, dA1);
   return hipGetLastError();
 }
 

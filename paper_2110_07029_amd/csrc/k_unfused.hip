@@ -467,15 +467,6 @@ __global__ __launch_bounds__(HID * DHC_GROUPS) void k_dh_combine(const float* __
   dA[(size_t)row * HID + j] = A[(size_t)row * HID + j] > 0.0f ? dh : 0.0f;
 }
 
-int unfused_dh_splits(int n_cu, int aux_cus, int B, bool use_bf16, int n_tiles) {
-  const int RB = out_rows_per_block(use_bf16);
-  const int nrb = (B + RB - 1) / RB;
-  const int wgs = n_cu - aux_cus > 1 ? n_cu - aux_cus : 1;
-  int s = (wgs + nrb - 1) / nrb;
-  if (s > n_tiles) s = n_tiles;
-  return s < 1 ? 1 : s;
-}
-
 hipError_t launch_unfused_dh(bool use_bf16, const float* W2, const float* b2, int L, const float* Z, int ldz,
                              const float* lse, int B, int splits, float* o_part, int ld_part, const CsrDev& y,
                              const float* rw, const float* A, float* dA, hipStream_t st) {
