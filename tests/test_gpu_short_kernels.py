@@ -1,6 +1,6 @@
 """The whole step at trained-scale weights where the output layer changes kernels: the forward
-with waves on tiles of their own and the backward with waves on row blocks of their own, on both
-sides of every line of their rules, with remainders in rows, labels and waves."""
+with waves on tiles of their own and the backward with waves on row blocks of their own, and the
+kernels past the lines of their rules, with remainders in rows, labels and waves."""
 import numpy as np
 import pytest
 
@@ -14,11 +14,11 @@ from test_gpu_trained_scale import trained_scale
 pytestmark = pytest.mark.gpu
 
 
-# forward: short up to 64 rows or 32,768 (tile, 32-row block) products; backward: up to 512
-# label blocks at 256 rows or less with bf16 operands, else 2,048.  L = 7, 32, 33: less than
-# a tile, a tile and one more; 16,385 and 65,537: one label past the backward's lines.
-# Splits of one tile each up to 1,024 labels, of eight from 8,192 on; 65 and
-# 129 splits at 16,640 and 33,000 (the per-row pass takes 64 at a time)
+# All of these run the forward for short label splits; L = 7, 32, 33: less than a tile, a tile and
+# one more.  Its splits have one tile each up to 1,024 labels and eight from 8,192 on; 65 and 129
+# splits at 16,640 and 33,000 (the per-row pass takes 64 at a time).  Backward with bf16 operands:
+# a workgroup per label block up to 512 blocks at 256 rows or less (16,384 | 16,385 labels), else
+# up to 2,048 (65,536 | 65,537); the lines with fp32 operands and the forward's are below.
 @pytest.mark.parametrize("B,L", [(1, 7), (1, 33), (33, 32), (64, 257), (65, 1_000), (256, 16_384), (255, 16_385),
                                  (257, 1_000), (300, 65_536), (257, 65_537), (1_000, 2_001),
                                  (128, 1_024), (128, 1_025), (40, 8_192), (40, 8_193),
@@ -66,3 +66,15 @@ def test_step_parity_at_the_line_of_the_fp32_backward(B, past):
     L = 32 * bwd_line(B) + past
     flush(f"fp32 backward's line: B={B} L={L}")
     step_parity(B, L, False)
+
+
+# The forward's line: 32,768 (tile, 32-row block) products, where B is above 64.  The last on one
+# side and the first on the other, by labels and by rows, up to the largest batch; the bf16 backward
+# is the one with a block per wave (256 rows), the chunked one (520 rows at 65,568 labels) or that
+# of few blocks, the fp32 one reads H1 from global memory at 256 rows.
+@pytest.mark.parametrize("B,L", [(256, 131_072), (256, 131_073), (2_048, 16_384), (2_048, 16_385), (1_024, 32_768),
+                                 (1_025, 32_768), (520, 65_568)])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_step_parity_at_the_line_of_the_forward(B, L, bf16):
+    flush(f"forward's line: B={B} L={L} bf16={bf16}")
+    step_parity(B, L, bf16)

@@ -116,3 +116,57 @@ def test_labels_masked_by_infinite_biases(B, L, nnz, bf16):
         assert_update_close("W1", p["W1"][t], got["W1"][t], ref["W1"][t], rtol, mag["W1"])
     finally:
         s.free()
+
+
+# The same two checks for the kernels of long label spaces, which 2,999 labels do not reach: the
+# forward with shared tiles, the bf16 backward with a label block per wave, the chunked one, and the
+# fp32 one that reads H1 from global memory.
+@pytest.mark.parametrize("B,L,bf16", [(256, 131_105, True), (96, 16_500, True), (300, 65_700, True), (513, 65_700, True),
+                                      (256, 131_105, False), (33, 20_640, False)])
+def test_bias_update_of_labels_without_targets_in_long_label_spaces(B, L, bf16):
+    """Bounds as above; here the probabilities are 1/L on average, so the update of one bias is
+    near the rounding of the bias itself: the rate is 0.1 L, and the updates' bound is the same
+    share of them."""
+    flush(f"trained scale, long label space: B={B} L={L} bf16={bf16}")
+    wl = synth.Workload("labels-long", 5_000, L, 700, B, 0.01, True, "lognormal", 3.5, 0.8, 500, 1.05, "uniform",
+                        "poisson", 4.0, 1.2, 2)
+    s = Setup(wl, 700, B, bf16=bf16)
+    try:
+        p = trained_scale(s.F, s.L, 5)
+        write_params(s.m, p)
+        lr = 0.1 * L
+        asgd.asgd_train_step(s.m, s.xb(0, B), s.yb(0, B), lr)
+        x, y = s.host_batch(0, B)
+        ref = om.train_step(p, x, y, lr, "bf16" if bf16 else "fp32")[0]["b2"].astype(np.float64) - p["b2"]
+        got = asgd.asgd_model_get_params(s.m, asgd.ASGD_PARAM_B2, (s.L,)).astype(np.float64) - p["b2"]
+        free = np.setdiff1d(np.arange(s.L), y.indices)
+        want = ref[free]
+        assert np.median(np.abs(want)) > 1e-2  # far above the bias' rounding
+        bound = (5e-3 if bf16 else 1e-4) * np.abs(want) + 2.0 * np.spacing(np.abs(p["b2"][free]) + np.abs(want)).astype(float)
+        err = np.abs(got[free] - want)
+        assert np.all(err <= bound), (err / bound).max()
+    finally:
+        s.free()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("label", [5, 39, 70_001])
+def test_one_label_far_above_the_rest_in_a_long_label_space(label, bf16):
+    flush(f"far label {label} of 131,105 bf16={bf16}")
+    B = 256
+    wl = synth.Workload("labels-long", 5_000, 131_105, 256, B, 0.01, True, "lognormal", 3.5, 0.8, 500, 1.05, "uniform",
+                        "poisson", 4.0, 1.2, 2)
+    s = Setup(wl, 256, B, bf16=bf16)
+    try:
+        p = trained_scale(s.F, s.L, 6)
+        p["b2"][label] = 200.0
+        write_params(s.m, p)
+        x, y = s.host_batch(0, B)
+        loss = asgd.asgd_train_step(s.m, s.xb(0, B), s.yb(0, B), 0.5, want_loss=True)
+        ref, ref_loss, g, _ = om.train_step(p, x, y, 0.5, "bf16" if bf16 else "fp32")
+        assert np.isfinite(loss) and abs(loss - ref_loss) <= 1e-3 * abs(ref_loss), (loss, ref_loss)
+        got = asgd.asgd_model_get_params(s.m, asgd.ASGD_PARAM_B1, (H,)).astype(np.float64)
+        d, dr = got - p["b1"], ref["b1"].astype(np.float64) - p["b1"]
+        assert np.linalg.norm(d - dr) <= 2e-2 * np.linalg.norm(dr)
+    finally:
+        s.free()
