@@ -38,15 +38,15 @@ OVERLAPPED = ("gather", "sort", "labels", "hidden", "dense_fwd", "dense_bwd", "w
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 PMC_TRAFFIC = {
     ("wide-label", 256, "out_bwd"): dict(
-        sources=('csrc/k_out_bwd.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
+        sources=('csrc/k_out_bwd.hip', 'csrc/aux_dev.h', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
         sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
         fetch_kib=169865.5, write_kib=337663.1),
     ("wide-label", 1024, "out_bwd"): dict(
-        sources=('csrc/k_out_bwd.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
+        sources=('csrc/k_out_bwd.hip', 'csrc/aux_dev.h', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
         sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
         fetch_kib=177892.1, write_kib=338237.3),
     ("wide-feature", 128, "out_bwd"): dict(
-        sources=('csrc/k_out_bwd.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
+        sources=('csrc/k_out_bwd.hip', 'csrc/aux_dev.h', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
         sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
         fetch_kib=52272.6, write_kib=103524.0),
     ("elastic", 4, "merge"): dict(
@@ -542,9 +542,9 @@ def main():
     mean_lnnz = float(np.mean([lnnz[j] for j in used]))
     uniq = float(np.mean([len(np.unique(ds.x.indices[ipx[bounds[j][0]]:ipx[bounds[j][1]]]))
                           for j in used[:32]]))
-    # label splits of the forward (and of the unfused path's P W2): one persistent workgroup per CU
-    # but 16, shared by the 256-row blocks; short splits (of 8 tiles, or up to 32 of fewer) by the
-    # 32-row blocks
+    # label splits of the forward (and of the unfused path's P W2), by the rule of fwd_plan in
+    # k_output.hip: one persistent workgroup per CU but 16, shared by the 256-row blocks; short
+    # splits (of 8 tiles, or up to 32 of fewer) by the 32-row blocks; whole tiles per split
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     n_tiles = (w.n_labels + 31) // 32
     if not args.unfused and (B <= 64 or n_tiles * -(-B // 32) <= 32768):
@@ -552,7 +552,10 @@ def main():
         splits = max(1, min(most, (n_cu - 16) // -(-B // 32)))
     else:
         splits = min(n_tiles, -(-(n_cu - 16) // -(-B // 256)))
+    splits = -(-n_tiles // -(-n_tiles // splits))
     model = kernel_model(w, B, mean_nnz, mean_lnnz, uniq, splits)
+    if "hidden" not in kt:  # the per-row launch forms dA1 too: it reads O and A1, dA1 in the targets' place
+        model["out_combine"]["bytes"] += splits * B * H * 4.0 + B * H * 4.0
     dtype = "bf16" if w.gemm_bf16 else "fp32"
     kernels = {}
     for name, (tot, n) in kt.items():

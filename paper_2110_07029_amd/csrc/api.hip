@@ -42,8 +42,11 @@ constexpr int64_t kAlign = 64;  // floats
 constexpr int kMaxBatch = 16384;      // rows of one prediction call
 constexpr int kMaxTrainBatch = 2048;  // rows of one training step (and of the inspection calls)
 // The output-layer forward runs one persistent workgroup per CU except
-// kAuxCus, which stay free for the feature sort on the internal stream and
-// the forward launch's own label-grouping workgroup.
+// kAuxCus, which stay free for the forward launch's own label-grouping
+// workgroup and the feature sort on the internal stream (whose workgroups also
+// fit beside the forward's).  How many makes no difference beyond that of the
+// runs: us per step at L = 670,091 with 16 | 8 | 4 of them, B = 256 263 | 261 |
+// 262, B = 611 581 | 584 | 581, B = 1024 803 | 805 | 798.
 constexpr int kAuxCus = 16;
 // Events that only order work between streams of this device: a device-scope
 // release when recorded (a system-scope one writes the caches back for the
