@@ -415,50 +415,40 @@ asgd_status run_gather(asgd_model* m, const asgd_csr* x, const asgd_csr* y, hipS
   return ASGD_OK;
 }
 
-// Which of a training step's work runs on the internal stream, beside the output layer.
-enum class Beside { NOTHING, SORT_AND_UPDATE, FIRST_LAYER };
-
-// FIRST_LAYER (gather, sort, dA1, sparse update) and SORT_AND_UPDATE (the sort beside the
-// forward, the sparse update beside the backward) hide that work, but each pair of streams'
-// event and wait costs 10-13 us of host time and a gap of 5-8 us on the GPU, and on one
-// stream the sort runs inside the output layer's launches, so a second stream pays only
-// beside a long output layer or when the first layer's own work is long.
-// Measured, us per step, one stream | two, at 75 entries per row:
+// Whether a training step puts the first layer's work on the internal stream, beside the
+// output layer: gather, sort, dA1 and sparse update, or, with stored logits, the sort and the
+// update.  That hides it, but each pair of streams' event and wait costs 10-13 us of host time
+// and a gap of 5-8 us on the GPU, and on one stream the sort runs inside the output layer's
+// launches, so it pays only beside a long output layer or when the first layer's own work is
+// long.  Measured, us per step of one model, one stream | two, at 75 entries per row:
 //   L = 60,000,  B = 256:  68 | 85     L = 120,000, B = 256: 93 | 97
 //   L = 205,443, B = 128:  93 | 97     L = 250,000, B = 256: 127 | 127
 //   L = 300,000, B = 128: 124 | 137    L = 40,000, B = 1024 (38,000 entries): 110 | 104
 // (the 70 us line is where the two met before the one-stream launches were shortened; at
-// few rows one stream now leads beyond it.)  By entries, B = 256, L = 30,000: 58,000 79 | 90;
-// at 330 per row (below), which fit beside nothing else, B = 200, L = 120,000: 106 | 119,
-// L = 205,443: 127 | 134, L = 400,000, B = 160: 168 | 165.
-// The entries' line is the room of the riding sort's counters, and for short rows where it takes
-// too long (B = 1024, L = 40,000: 60,000 114 | 111).
-// Rows split over several gather workgroups do not fit beside the backward, and where their
-// gather, sort, dA1 and update take longer than the output layer, the gather and dA1 belong on
-// the other stream.  FIRST_LAYER | SORT_AND_UPDATE at 330 entries per row:
-//   L = 30,000,  B = 256: 107 | 117    L = 60,000,  B = 384: 137 | 142   (below 40 us)
-//   L = 100,000, B = 256: 131 | 127    L = 130,000, B = 256: 140 | 136
-//   L = 400,000, B = 200: 187 | 175    L = 205,443, B = 256: 158 | 145
-//   L = 400,000, B = 160: 184 | 165    L = 400,000, B = 384: 307 | 293
-//   L = 670,091, B = 160: 253 | 256    L = 670,091, B = 256: 286 | 286   (10 labels per entry)
-//   L = 60,000,  B = 600: 172 | 175    L = 100,000, B = 600: 193 | 187   (2 entries per label)
-//   75 per row, B = 1024: L = 205,443: 300 | 316, L = 670,091: 802 | 802
+// few rows one stream now leads beyond it.)  By entries, up to what the riding sort's counters
+// hold: L = 12,000, B = 700, 52,000 67 | 87; L = 40,000, B = 1024, 60,000 114 | 111.
+// Rows split over several gather workgroups do not fit beside the backward.  330 per row:
+//   L = 30,000,  B = 200: 83 | 99      L = 120,000, B = 200: 106 | 122
+//   L = 205,443, B = 200: 127 | 137    L = 400,000, B = 160: 168 | 184
+// Where several models step in turn on one stream, the internal streams of the others fill the
+// gaps, and two streams gain.  Three models, one stream | two:
+//   L = 100,000, B = 180, 320 per row: 95 | 92     L = 205,443, B = 200, 230 per row: 137 | 133
+//   L = 300,000, B = 125, 330 per row: 154 | 160   L = 350,000, B = 85, 200 per row: 150 | 158
+//   L = 12,000, B = 650, 75 per row: 68 | 67       L = 25,000, B = 850, 65 per row: 89 | 83
+// so the lines lie where neither use loses more than it gains.
 // Stored logits: none of their launches takes the sort along, so on one stream it stands
-// alone: beside them from 3 us of one pass's estimate on.  One stream | SORT_AND_UPDATE:
+// alone: two streams from 3 us of one pass's estimate on.
 //   L = 1,000,  B = 128 (fp32): 82 | 97     L = 3,000,  B = 256: 95 | 98
 //   L = 5,000,  B = 600: 114 | 104          L = 12,000, B = 256: 106 | 101
 //   L = 30,000, B = 256: 123 | 116          L = 30,000, B = 64: 100 | 100
 //   L = 45,000, B = 256: 145 | 128          L = 100,000, B = 64: 135 | 127
-Beside step_streams(const asgd_model* m, int B, int nnz) {
+bool overlap_pays(const asgd_model* m, int B, int nnz) {
   // forward and backward of the output layer: per label 0.2 ns of memory traffic and
   // 0.87 ns per 1,000 rows of products
   const double out_us = (double)m->L * (2e-4 + 8.7e-7 * B);
-  if (m->unfused) return out_us >= 3.0 || nnz > 49152 ? Beside::SORT_AND_UPDATE : Beside::NOTHING;
+  if (m->unfused) return out_us >= 3.0 || nnz > 49152;
   const bool long_rows = gather_splits_rows(B, nnz);
-  if (out_us < (long_rows ? 100.0 : 70.0) && nnz <= (out_us < 40.0 || long_rows ? SORT_RIDE_MAX : 49152))
-    return Beside::NOTHING;
-  const bool behind = out_us >= 40.0 && long_rows && nnz <= 2LL * m->L && m->L < 10LL * nnz;
-  return behind ? Beside::SORT_AND_UPDATE : Beside::FIRST_LAYER;
+  return out_us >= (long_rows ? 100.0 : 70.0) || nnz > (out_us < 15.0 || long_rows ? SORT_RIDE_MAX : 49152);
 }
 
 SortPlan plan_sort(asgd_model* m, int n_keys) {
@@ -474,15 +464,13 @@ asgd_status run_sort(asgd_model* m, hipStream_t st, const SortPlan& plan) {
 // The fused output-layer forward and the per-row lse / target terms on the
 // model's stream; with y, dA1 (dA2 with the second hidden layer) follows on
 // da_stream, after an event when that is another stream (the training step
-// runs it beside the backward) or, on the model's stream, in the same launch, which then
-// completes `done`.  With sort (da_stream the model's stream), the passes of the feature
-// sort run inside the two launches, and the second of them carries dA2 on to dA1.
-// sort_beside: the sort runs beside the forward and is what the step waits for.
+// runs it beside the backward).  With sort (da_stream the model's stream), the
+// passes of the feature sort run inside the two launches, and the second of them
+// carries dA2 on to dA1.
 asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int rows_pad,
-                        const LabelJob* labels, hipStream_t da_stream, const SortPlan* sort = nullptr,
-                        bool sort_beside = false, hipEvent_t done = nullptr) {
+                        const LabelJob* labels, hipStream_t da_stream, const SortPlan* sort = nullptr) {
   const int B = x->n_rows;
-  const FwdPlan fp = fwd_plan(m->bf16, m->L, B, std::max(1, m->n_cu - kAuxCus), sort_beside);
+  const FwdPlan fp = fwd_plan(m->bf16, m->L, B, std::max(1, m->n_cu - kAuxCus));
   const int s_eff = fp.splits;
   if ((int64_t)s_eff * rows_pad > m->part_rows) return fail(ASGD_ERANGE, "partial buffer too small");
   TIMED_LAUNCH(m, ASGD_K_OUT_FWD,
@@ -500,7 +488,7 @@ asgd_status run_forward(asgd_model* m, const asgd_csr* x, const asgd_csr* y, int
                                                       m->b2(), m->L, m->H1, y ? &yd : nullptr, m->lse,
                                                       m->loss_rows, m->tw, m->o_part, A, fused ? dA : nullptr,
                                                       sort && m->extra ? &dn : nullptr, sort && sort->passes > 1 ? &sort->pass[1] : nullptr, m->stream,
-                                                      fused ? done : y ? m->ev_dA1 : nullptr));
+                                                      y && !fused ? m->ev_dA1 : nullptr));
   if (!y || fused) return ASGD_OK;
   // the event was completed by the lse/targets launch itself: a separate record
   // would put a marker between lse/targets and the backward on the model's
@@ -753,8 +741,7 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
   SortPlan sort = plan_sort(m, x->nnz);
   const LabelJob labels{m->lkeys, y->nnz, m->lrow, m->lbeg, m->lpair, m->lcnt, 0};
   CsrDev xd = dev(x);
-  const Beside beside = step_streams(m, B, x->nnz);
-  const bool pipelined = beside == Beside::FIRST_LAYER, one_stream = beside == Beside::NOTHING;
+  const bool one_stream = !overlap_pays(m, B, x->nnz), pipelined = !one_stream && !m->unfused;
   m->pipe = m->pipe && pipelined;
   bool wgrad_rides = false;  // the second hidden layer's update inside the sparse update's launch
   if (pipelined) {
@@ -783,11 +770,9 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
                                                              m->dA1, m->aux));
   } else {
     // One stream (the feature sort's passes inside the forward's and the per-row
-    // launch; with stored logits the sort alone), or the sort and the sparse update
-    // on the internal one, beside the forward and the backward.
-    // (the events are completed by the launches themselves where one ends with it: a
-    // separate record would put a marker, and a gap, into the model's stream)
-    const bool sort_rides = one_stream && !m->unfused;
+    // launch), or, with stored logits, the sort and the sparse update on the
+    // internal one, beside the logits and the backward, or the sort alone.
+    const bool sort_rides = !m->unfused;  // (one stream: at most SORT_RIDE_MAX entries)
     const int n_zero = sort_rides ? sort_plan_ride(&sort, lse_sort_threads(), LSE_SORT_WGS, m->hist) : 0;
     s = run_gather(m, x, y, m->stream, &rows_pad, one_stream ? nullptr : m->ev_fork, sort_rides && m->extra, m->hist,
                    n_zero);
@@ -797,17 +782,15 @@ asgd_status asgd_train_step(asgd_model* m, const asgd_csr* x, const asgd_csr* y,
       s = run_sort(m, one_stream ? m->stream : m->aux, sort);
       if (s) return s;
     }
-    const bool dA1_by_launch = !one_stream && !m->unfused && !m->extra;
     s = m->unfused ? run_forward_unfused(m, x, y, rows_pad, &labels)
-                   : run_forward(m, x, y, rows_pad, &labels, m->stream, sort_rides ? &sort : nullptr, !one_stream,
-                                 dA1_by_launch ? m->ev_dA1 : nullptr);
+                   : run_forward(m, x, y, rows_pad, &labels, m->stream, &sort);
     if (s) return s;
     wgrad_rides = m->extra && sort_rides;
     if (m->extra && !wgrad_rides)
       TIMED(m, ASGD_K_DENSE_BWD, launch_dense_bwd(m->dA2, m->A1, m->Wh(), m->bh(), B, rows_pad, lr, m->dA1,
                                                   m->stream));
     if (!one_stream) {
-      if (!dA1_by_launch) HIP_TRY(hipEventRecord(m->ev_dA1, m->stream));
+      HIP_TRY(hipEventRecord(m->ev_dA1, m->stream));
       HIP_TRY(hipStreamWaitEvent(m->aux, m->ev_dA1, 0));
     }
   }

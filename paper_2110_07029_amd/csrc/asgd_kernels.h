@@ -133,11 +133,10 @@ int out_rows_per_block(bool use_bf16);
 // label_job_plan).
 // Its launch shape: nrb row blocks x `splits` label splits of tps tiles each; is_short: 32
 // rows per row block and waves on tiles of their own (k_out_fwd_short).  wgs: workgroups wanted.
-// sort_beside: launches of the feature sort run beside it, and the step waits for them.
 struct FwdPlan {
   int is_short, nrb, splits, tps;
 };
-FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs, bool sort_beside);
+FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs);
 hipError_t launch_out_fwd_train(bool use_bf16, const float* W2, const float* b2, int L, const void* H1,
                                 int B, const FwdPlan& shape, float* m_part, float* s_part, float* o_part,
                                 int ld_part, const LabelJob* job, const LabelJobPlan* plan, const SortJob* sort,

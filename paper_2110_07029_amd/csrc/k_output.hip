@@ -522,12 +522,10 @@ static bool fwd_is_short(int n_tiles, int B) {
 }
 
 // Splits of the forward and whether it runs k_out_fwd_short.
-FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs, bool sort_beside) {
+FwdPlan fwd_plan(bool use_bf16, int L, int B, int wgs) {
   const int n_tiles = (L + OUT_TILE - 1) / OUT_TILE;
   FwdPlan p;
-  // (the short one leaves a CU no registers or LDS for the sort's workgroups: L = 130,000,
-  // B = 256, 79,000 entries 138.6 | 135.5 us per step; L = 100,000, B = 300 134.4 | 131.8)
-  p.is_short = !sort_beside && fwd_is_short(n_tiles, B);
+  p.is_short = fwd_is_short(n_tiles, B);
   const int rb = p.is_short ? 32 : out_rows_per_block(use_bf16);
   p.nrb = (B + rb - 1) / rb;
   int s = p.is_short ? wgs / p.nrb : (wgs + p.nrb - 1) / p.nrb;

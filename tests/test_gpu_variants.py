@@ -231,9 +231,9 @@ def test_unfused_steps_alternate_between_one_stream_and_two(bf16):
 @pytest.mark.parametrize("extra", [0, 1])
 @pytest.mark.parametrize("bf16", [True, False])
 def test_steps_alternate_between_the_stream_layouts(bf16, extra):
-    """300,001 labels: 60 short rows put the whole first layer on the internal stream, 60 rows of 1,100
-    entries (split over gather workgroups) only the sort and the sparse update, 20 rows nothing.
-    Every change from one to another, issued back to back, with and without the second hidden layer."""
+    """300,001 labels: 60 rows put the whole first layer on the internal stream, whether short or of
+    1,100 entries (split over gather workgroups), 20 rows nothing.  Every change from one to another,
+    issued back to back, with and without the second hidden layer."""
     flush(f"steps in the stream layouts: bf16={bf16} extra={extra}")
     r = np.random.default_rng(17)
     F, L = 20_000, 300_001
