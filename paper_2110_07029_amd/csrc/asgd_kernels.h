@@ -53,7 +53,6 @@ hipError_t launch_gather_fwd(bool use_bf16, const CsrDev& x, const CsrDev* y, co
 // ---- stable LSD radix sort of (key, position) -----------------------------
 constexpr int SORT_CHUNK = 1024;   // keys per workgroup
 constexpr int SORT_MAX_BITS = 11;  // digit width limit per pass
-constexpr int SORT_SCAN_CHUNKS = 48;  // chunks from which the scatter's offsets have a launch of their own
 int sort_blocks(int n);
 // One pass over the digit (key >> shift) & (2^nbits - 1): keys_in / vals_in (null: the
 // positions) to keys_out / vals_out.

@@ -11,12 +11,14 @@
 //             the chunk from 64-lane ballots (lanes with the same digit in one wave),
 //             per-wave running counts, then a prefix over the four waves; keys land
 //             at offset + rank.
-// Summing in the scatter reads (chunks)^2 rows of counts, which beside the output layer's
-// launches, on the few CUs and registers these leave, costs more than it saves from about
-// SORT_SCAN_CHUNKS on: from there a launch of its own (scan, one workgroup) forms the offsets.
-// us per step with the sort the longest chain, summing in the scatter | in a launch: 61,000
-// keys 151 | 134, 79,000 172 | 145, 120,000 186 | 142; 46,000 keys (45 chunks) 109.0 | 110.1
-// and 139 | 132, 28,000 113 | 121 and 120 | 115.
+// Every workgroup that sums reads all chunks' counts (up to 4 KB per chunk), which beside the
+// output layer's launches, on the few CUs and registers these leave, costs more than it saves
+// from about SORT_SCAN_COUNTS on: from there a launch of its own (scan, one workgroup) forms the
+// offsets.  us per step, summing in the scatter | in a launch, one model by itself and three in
+// turn: 79,000 keys of 20 bits (10-bit digits, 79,000 counts) L = 100,000 128 | 132, 113 | 110;
+// 120,000 keys of 20 bits L = 100,000 190 | 136, 142 | 138, L = 30,000 142 | 126, 100 | 99;
+// 87,000 keys of 17 bits (44,000 counts) 99 | 101, 88 | 91; 72,000 keys of 15 bits (18,000
+// counts) three in turn 113 | 116; 46,000 keys of 20 bits (46,000 counts) 109 | 110.
 // hist and scatter size their LDS by the pass's digit width (dynamic LDS, 4 << bits
 // and 12 << bits bytes), not by the widest digit: a narrow pass then fits on a CU
 // beside the output-layer kernels of the other stream.
@@ -123,6 +125,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_sort_scan(const int32_t* __res
     }
   }
 }
+
+constexpr int SORT_SCAN_COUNTS = 48 << 10;  // (chunk, digit) counts
 
 // offs: the scan's offsets, or null: this workgroup forms its own from hist.
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(SortJob j, int nblk, const int32_t* __restrict__ hist,
@@ -276,7 +280,7 @@ hipError_t launch_sort(const SortPlan& plan, int32_t* hist, hipStream_t st) {
     const int32_t* offs = nullptr;
     hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(SORT_THREADS), (size_t)4 << j.nbits, st, j.keys_in, j.n, j.shift,
                        j.nbits, nblk, hist);
-    if (nblk >= SORT_SCAN_CHUNKS) {
+    if (nblk << j.nbits >= SORT_SCAN_COUNTS) {
       int32_t* o = hist + ((size_t)nblk << SORT_MAX_BITS);
       hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(SCAN_THREADS), 0, st, hist, nblk, 1 << j.nbits, o);
       offs = o;

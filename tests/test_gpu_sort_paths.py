@@ -1,5 +1,5 @@
 """The feature sort in its three forms (inside the output layer's launches, two launches per
-pass, three from 48 chunks of 1,024 keys) and the step on one stream and on two: the touched
+pass, three from 49,152 (chunk, digit) counts on) and the step on one stream and on two: the touched
 rows bit for bit, and the whole step's W1 update against the oracle."""
 import numpy as np
 import pytest
@@ -38,12 +38,13 @@ def dataset(F, L, B, nnz, seed):
     return wl, synth.Dataset(wl, x, y)
 
 
-# F 2,000: one pass; 3,000 / 100,000 / 2^21: two passes of 6 / 9 / 11 bits.  Entries: around a
-# chunk of 512 or 1,024, where pass 0 starts to leave pass 1's counts (16,384), at 48 chunks
-# (47 x 1,024 = 48,128), at the 16-bit counters' limit, where the step goes from one stream to two, and at 128
-# chunks
+# F 2,000: one pass; 3,000 / 100,000 / 600,000 / 2^21: two passes of 6 / 9 / 10 / 11 bits.  Entries:
+# around a chunk of 512 or 1,024, where pass 0 starts to leave pass 1's counts (16,384), where the
+# offsets get their own launch (47 | 48 chunks of 10 bits, 95 | 96 of 9, 23 | 24 of 11), and at the
+# 16-bit counters' limit, where the step goes from one stream to two
 @pytest.mark.parametrize("F,nnz", [(2_000, 511), (3_000, 512), (100_000, 513), (100_000, 1_025), (100_000, 16_383), (2_500, 16_384), (1 << 21, 18_600),
-                                   (100_000, 48_128), (3_000, 48_129), (100_000, 49_152), (100_000, 49_153), (100_000, 65_535), (3_000, 65_536),
+                                   (600_000, 48_128), (600_000, 48_129), (100_000, 97_280), (100_000, 97_281), (1 << 21, 23_552),
+                                   (1 << 21, 23_553), (3_000, 131_073), (100_000, 49_152), (100_000, 49_153), (100_000, 65_535), (3_000, 65_536),
                                    (100_000, 65_537), (2_000, 131_072),
                                    (100_000, 131_073)])
 def test_touched_rows_and_w1_update(F, nnz):
