@@ -39,20 +39,20 @@ FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 PMC_TRAFFIC = {
     ("wide-label", 256, "out_bwd"): dict(
         sources=('csrc/k_out_bwd.hip', 'csrc/aux_dev.h', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
-        fetch_kib=169865.5, write_kib=337663.1),
+        sha256="739bb00e51ebb218b9bf5bca131dfcb7b1d71eed52ddb23b85730b62f3a3f533",
+        fetch_kib=169854.1, write_kib=337663.1),
     ("wide-label", 1024, "out_bwd"): dict(
         sources=('csrc/k_out_bwd.hip', 'csrc/aux_dev.h', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
-        fetch_kib=177892.1, write_kib=338237.3),
+        sha256="739bb00e51ebb218b9bf5bca131dfcb7b1d71eed52ddb23b85730b62f3a3f533",
+        fetch_kib=177950.5, write_kib=338249.3),
     ("wide-feature", 128, "out_bwd"): dict(
         sources=('csrc/k_out_bwd.hip', 'csrc/aux_dev.h', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="b532a81e00e19e35b8963f93feb5d311b3122d906f4a05b916f8c8927687a23f",
-        fetch_kib=52272.6, write_kib=103524.0),
+        sha256="739bb00e51ebb218b9bf5bca131dfcb7b1d71eed52ddb23b85730b62f3a3f533",
+        fetch_kib=52272.2, write_kib=103524.0),
     ("elastic", 4, "merge"): dict(
         sources=('csrc/k_merge.hip', 'csrc/asgd_dev.h', 'csrc/asgd_kernels.h'),
-        sha256="c895a649d5cee7beeed44a8dd0c4fc327f1e8af60498452bbdc54a8b9c966e38",
-        fetch_kib=1216912.6, write_kib=2028091.2),
+        sha256="2ebde60fef4d821699c4e26d91d3f0fa0abe521cae7ed28e78eb8a2610f2df2c",
+        fetch_kib=1216911.7, write_kib=2028091.3),
 }
 
 
